@@ -538,155 +538,115 @@ struct Adj14 {
     kb.t2 += T(2) * (Cmb[0] + Cmb[3] + Cmb[5]);
   }
 
-  // hyperbola(zeta, rest) reverse
-  template <class T> MX_HD static void hyperbola_vjp(T zeta, T rest, T hb, T& zetab, T& restb) {
-    // the partials are formed in locals and added once at the end (no branch writes through
-    // the references, which keeps both callers' accumulators in registers)
-    T X = zeta * zeta + rest;
-    T zb = hb, rb = T(0);
-    if (X > T(0)) {
-      T sX = msqrt(X);
-      T Xb = T(0);
-      if (zeta >= T(0)) {
-        sqrt_vjp(X, sX, hb, Xb);
-      } else {
-        T den = sX - zeta;
-        T h = mdiv(rest, den);
-        T iden = mrcp(den);
-        rb = hb * iden;
-        T denb = -hb * h * iden;
-        sqrt_vjp(X, sX, denb, Xb);
-        zb = -denb;
-      }
-      zb += T(2) * zeta * Xb;
-      rb += Xb;
-    }
-    zetab += zb;
-    restb += rb;
-  }
-
-  // wavespeeds<d>(k, ud) -> (lmin, lmax): kb, udb
+  // wavespeeds<d>(k, ud) -> (lmin, lmax): kb, udb.  The forward part repeats sigma_fit and
+  // wave_pair expression by expression, so that a caller that has just evaluated them shares it.
+  // A clamped square root (argument not positive) carries no derivative.
   template <int d, class T>
   MX_HD static void wavespeeds_vjp(const S::Core<T>& k, T ud, T kws, T lminb, T lmaxb, CoreB<T>& kb,
                                    T& udb) {
     constexpr int t1i = (d == 0) ? 1 : 0;
     constexpr int t2i = (d == 2) ? 1 : 2;
+    (void)ud;
     // forward, kept
-    bool sw_clamp = !(k.sb < T(1));
-    T sw = sw_clamp ? T(1) : k.sb;
-    T Pdd_raw = k.Ph[sidx(d, d)];
-    bool Pclamp = !(Pdd_raw > T(0));
-    T Pdd = Pclamp ? T(0) : Pdd_raw;
-    T qd = k.qh[d];
-    T qt2 = k.qh[t1i] * k.qh[t1i] + k.qh[t2i] * k.qh[t2i];
-    T qt = msqrt(qt2);
-    T alpha = T(0.6) * Pdd * Pdd - T(0.38) * Pdd + T(0.35);
-    T a = T(0), b = T(0), lP = T(0), ea = T(0), e14 = T(0), eb = T(0);
-    if (Pdd > T(0)) {
-      lP = mlog(Pdd);
-      ea = mexp(T(1.1) * lP - Pdd * Pdd);
-      a = T(1.4) * ea;
-      e14 = mexp(T(1.4) * lP);
-      eb = mexp(T(-0.5) * e14);
-      b = T(0.9) * Pdd * eb;
-    }
-    // byec(sw, Pdd)
-    T Carg = (T(3) - T(3) * sw) * Pdd;
-    bool Cclamp = !(Carg > T(0));
-    T Cc = Cclamp ? T(0) : msqrt(Carg);
-    T E = T(0.8) * Cc;
-    T rs = msqrt(sw);
-    T Barg = T(10) - T(16) * rs + T(6) * sw;
-    bool Bclamp = !(Barg > T(0));
-    T sBa = Bclamp ? T(0) : msqrt(Barg);
-    T B = T(5) - T(4) * rs + sBa;
-    T sB = msqrt(B);
-    T Y = B + E * E - T(2) * E * sB;
-    T twosw = T(2) * sw;
-    T pref = mdiv(a * sw + b, twosw);
-    T base = T(4) * sw * sw * Y + qt * qt * T(0.1);
-    T zmax = qd + qt * alpha;
-    T zmin = -qd + qt * alpha;
-    T rmax = T(-0.8) * zmax * sw * Cc + base;
-    T rmin = T(-0.8) * zmin * sw * Cc + base;
-    T hmax = hyperbola(zmax, rmax);
-    T hmin = hyperbola(zmin, rmin);
-    T Lmax = pref * hmax + E;
-    T Lmin = pref * hmin + E;
-    // reverse: lmax = ud + kws Lmax c ; lmin = ud - kws Lmin c
+    const T isb = mrcp(k.sb), rsb = msqrt_pos(k.sb);
+    SigmaFit<T> f;
+    sigma_fit(k.sb, rsb, isb, f);
+    const bool sw_clamp = !(k.sb < T(1));
+    const T sw = T(0.5) * f.sw2, r = cmin(rsb, T(1));
+    const T Pdd_raw = k.Ph[sidx(d, d)];
+    const bool Pclamp = !(Pdd_raw > T(0));
+    const T P = cmax(Pdd_raw, T(0));
+    const T qd = k.qh[d];
+    const T qt = msqrt_pos(k.qh[t1i] * k.qh[t1i] + k.qh[t2i] * k.qh[t2i]);
+    const T alpha = T(0.6) * P * P - T(0.38) * P + T(0.35);
+    T a, b, P04;
+    fit_ab(P, a, b, P04);
+    const T Carg = T(3) * f.om * P;
+    const T C = msqrt_pos(Carg);
+    const T E = T(0.8) * C;
+    const T pref = T(0.5) * (a + b * f.isw);
+    const T kc = kws * k.c;
+    const T dBE = f.sB - E;
+    const T D = f.sw2 * dBE;
+    const T g = T(0.5) * f.sw2 * E;
+    const T aq = tabs(qd), w = qt * alpha;
+    const T base = D * D + T(0.1) * (qt * qt);
+    const T zp = w + aq, zn = w - aq;
+    const T Xp = zp * (zp - g) + base;
+    const T sp = msqrt_pos(Xp);
+    const T hp = zp + sp;
+    const T rest = base - zn * g;
+    const T Xn = zn * zn + rest;
+    const T sX = msqrt_pos(Xn);
+    const T sn = sX + tabs(zn);
+    const bool npos = zn >= T(0);
+    const T hn = npos ? sn : mdiv(rest, sn);
+    const bool fwd = qd >= T(0);
+    const T Lp = pref * hp + E, Ln = pref * hn + E;
+    // reverse: lmax = ud + kc Lmax ; lmin = ud - kc Lmin
     udb += lmaxb + lminb;
-    T Lmaxb = lmaxb * kws * k.c;
-    T Lminb = -lminb * kws * k.c;
-    kb.c += lmaxb * kws * Lmax - lminb * kws * Lmin;
-    T prefb = Lmaxb * hmax + Lminb * hmin;
-    T hmaxb = Lmaxb * pref, hminb = Lminb * pref;
-    T Eb = Lmaxb + Lminb;
-    T zmaxb = T(0), rmaxb = T(0), zminb = T(0), rminb = T(0);
-    hyperbola_vjp(zmax, rmax, hmaxb, zmaxb, rmaxb);
-    hyperbola_vjp(zmin, rmin, hminb, zminb, rminb);
-    T baseb = rmaxb + rminb;
-    T swb = T(0), Ccb = T(0), qtb = T(0), alphab = T(0), qdb = T(0);
-    zmaxb += rmaxb * T(-0.8) * sw * Cc;
-    swb += rmaxb * T(-0.8) * zmax * Cc;
-    Ccb += rmaxb * T(-0.8) * zmax * sw;
-    zminb += rminb * T(-0.8) * sw * Cc;
-    swb += rminb * T(-0.8) * zmin * Cc;
-    Ccb += rminb * T(-0.8) * zmin * sw;
-    // zmax = qd + qt alpha ; zmin = -qd + qt alpha
-    qdb += zmaxb - zminb;
-    qtb += (zmaxb + zminb) * alpha;
-    alphab += (zmaxb + zminb) * qt;
-    // base = 4 sw^2 Y + 0.1 qt^2
-    swb += baseb * T(8) * sw * Y;
-    T Yb = baseb * T(4) * sw * sw;
-    qtb += baseb * T(0.2) * qt;
-    // pref = (a sw + b) / (2 sw)
-    T itw = mrcp(twosw);
-    T ab = prefb * sw * itw;
-    T bb = prefb * itw;
-    swb += prefb * (a - T(2) * pref) * itw;
-    // Y = B + E^2 - 2 E sB
-    T Bb = Yb;
-    Eb += Yb * (T(2) * E - T(2) * sB);
-    T sBb = -Yb * T(2) * E;
-    sqrt_vjp(B, sB, sBb, Bb);
-    // B = 5 - 4 rs + sBa
-    T rsb = -T(4) * Bb;
-    T sBab = Bb;
-    T Bargb = T(0);
-    if (!Bclamp) sqrt_vjp(Barg, sBa, sBab, Bargb);
-    rsb += -T(16) * Bargb;
-    swb += T(6) * Bargb;
-    sqrt_vjp(sw, rs, rsb, swb);
-    // E = 0.8 Cc ; Cc = sqrt((3 - 3 sw) Pdd)
-    Ccb += T(0.8) * Eb;
-    T Cargb = T(0);
-    if (!Cclamp) sqrt_vjp(Carg, Cc, Ccb, Cargb);
-    swb += -T(3) * Pdd * Cargb;
-    T Pddb = (T(3) - T(3) * sw) * Cargb;
-    // a, b
-    if (Pdd > T(0)) {
-      // b = 0.9 Pdd eb ; eb = exp(-0.5 e14) ; e14 = exp(1.4 lP)
-      Pddb += bb * T(0.9) * eb;
-      T ebb = bb * T(0.9) * Pdd;
-      T e14b = ebb * eb * T(-0.5);
-      T lPb = e14b * e14 * T(1.4);
-      // a = 1.4 ea ; ea = exp(1.1 lP - Pdd^2)
-      T eab = ab * T(1.4);
-      T argb = eab * ea;
-      lPb += argb * T(1.1);
-      Pddb += -argb * T(2) * Pdd;
-      Pddb += mdiv(lPb, Pdd);
+    const T Lmaxb = lmaxb * kc, Lminb = -lminb * kc;
+    kb.c += kws * (lmaxb * (fwd ? Lp : Ln) - lminb * (fwd ? Ln : Lp));
+    const T Lpb = fwd ? Lmaxb : Lminb, Lnb = fwd ? Lminb : Lmaxb;
+    const T prefb = Lpb * hp + Lnb * hn;
+    const T hpb = Lpb * pref, hnb = Lnb * pref;
+    T Eb = Lpb + Lnb;
+    // hp = zp + sqrt(Xp), Xp = zp (zp - g) + base
+    T Xpb = T(0);
+    if (Xp > T(0)) Xpb = mdiv(hpb, T(2) * sp);
+    const T zpb = hpb + Xpb * (T(2) * zp - g);
+    // hn = sn (zn >= 0) or rest / sn, sn = sqrt(Xn) + |zn|, Xn = zn^2 + rest, rest = base - zn g
+    T snb = hnb, restb = T(0);
+    if (!npos) {
+      restb = mdiv(hnb, sn);
+      snb = -restb * hn;
     }
-    // alpha = 0.6 Pdd^2 - 0.38 Pdd + 0.35
-    Pddb += alphab * (T(1.2) * Pdd - T(0.38));
-    // qt = sqrt(qt2)
-    T qt2b = T(0);
-    sqrt_vjp(qt2, qt, qtb, qt2b);
-    kb.qh[t1i] += qt2b * T(2) * k.qh[t1i];
-    kb.qh[t2i] += qt2b * T(2) * k.qh[t2i];
-    kb.qh[d] += qdb;
-    if (!Pclamp) kb.Ph[sidx(d, d)] += Pddb;
+    T Xnb = T(0);
+    if (Xn > T(0)) Xnb = mdiv(snb, T(2) * sX);
+    restb += Xnb;
+    const T znb = (npos ? snb : -snb) + T(2) * zn * Xnb - restb * g;
+    const T gb = -Xpb * zp - restb * zn;
+    const T baseb = Xpb + restb;
+    // g = sw E ; base = D^2 + 0.1 qt^2 ; D = 2 sw (sB - E)
+    T swb = gb * E;
+    Eb += gb * sw;
+    const T Db = T(2) * D * baseb;
+    T qtb = T(0.2) * qt * baseb;
+    swb += T(2) * dBE * Db;
+    const T sBb = f.sw2 * Db;
+    Eb -= sBb;
+    // zp = w + |qd| ; zn = w - |qd| ; w = qt alpha
+    const T wb = zpb + znb, aqb = zpb - znb;
+    kb.qh[d] += fwd ? aqb : -aqb;
+    qtb += wb * alpha;
+    T Pb = wb * qt * (T(1.2) * P - T(0.38));
+    // pref = (a + b / sw) / 2
+    const T ab = T(0.5) * prefb, bb = ab * f.isw;
+    swb -= ab * b * f.isw * f.isw;
+    // E = 0.8 sqrt(3 (1 - sw) P)
+    if (Carg > T(0)) {
+      const T Cb = mdiv(T(0.4) * Eb, C) * T(3);
+      swb -= Cb * P;
+      Pb += Cb * f.om;
+    }
+    // sB = sqrt(B), B = 5 - 4 r + sqrt(2 (1 - r)(5 - 3 r)), r = sqrt(sw)
+    const T Bb = mdiv(sBb, T(2) * f.sB);
+    T rb = T(-4) * Bb;
+    const T Ba = T(2) * (T(1) - r) * (T(5) - T(3) * r);
+    if (Ba > T(0)) rb += mdiv(Bb * (T(6) * r - T(8)), msqrt_pos(Ba));
+    swb += mdiv(rb, T(2) * r);
+    // a = 1.4 P^1.1 exp(-P^2) ; b = 0.9 P exp(-P^1.4 / 2)
+    if (P > T(0)) {
+      const T iP = mrcp(P);
+      Pb += ab * a * (T(1.1) * iP - T(2) * P) + bb * b * (iP - T(0.7) * P04);
+    }
+    // qt = |transverse q|
+    if (qt > T(1e-144)) {
+      const T s = mdiv(qtb, qt);
+      kb.qh[t1i] += s * k.qh[t1i];
+      kb.qh[t2i] += s * k.qh[t2i];
+    }
+    if (!Pclamp) kb.Ph[sidx(d, d)] += Pb;
     if (!sw_clamp) kb.sb += swb;
   }
 

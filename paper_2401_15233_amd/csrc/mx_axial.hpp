@@ -232,11 +232,84 @@ struct Sys14A {
     lmin = ud - kws * Lmin * k.c;
   }
 
+  // dimensionless state of the FP64 flux and wave speeds (the formulas stand at Sys14::Norm;
+  // with a diagonal P* the products with z = h / P*_xx need no division)
+  template <class T> struct Norm {
+    T trP, pT, T0, ic, kc, Ph[3], h, P2[3], t2;
+    SigmaBar<T> s;
+  };
+  template <class T> MX_HD static void norm(const T* W, T sigma_lim, T kws, Norm<T>& n) {
+    n.trP = W[2] + W[3] + W[4];
+    const T p = n.trP * T(1.0 / 3.0);
+    const T ip = mrcp(p);
+    n.T0 = p * mrcp(W[0]);
+    n.pT = p * n.T0;
+    n.ic = mrsqrt(n.T0);
+    const T ic2 = W[0] * ip;
+    n.kc = kws * (n.T0 * n.ic);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) { n.Ph[m] = W[2 + m] * ip; n.P2[m] = n.Ph[m] * n.Ph[m]; }
+    n.h = W[5] * ip;
+    const T t1 = n.Ph[0] + n.Ph[1] + n.Ph[2];
+    n.t2 = n.P2[0] + n.P2[1] + n.P2[2];
+    const T D = n.h * (n.h * mrcp(n.Ph[0])) * ic2;
+    sigma_bar(T(2) * n.t2 + t1 * t1 - W[6] * (ic2 * ip), D, n.t2, sigma_lim, n.s);
+  }
+  template <class T> MX_HD static void speeds(const Norm<T>& n, T ux, T& lmin, T& lmax) {
+    SigmaFit<T> f;
+    sigma_fit(n.s.sb, n.s.rsb, n.s.isb, f);
+    wave_pair<false>(f, cmax(n.Ph[0], T(0)), n.h * n.ic, T(0), ux, n.kc, lmin, lmax);
+  }
+
   template <int d, class T>
   MX_HD static void face_terms(const T* W, T sigma_lim, T kws, T* U, T* F, T& lmin, T& lmax) {
-    Core<T> k;
+    static_assert(d == 0, "flows along x only");
+    Norm<T> n;
+    norm(W, sigma_lim, kws, n);
+    const T rho = W[0], ux = W[1], Pxx = W[2], q = W[5];
+    const T a = n.Ph[0], A = n.P2[0];
+    const T v = q * mrcp(T(2) * A + n.t2);
+    const T isb = n.s.isb;
+    const T vs = v * isb;
+    // v z (P*^2)_xx = v h P*_xx, so the three terms of Q_xxl z_l are equal
+    const T R = T(3) * (vs * (a * n.h)) + (T(2) * (T(1) - n.s.sb) * n.pT * A + T(3) * n.T0 * Pxx);
+    const T det = a * n.Ph[1] * n.Ph[2];
+    const T Wq = v * (T(24) * n.t2 - T(54) + T(28) * det + ((T(12) * n.t2 - T(72)) * a + T(60) * A));
+    const T hs = n.h * isb;
+    const T S = T(3) * v * (hs * hs) + n.T0 * (T(6) * n.s.rsb * q + (T(1) - n.s.rsb) * Wq);
+    const T Qx = T(3) * (v * A);
+
+    const T uu = ux * ux;
+    const T e = rho * uu + n.trP;
+    const T Pu = Pxx * ux;
+    const T s = Pu + q;
+    U[0] = rho;
+    U[1] = rho * ux;
+    U[2] = U[1] * ux + Pxx;
+    U[3] = W[3];
+    U[4] = W[4];
+    U[5] = e * ux + (s + Pu);
+    U[6] = uu * (e + n.trP) + (T(4) * (ux * s) + W[6]);
+    const T m = T(2) * Pu + q;
+    const T Qu = Qx * ux;
+    const T Rq = R + Qu;
+    F[0] = U[1];
+    F[1] = U[2];
+    F[2] = ux * U[2] + (T(2) * Pu + Qx);
+    F[3] = ux * W[3] + v * n.P2[1];
+    F[4] = ux * W[4] + v * n.P2[2];
+    F[5] = ux * U[5] + (ux * m + (uu * Pxx + (Rq + Qu)));
+    F[6] = ux * U[6] + (T(2) * uu * m + (T(4) * (ux * Rq) + S));
+    speeds(n, ux, lmin, lmax);
+  }
+
+  // U, F_d and the wave speeds of a face state in single precision (the FP32 setting)
+  template <int d>
+  MX_HD static void face_terms_fp32(const float* W, float sigma_lim, float kws, float* U, float* F, float& lmin,
+                                    float& lmax) {
+    Core<float> k;
     core(W, sigma_lim, k);
-    T Qd[3], Rd[1], Sd;
+    float Qd[3], Rd[1], Sd;
     closure_dir<d>(k, Qd, Rd, Sd);
     flux<d>(W, Qd, Rd, Sd, F);
     prim_to_cons(W, U);
@@ -252,10 +325,10 @@ struct Sys14A {
   }
 
   template <int d, class T> MX_HD static T cell_lambda(const T* W, T sigma_lim, T kws) {
-    Core<T> k;
-    core(W, sigma_lim, k);
+    Norm<T> n;
+    norm(W, sigma_lim, kws, n);
     T lmin, lmax;
-    wavespeeds<d>(k, W[1], kws, lmin, lmax);
+    speeds(n, W[1], lmin, lmax);
     return tmax(tabs(lmin), tabs(lmax));
   }
 

@@ -31,6 +31,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cmath>
+#include <type_traits>
 
 namespace mx {
 
@@ -60,22 +61,26 @@ template <> MX_HD float tabs<float>(float a) { return __builtin_fabsf(a); }
 #endif
 
 // FP64 square root, reciprocal and quotient.  On the device: the hardware reciprocal /
-// reciprocal-square-root seed (single-precision accurate) refined by Newton-Raphson -- two
-// steps of r <- r + r (1 - b r) for 1/b, then one residual correction of the quotient; for the
-// square root two steps of the coupled iteration on g ~ sqrt(a), h ~ 1/(2 sqrt(a)) with
-// r = 1/2 - g h, then one residual correction -- about 1 ulp, in fewer instructions than the
-// correctly rounded sequences.  The arguments of the step (densities, pressures, determinants,
-// positive sums) are positive and far from the exponent range's ends; sqrt(0) = 0 is kept, and
-// a negative, zero-divisor or non-finite argument still gives a non-finite result, which the
+// reciprocal-square-root seed (measured on 4M samples: 4.6e-8 and 5.2e-8 relative) refined to
+// the last bit.  1/b: one third-order step r <- r + r (e + e^2), e = 1 - b r (error e^3).  The
+// quotient: one second-order step of the reciprocal (1e-15), then a residual correction of
+// a r, which squares that error.  The square root: one step of the coupled iteration on
+// g ~ sqrt(a), h ~ 1/(2 sqrt(a)) (1e-15), then a residual correction of g.  Each gives the
+// correctly rounded result on those samples (1.11e-16 relative at most), as the sequences with
+// one more iteration did that stood here before, in one (1/b), two (a/b) and three (sqrt)
+// instructions less.  The arguments of the step (densities, pressures, determinants, positive
+// sums) are positive and far from the exponent range's ends; sqrt(0) = 0 is kept, and a
+// negative, zero-divisor or non-finite argument still gives a non-finite result, which the
 // step's state check reports.  On the host: the IEEE operations.
+//   mrsqrt      1/sqrt(a), a > 0 (1.4e-16 relative)
+//   msqrt_pos   sqrt(max(a, 1e-290)): an argument that may round to zero or below; no select
+//   cmax, cmin  maximum / minimum with a value that is never NaN (a NaN first operand gives
+//               it, as the compare and select of tmax and tmin do): one instruction for three
 #if defined(__HIP_DEVICE_COMPILE__)
 MX_HD double msqrt(double a) {
   const double y = __builtin_amdgcn_rsq(a);
   double g = a * y, h = 0.5 * y;
-  double r = __builtin_fma(-g, h, 0.5);
-  g = __builtin_fma(g, r, g);
-  h = __builtin_fma(h, r, h);
-  r = __builtin_fma(-g, h, 0.5);
+  const double r = __builtin_fma(-g, h, 0.5);
   g = __builtin_fma(g, r, g);
   h = __builtin_fma(h, r, h);
   const double d = __builtin_fma(-g, g, a);
@@ -83,24 +88,45 @@ MX_HD double msqrt(double a) {
   return a == 0.0 ? a : s;
 }
 MX_HD double mrcp(double b) {
-  double r = __builtin_amdgcn_rcp(b);
+  const double r = __builtin_amdgcn_rcp(b);
   double e = __builtin_fma(-b, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  e = __builtin_fma(-b, r, 1.0);
+  e = __builtin_fma(e, e, e);
   return __builtin_fma(r, e, r);
 }
 MX_HD double mdiv(double a, double b) {
-  const double r = mrcp(b);
+  double r = __builtin_amdgcn_rcp(b);
+  r = __builtin_fma(r, __builtin_fma(-b, r, 1.0), r);
   const double q = a * r;
   return __builtin_fma(__builtin_fma(-b, q, a), r, q);
+}
+MX_HD double mrsqrt(double a) {
+  const double y = __builtin_amdgcn_rsq(a);
+  const double e = __builtin_fma(-(a * y), y, 1.0);
+  return __builtin_fma(__builtin_fma(0.375, e, 0.5) * e, y, y);
+}
+MX_HD double cmax(double a, double b) { return __builtin_fmax(a, b); }
+MX_HD double cmin(double a, double b) { return __builtin_fmin(a, b); }
+MX_HD double msqrt_pos(double x) {
+  const double a = cmax(x, 1e-290);
+  const double y = __builtin_amdgcn_rsq(a);
+  double g = a * y, h = 0.5 * y;
+  const double r = __builtin_fma(-g, h, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  return __builtin_fma(__builtin_fma(-g, g, a), h, g);
 }
 #else
 MX_HD double msqrt(double a) { return sqrt(a); }
 MX_HD double mrcp(double b) { return 1.0 / b; }
 MX_HD double mdiv(double a, double b) { return a / b; }
+MX_HD double mrsqrt(double a) { return 1.0 / sqrt(a); }
 #endif
 template <class T> MX_HD T mrcp(T b) { return T(1) / b; }
 template <class T> MX_HD T mdiv(T a, T b) { return a / b; }
+template <class T> MX_HD T mrsqrt(T a) { return T(1) / msqrt(a); }
+template <class T> MX_HD T cmax(T a, T b) { return tmax(a, b); }
+template <class T> MX_HD T cmin(T a, T b) { return tmin(a, b); }
+template <class T> MX_HD T msqrt_pos(T a) { return msqrt(tmax(a, T(1e-290))); }
 MX_HD double mexp(double a) { return exp(a); }
 MX_HD double mlog(double a) { return log(a); }
 // single precision: the hardware square root / exponential / logarithm (about 1 ulp)
@@ -174,6 +200,128 @@ template <class T> MX_HD BYEC<T> byec(T sw, T Pdd) {
   r.B = T(5) - T(4) * rs + msqrt(tmax(T(10) - T(16) * rs + T(6) * sw, T(0)));
   r.Y = r.B + r.E * r.E - T(2) * r.E * msqrt(r.B);
   return r;
+}
+
+// The two factors of the wave-speed fit that depend on the normal pressure alone,
+// a = 1.4 P^1.1 exp(-P^2) and b = 0.9 P exp(-P^1.4 / 2), zero for P <= 0.
+// P04 = P^0.4 (their derivatives need it).
+template <class T> MX_HD void fit_ab(T P, T& a, T& b, T& P04) {
+  a = T(0); b = T(0); P04 = T(0);
+  if (P > T(0)) {
+    T lP = mlog(P);
+    P04 = mexp(T(0.4) * lP);
+    a = T(1.4) * mexp(T(1.1) * lP - P * P);
+    b = T(0.9) * P * mexp(T(-0.5) * (P * P04));
+  }
+}
+#if defined(__HIP_DEVICE_COMPILE__)
+// On the device, FP64: no logarithm and two exponentials instead of three.  u = P^-0.1 from
+// the single-precision logarithm and exponential units; P u^10 = 1 + d with |d| < 1e-5, so
+//   P^0.1 = P u^9 (1 + d)^-0.9,   P^0.4 = P u^6 (1 + d)^-0.6
+// with both powers of 1 + d to second order (the next term is below 1e-16).  The
+// exponentials: argument k ln 2 + r, |r| <= 0.347, a polynomial of degree 11 in r (interpolated
+// at the Chebyshev points of (e^r - 1 - r) / r^2, 1.6e-17 relative).  For exp(-P^2) the
+// reduction subtracts k ln 2 (its upper part of 38 bits, so that the product is exact) from
+// the unrounded square.  Against 80-bit evaluation on 4M samples: a 6.8e-16 at most and
+// 1.2e-16 on average, b 1.1e-15 and 1.0e-16 (the logarithm and exponentials of the math
+// library in the formulas above: 4.2e-15, 4.0e-16 and 1.2e-15, 1.1e-16, part of it the rounding
+// of the exponents 1.1 and 1.4).  P is at most 3 for a positive definite pressure tensor; above
+// 32 a is zero and b below 1e-26, so the clamp changes nothing that reaches a wave speed.
+MX_HD double exp_reduced(double k, double r) {
+  double p = 2.5100472505694996e-08;
+  p = __builtin_fma(p, r, 2.7620201591031547e-07);
+  p = __builtin_fma(p, r, 2.7557268275905696e-06);
+  p = __builtin_fma(p, r, 2.4801521057868204e-05);
+  p = __builtin_fma(p, r, 0.00019841269863171557);
+  p = __builtin_fma(p, r, 0.0013888888917367081);
+  p = __builtin_fma(p, r, 0.008333333333330039);
+  p = __builtin_fma(p, r, 0.041666666666623824);
+  p = __builtin_fma(p, r, 0.16666666666666669);
+  p = __builtin_fma(p, r, 0.5);
+  return __builtin_ldexp(1.0 + __builtin_fma(r * r, p, r), (int)k);
+}
+MX_HD void fit_ab(double Pin, double& a, double& b, double& P04) {
+  const double P = cmin(Pin, 32.0);
+  const float pf = __builtin_fmaxf((float)P, 1e-30f);
+  const double u = (double)__builtin_amdgcn_exp2f(-0.1f * __builtin_amdgcn_logf(pf));
+  const double u2 = u * u, u4 = u2 * u2, u6 = u4 * u2, u8 = u4 * u4, u9 = u8 * u, u10 = u8 * u2;
+  const double d = __builtin_fma(P, u10, -1.0);
+  const double w9 = d * __builtin_fma(0.855, d, -0.9), w6 = d * __builtin_fma(0.48, d, -0.6);
+  const double PP = P * P;
+  const double v6 = __builtin_fma(u6, w6, u6);
+  const double P11 = PP * __builtin_fma(u9, w9, u9), P14 = PP * v6;
+  P04 = P * v6;
+  const double ka = __builtin_rint(PP * -1.4426950408889634);
+  double ra = __builtin_fma(-P, P, ka * -0x1.62e42fefa0000p-1);
+  ra = __builtin_fma(ka, -1.6465949582897082e-12, ra);
+  const double x = -0.5 * P14;
+  const double kb = __builtin_rint(x * 1.4426950408889634);
+  double rb = __builtin_fma(kb, -0.6931471805599453, x);
+  rb = __builtin_fma(kb, -2.3190468138462996e-17, rb);
+  a = 1.4 * P11 * exp_reduced(ka, ra);
+  b = 0.9 * P * exp_reduced(kb, rb);
+}
+#endif
+
+// The part of the wave-speed fit that depends on sigma_bar alone (rsb, isb: its square root and
+// reciprocal): 1 - sigma_w, 1/sigma_w, 2 sigma_w and sqrt(B), sigma_w = min(sigma_bar, 1).
+// 10 - 16 r + 6 r^2 = 2 (1 - r)(5 - 3 r) with r = sqrt(sigma_w).
+template <class T> struct SigmaFit { T om, isw, sw2, sB; };
+template <class T> MX_HD void sigma_fit(T sb, T rsb, T isb, SigmaFit<T>& f) {
+  const T sw = cmin(sb, T(1)), r = cmin(rsb, T(1));
+  f.om = T(1) - sw;
+  f.isw = cmax(isb, T(1));
+  f.sw2 = T(2) * sw;
+  f.sB = msqrt_pos(T(5) - T(4) * r + msqrt_pos(T(2) * (T(1) - r) * (T(5) - T(3) * r)));
+}
+
+// Both approximate wave speeds along one direction (Section 5.1) from the dimensionless normal
+// pressure P >= 0, normal and transverse heat flux; kc = k_ws c.  With Y = (sqrt(B) - E)^2 and
+// zeta = +-q_d + |q_t| alpha the fit is
+//   Lambda = pref (zeta + sqrt(zeta^2 - zeta sigma_w E + (2 sigma_w (sqrt(B) - E))^2 + q_t^2/10)) + E.
+// alpha > 0, so of the two zeta only the smaller can be negative, and only it needs the
+// cancellation-free form rest / (sqrt(X) - zeta): one division instead of two.
+template <bool TRANSVERSE, class T>
+MX_HD void wave_roots(const SigmaFit<T>& f, T pref, T E, T qd, T qt, T alpha, T ud, T kc, T& lmin, T& lmax) {
+  const T D = f.sw2 * (f.sB - E);
+  const T g = T(0.5) * f.sw2 * E;
+  const T aq = tabs(qd);
+  T base = D * D, zp = aq, zn = -aq;
+  if constexpr (TRANSVERSE) {
+    const T w = qt * alpha;
+    base = base + T(0.1) * (qt * qt);
+    zp = w + aq;
+    zn = w - aq;
+  }
+  const T hp = zp + msqrt_pos(zp * (zp - g) + base);
+  const T rest = base - zn * g;
+  const T sn = msqrt_pos(zn * zn + rest) + tabs(zn);
+  T hn = mdiv(rest, sn);
+  if constexpr (TRANSVERSE) hn = (zn >= T(0)) ? sn : hn;
+  const T Lp = pref * hp + E, Ln = pref * hn + E;
+  const bool fwd = qd >= T(0);
+  const T Lmax = fwd ? Lp : Ln, Lmin = fwd ? Ln : Lp;
+  lmax = ud + kc * Lmax;
+  lmin = ud - kc * Lmin;
+}
+template <bool TRANSVERSE, class T>
+MX_HD void wave_pair(const SigmaFit<T>& f, T P, T qd, T qt, T ud, T kc, T& lmin, T& lmax) {
+  T a, b, P04;
+  fit_ab(P, a, b, P04);
+  wave_roots<TRANSVERSE>(f, T(0.5) * (a + b * f.isw), T(0.8) * msqrt_pos(T(3) * f.om * P), qd, qt,
+                         T(0.6) * P * P - T(0.38) * P + T(0.35), ud, kc, lmin, lmax);
+}
+
+// sigma (sigma_root's two forms, the magnitude |A| + sqrt(X) shared), sigma_bar, its reciprocal
+// and square root
+template <class T> struct SigmaBar { T sig, sb, isb, rsb; };
+template <class T> MX_HD void sigma_bar(T A, T D, T t2, T sigma_lim, SigmaBar<T>& s) {
+  const T big = tabs(A) + msqrt(A * A + T(8) * (t2 * D));
+  const bool pos = A >= T(0);
+  s.sig = mdiv(pos ? big : T(2) * D, pos ? T(4) * t2 : big);
+  s.sb = cmax(s.sig, sigma_lim);
+  s.isb = mrcp(s.sb);
+  s.rsb = msqrt_pos(s.sb);
 }
 
 // ===================================================================== 14 moments
@@ -442,6 +590,13 @@ struct Sys14 {
   MX_HD static void wavespeeds(const Core<T>& k, T ud, T kws, T& lmin, T& lmax) {
     constexpr int t1i = (d == 0) ? 1 : 0;
     constexpr int t2i = (d == 2) ? 1 : 2;
+    if constexpr (!std::is_same<T, float>::value) {
+      SigmaFit<T> f;
+      sigma_fit(k.sb, msqrt_pos(k.sb), mrcp(k.sb), f);
+      wave_pair<true>(f, cmax(k.Ph[sidx(d, d)], T(0)), k.qh[d],
+                      msqrt_pos(k.qh[t1i] * k.qh[t1i] + k.qh[t2i] * k.qh[t2i]), ud, kws * k.c, lmin, lmax);
+      return;
+    }
     T sw = tmin(k.sb, T(1));
     T Pdd = tmax(k.Ph[sidx(d, d)], T(0));
     T qd = k.qh[d];
@@ -464,12 +619,141 @@ struct Sys14 {
     lmin = ud - kws * Lmin * k.c;
   }
 
-  // U, F_d and the wave speeds of a face state
+  // Dimensionless state of the flux and wave speeds in FP64: P* = P / p, P*^2, h = q / p = c q*,
+  // z = P*^-1 h, T = p / rho, 1/c, sigma_bar.  Dimensional closing values follow from these
+  // without powers of c: with v = (2 P*^2 + tr(P*^2) I)^-1 q (v = 2 rho c^3 w),
+  //   Q_ijd = v_i (P*^2)_jd + v_j (P*^2)_id + v_d (P*^2)_ij,
+  //   R_id  = (v_i (P* h)_d + v_d (P* h)_i + (v.z)(P*^2)_id) / sigma
+  //           + 2 (1 - sigma) p T (P*^2)_id + 3 T P_id,
+  //   S_d   = (v_d |P* z|^2 + 2 (v.z)(P* h)_d) / sigma^2
+  //           + T (6 sqrt(sigma) q_d + (1 - sqrt(sigma)) Wq),
+  // since P*^2 z = P* h, z.P*^2 z = h.h and tr P* = 3.  Wq is (2 t1^3 + 12 t3 - 2 t2 t1) w_d + ...
+  // with P*^3 and t3 = tr(P*^3) eliminated by the Cayley-Hamilton theorem:
+  //   Wq = (24 t2 - 54 + 28 det P*) v_d + (12 t2 - 72) (P* v)_d + 60 (P*^2 v)_d.
+  template <class T> struct Norm {
+    T trP, pT, T0, ic, kc, Ph[6], h[3], z[3], P2[6], t2, det;
+    SigmaBar<T> s;
+  };
+  template <class T> MX_HD static void norm(const T* W, T sigma_lim, T kws, Norm<T>& n) {
+    n.trP = W[4] + W[7] + W[9];
+    const T p = n.trP * T(1.0 / 3.0);
+    const T ip = mrcp(p);
+    n.T0 = p * mrcp(W[0]);
+    n.pT = p * n.T0;
+    n.ic = mrsqrt(n.T0);
+    const T ic2 = W[0] * ip;
+    n.kc = kws * (n.T0 * n.ic);
+#pragma unroll
+    for (int m = 0; m < 6; ++m) n.Ph[m] = W[4 + m] * ip;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) n.h[i] = W[10 + i] * ip;
+    symsq(n.Ph, n.P2);
+    const T t1 = n.Ph[0] + n.Ph[3] + n.Ph[5];
+    n.t2 = n.P2[0] + n.P2[3] + n.P2[5];
+    T C[6], y[3];
+    n.det = symadj(n.Ph, C);
+    const T idet = mrcp(n.det);
+    symv(C, n.h, y);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) n.z[i] = y[i] * idet;
+    const T D = (n.h[0] * n.z[0] + n.h[1] * n.z[1] + n.h[2] * n.z[2]) * ic2;
+    sigma_bar(T(2) * n.t2 + t1 * t1 - W[13] * (ic2 * ip), D, n.t2, sigma_lim, n.s);
+  }
+  template <int d, class T>
+  MX_HD static void speeds(const Norm<T>& n, const SigmaFit<T>& f, T ud, T& lmin, T& lmax) {
+    constexpr int t1i = (d == 0) ? 1 : 0;
+    constexpr int t2i = (d == 2) ? 1 : 2;
+    wave_pair<true>(f, cmax(n.Ph[sidx(d, d)], T(0)), n.h[d] * n.ic,
+                    msqrt_pos(n.h[t1i] * n.h[t1i] + n.h[t2i] * n.h[t2i]) * n.ic, ud, n.kc, lmin, lmax);
+  }
+
+  // U, F_d and the wave speeds of a face state.  F is written with U: each flux is u_d U plus
+  // the terms in which d is a velocity's or a tensor's second index (u_j P_jd = (P u)_d).
   template <int d, class T>
   MX_HD static void face_terms(const T* W, T sigma_lim, T kws, T* U, T* F, T& lmin, T& lmax) {
-    Core<T> k;
+    Norm<T> n;
+    norm(W, sigma_lim, kws, n);
+    const T rho = W[0];
+    const T* u = W + 1;
+    const T* P = W + 4;
+    const T* q = W + 10;
+    T M[6], Ma[6], v[3];
+#pragma unroll
+    for (int m = 0; m < 6; ++m) M[m] = T(2) * n.P2[m];
+    M[0] = M[0] + n.t2; M[3] = M[3] + n.t2; M[5] = M[5] + n.t2;
+    const T idm = mrcp(symadj(M, Ma));
+    symv(Ma, q, v);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[i] = v[i] * idm;
+    const T vz = v[0] * n.z[0] + v[1] * n.z[1] + v[2] * n.z[2];
+    const T hh = n.h[0] * n.h[0] + n.h[1] * n.h[1] + n.h[2] * n.h[2];
+    T Phh[3];
+    symv(n.Ph, n.h, Phh);
+    const T isb = n.s.isb;
+    T Q[6], R[3], vs[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = i; j < 3; ++j)
+        Q[sidx(i, j)] = v[i] * n.P2[sidx(j, d)] + v[j] * n.P2[sidx(i, d)] + v[d] * n.P2[sidx(i, j)];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) vs[i] = v[i] * isb;
+    const T k2 = vz * isb + T(2) * (T(1) - n.s.sb) * n.pT;
+    const T T3 = T(3) * n.T0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      R[i] = vs[i] * Phh[d] + vs[d] * Phh[i] + k2 * n.P2[sidx(i, d)] + T3 * P[sidx(i, d)];
+    const T n1 = n.Ph[sidx(d, 0)] * v[0] + n.Ph[sidx(d, 1)] * v[1] + n.Ph[sidx(d, 2)] * v[2];
+    const T n2 = n.P2[sidx(d, 0)] * v[0] + n.P2[sidx(d, 1)] * v[1] + n.P2[sidx(d, 2)] * v[2];
+    const T Wq = (T(24) * n.t2 - T(54) + T(28) * n.det) * v[d] + (T(12) * n.t2 - T(72)) * n1 + T(60) * n2;
+    const T S = (v[d] * hh + T(2) * vz * Phh[d]) * (isb * isb) +
+                n.T0 * (T(6) * n.s.rsb * q[d] + (T(1) - n.s.rsb) * Wq);
+
+    const T ud = u[d];
+    const T uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+    const T e = rho * uu + n.trP;
+    T Pu[3], s[3], Qu[3], Rq[3];
+    symv(P, u, Pu);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) s[i] = Pu[i] + q[i];
+    U[0] = rho;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) U[1 + i] = rho * u[i];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = i; j < 3; ++j) U[4 + sidx(i, j)] = U[1 + i] * u[j] + P[sidx(i, j)];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) U[10 + i] = e * u[i] + (s[i] + Pu[i]);
+    U[13] = uu * (e + n.trP) + T(4) * (u[0] * s[0] + u[1] * s[1] + u[2] * s[2]) + W[13];
+    const T m = T(2) * Pu[d] + q[d];
+    symv(Q, u, Qu);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) Rq[i] = R[i] + Qu[i];
+    F[0] = U[1 + d];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) F[1 + i] = ud * U[1 + i] + P[sidx(i, d)];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = i; j < 3; ++j)
+        F[4 + sidx(i, j)] = ud * U[4 + sidx(i, j)] + (u[i] * P[sidx(j, d)] + (u[j] * P[sidx(i, d)] + Q[sidx(i, j)]));
+#pragma unroll
+    for (int i = 0; i < 3; ++i) F[10 + i] = ud * U[10 + i] + (u[i] * m + (uu * P[sidx(i, d)] + (Rq[i] + Qu[i])));
+    F[13] = ud * U[13] + (T(2) * uu * m + (T(4) * (u[0] * Rq[0] + u[1] * Rq[1] + u[2] * Rq[2]) + S));
+
+    SigmaFit<T> f;
+    sigma_fit(n.s.sb, n.s.rsb, isb, f);
+    speeds<d>(n, f, ud, lmin, lmax);
+  }
+
+  // U, F_d and the wave speeds of a face state in single precision (the FP32 setting)
+  template <int d>
+  MX_HD static void face_terms_fp32(const float* W, float sigma_lim, float kws, float* U, float* F, float& lmin,
+                                    float& lmax) {
+    Core<float> k;
     core(W, sigma_lim, k);
-    T Qd[6], Rd[3], Sd;
+    float Qd[6], Rd[3], Sd;
     closure_dir<d>(k, Qd, Rd, Sd);
     flux<d>(W, Qd, Rd, Sd, F);
     prim_to_cons(W, U);
@@ -487,23 +771,27 @@ struct Sys14 {
 
   // max(|lambda_min|, |lambda_max|) along d at a cell state
   template <int d, class T> MX_HD static T cell_lambda(const T* W, T sigma_lim, T kws) {
-    Core<T> k;
-    core(W, sigma_lim, k);
+    Norm<T> n;
+    norm(W, sigma_lim, kws, n);
+    SigmaFit<T> f;
+    sigma_fit(n.s.sb, n.s.rsb, n.s.isb, f);
     T lmin, lmax;
-    wavespeeds<d>(k, W[1 + d], kws, lmin, lmax);
+    speeds<d>(n, f, W[1 + d], lmin, lmax);
     return tmax(tabs(lmin), tabs(lmax));
   }
 
-  // 2D CFL rate Lambda_x / dx + Lambda_y / dy of a cell state (one closure core for both
-  // directions; the same values as cell_lambda<0> / dx + cell_lambda<1> / dy)
+  // 2D CFL rate Lambda_x / dx + Lambda_y / dy of a cell state (one dimensionless state and
+  // sigma part for both directions)
   template <class T>
   MX_HD static T cell_rate2d(const T* W, T sigma_lim, T kws, T dx, T dy) {
-    Core<T> k;
-    core(W, sigma_lim, k);
+    Norm<T> n;
+    norm(W, sigma_lim, kws, n);
+    SigmaFit<T> f;
+    sigma_fit(n.s.sb, n.s.rsb, n.s.isb, f);
     T a, b, c, d;
-    wavespeeds<0>(k, W[1], kws, a, b);
-    wavespeeds<1>(k, W[2], kws, c, d);
-    return tmax(tabs(a), tabs(b)) / dx + tmax(tabs(c), tabs(d)) / dy;
+    speeds<0>(n, f, W[1], a, b);
+    speeds<1>(n, f, W[2], c, d);
+    return mdiv(tmax(tabs(a), tabs(b)), dx) + mdiv(tmax(tabs(c), tabs(d)), dy);
   }
 
   template <class T> MX_HD static T sigma(const T* W) {
@@ -650,9 +938,50 @@ struct Sys5 {
     lmin = u - kws * Lmin * k.c;
   }
 
+  // dimensionless state in FP64: q*, T = P / rho, k_ws c, sigma_bar
+  template <class T> struct Norm { T qh, T0, kc; SigmaBar<T> s; };
+  template <class T> MX_HD static void norm(const T* W, T sigma_lim, T kws, Norm<T>& n) {
+    const T ip = mrcp(W[2]);
+    n.T0 = W[2] * mrcp(W[0]);
+    const T ic = mrsqrt(n.T0);
+    n.kc = kws * (n.T0 * ic);
+    n.qh = W[3] * ip * ic;
+    sigma_bar(T(3) - W[4] * (W[0] * ip * ip), n.qh * n.qh, T(1), sigma_lim, n.s);
+  }
+  template <class T> MX_HD static void speeds(const Norm<T>& n, T u, T& lmin, T& lmax) {
+    SigmaFit<T> f;
+    sigma_fit(n.s.sb, n.s.rsb, n.s.isb, f);
+    // the 5-moment fit: pref = 1 / (2 sigma_w), P* = 1, no transverse heat flux
+    wave_roots<false>(f, T(0.5) * f.isw, T(0.8) * msqrt_pos(T(3) * f.om), n.qh, T(0), T(0), u, n.kc, lmin, lmax);
+  }
+
+  // U, F and the wave speeds of a face state (F is u U plus the terms above the previous
+  // moment's); closing moment s = q T (q*^2 / sigma^2 + 10 - 8 sqrt(sigma))
   template <int d, class T>
   MX_HD static void face_terms(const T* W, T sigma_lim, T kws, T* U, T* F, T& lmin, T& lmax) {
-    Core<T> k;
+    Norm<T> n;
+    norm(W, sigma_lim, kws, n);
+    const T u = W[1], P = W[2], q = W[3], r = W[4];
+    const T qs = n.qh * n.s.isb;
+    const T s = q * n.T0 * (qs * qs + T(10) - T(8) * n.s.rsb);
+    const T u2 = u * u;
+    U[0] = W[0];
+    U[1] = W[0] * u;
+    U[2] = U[1] * u + P;
+    U[3] = u * (U[2] + T(2) * P) + q;
+    U[4] = u * (u * (U[2] + T(5) * P) + T(4) * q) + r;
+    F[0] = U[1];
+    F[1] = U[2];
+    F[2] = U[3];
+    F[3] = U[4];
+    F[4] = u * U[4] + (u2 * (T(4) * (u * P) + T(6) * q) + (T(4) * (u * r) + s));
+    speeds(n, u, lmin, lmax);
+  }
+
+  template <int d>
+  MX_HD static void face_terms_fp32(const float* W, float sigma_lim, float kws, float* U, float* F, float& lmin,
+                                    float& lmax) {
+    Core<float> k;
     core(W, sigma_lim, k);
     flux(W, closing_s(k), F);
     prim_to_cons(W, U);
@@ -666,10 +995,10 @@ struct Sys5 {
   }
 
   template <int d, class T> MX_HD static T cell_lambda(const T* W, T sigma_lim, T kws) {
-    Core<T> k;
-    core(W, sigma_lim, k);
+    Norm<T> n;
+    norm(W, sigma_lim, kws, n);
     T lmin, lmax;
-    wavespeeds(k, W[1], kws, lmin, lmax);
+    speeds(n, W[1], lmin, lmax);
     return tmax(tabs(lmin), tabs(lmax));
   }
 

@@ -65,6 +65,12 @@ MX_HD bool faces_admissible(const T* Wm, const T* Wc, const T* Wp, T phi) {
   return SYS::admissible(Wu) && SYS::admissible(Wd);
 }
 
+// Interface flux of two face states: HLL (Davis speeds) or Rusanov, in one form
+//   Fh = cL FL + cR FR + d (UR - UL).
+// HLL: S- = min(SL, 0), S+ = max(SR, 0), cL = S+ / (S+ - S-), cR = -S- / (S+ - S-),
+// d = S- S+ / (S+ - S-): the upwind fluxes of the supersonic cases follow from S- = 0 or
+// S+ = 0 without a branch or a select per component.  Rusanov: cL = cR = 1/2, d = -a*/2.  A NaN
+// wave speed of either side reaches every component through d.
 template <class SYS, int D, class T>
 MX_HD void face_flux(const T* WL, const T* WR, T sigma_lim, T kws, int flux_kind, T* Fh) {
   constexpr int NV = SYS::NV;
@@ -72,25 +78,20 @@ MX_HD void face_flux(const T* WL, const T* WR, T sigma_lim, T kws, int flux_kind
   T lminL, lmaxL, lminR, lmaxR;
   SYS::template face_terms<D>(WL, sigma_lim, kws, UL, FL, lminL, lmaxL);
   SYS::template face_terms<D>(WR, sigma_lim, kws, UR, FR, lminR, lmaxR);
+  T cL, cR, d;
   if (flux_kind == 0) {
-    T SL = tmin(lminL, lminR), SR = tmax(lmaxL, lmaxR);
-    if (SL >= T(0)) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Fh[v] = FL[v];
-    } else if (SR <= T(0)) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Fh[v] = FR[v];
-    } else {
-      T inv = mrcp(SR - SL);
-      T SLR = SL * SR;
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Fh[v] = (SR * FL[v] - SL * FR[v] + SLR * (UR[v] - UL[v])) * inv;
-    }
+    const T Sm = cmin(tmin(lminL, lminR), T(0)), Sp = cmax(tmax(lmaxL, lmaxR), T(0));
+    const T inv = mrcp(Sp - Sm);
+    cL = Sp * inv;
+    cR = -Sm * inv;
+    d = Sm * cL + T(0) * (lminL + lminR);
   } else {
-    T am = tmax(tmax(tabs(lminL), tabs(lmaxL)), tmax(tabs(lminR), tabs(lmaxR)));
-#pragma unroll
-    for (int v = 0; v < NV; ++v) Fh[v] = T(0.5) * (FL[v] + FR[v]) - T(0.5) * am * (UR[v] - UL[v]);
+    const T am = tmax(tmax(tabs(lminL), tabs(lmaxL)), tmax(tabs(lminR), tabs(lmaxR)));
+    cL = cR = T(0.5);
+    d = T(-0.5) * am;
   }
+#pragma unroll
+  for (int v = 0; v < NV; ++v) Fh[v] = cL * FL[v] + (cR * FR[v] + d * (UR[v] - UL[v]));
 }
 
 // Mixed precision (Section 3.3: the dimensionless closure is robust in single precision).
@@ -165,7 +166,9 @@ MX_HD void face_flux_mixed(const double* WL, const double* WR, double sigma_lim,
 
 // Single precision (the FP32 setting): the closure, wave speeds, physical fluxes and the HLL /
 // Rusanov combination of both face states in FP32, with no FP64 re-evaluation; the face
-// states arrive in FP64 and the interface flux leaves in FP64.
+// states arrive in FP64 and the interface flux leaves in FP64.  It keeps the sequence of
+// operations it always had (Core, closure_dir, flux, prim_to_cons, wavespeeds): rearranged as
+// the FP64 path is, its results would move by single-precision rounding.
 template <class SYS, int D>
 MX_HD void face_flux_fp32(const double* WL, const double* WR, double sigma_lim, double kws,
                           int flux_kind, double* Fh) {
@@ -173,7 +176,29 @@ MX_HD void face_flux_fp32(const double* WL, const double* WR, double sigma_lim, 
   float wl[NV], wr[NV], f[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) { wl[v] = (float)WL[v]; wr[v] = (float)WR[v]; }
-  face_flux<SYS, D, float>(wl, wr, (float)sigma_lim, (float)kws, flux_kind, f);
+  float UL[NV], FL[NV], UR[NV], FR[NV];
+  float lminL, lmaxL, lminR, lmaxR;
+  SYS::template face_terms_fp32<D>(wl, (float)sigma_lim, (float)kws, UL, FL, lminL, lmaxL);
+  SYS::template face_terms_fp32<D>(wr, (float)sigma_lim, (float)kws, UR, FR, lminR, lmaxR);
+  if (flux_kind == 0) {
+    float SL = tmin(lminL, lminR), SR = tmax(lmaxL, lmaxR);
+    if (SL >= 0.0f) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) f[v] = FL[v];
+    } else if (SR <= 0.0f) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) f[v] = FR[v];
+    } else {
+      float inv = mrcp(SR - SL);
+      float SLR = SL * SR;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) f[v] = (SR * FL[v] - SL * FR[v] + SLR * (UR[v] - UL[v])) * inv;
+    }
+  } else {
+    float am = tmax(tmax(tabs(lminL), tabs(lmaxL)), tmax(tabs(lminR), tabs(lmaxR)));
+#pragma unroll
+    for (int v = 0; v < NV; ++v) f[v] = 0.5f * (FL[v] + FR[v]) - 0.5f * am * (UR[v] - UL[v]);
+  }
 #pragma unroll
   for (int v = 0; v < NV; ++v) Fh[v] = (double)f[v];
 }

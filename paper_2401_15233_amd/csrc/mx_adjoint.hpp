@@ -1086,25 +1086,10 @@ struct Adj14 {
   // sets vstar (-1 when phi is a constant 0 or 1, i.e. carries no derivative).
   template <class T>
   MX_HD static T limiter_select(const T* Wm, const T* Wc, const T* Wp, int kind, int fallback, int& vstar) {
-    constexpr int NV = 14;
-    T sc[NV];
-    S::scales(Wc, sc);
-    T num = T(1), den = T(1);
-    vstar = -1;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      T a = Wc[v] - Wm[v];
-      T b = Wp[v] - Wc[v];
-      T aa = tabs(a), ab = tabs(b);
-      T fn, fd;
-      int var = -1;
-      if (aa + ab <= T(NEUTRAL_EPS) * sc[v]) { fn = T(1); fd = T(1); }
-      else if (a * b <= T(0)) { fn = T(0); fd = T(1); }
-      else if (kind == 0) { fn = T(2) * tmin(aa, ab); fd = aa + ab; var = v; }
-      else { fn = T(2) * a * b; fd = a * a + b * b; var = v; }
-      if (fn * den < num * fd) { num = fn; den = fd; vstar = var; }
-    }
-    T phi = (den == T(1)) ? num : mdiv(num, den);
+    T num, den;
+    limiter_ratio<S>(Wm, Wc, Wp, num, den, vstar);
+    T phi = limiter_of_ratio(num, den, kind);
+    if (!(phi > T(0))) vstar = -1;
     if (fallback && phi > T(0)) {
       if (!faces_admissible<S>(Wm, Wc, Wp, phi)) { phi = T(0); vstar = -1; }
     }

@@ -75,13 +75,13 @@ struct Sys14A {
   template <class T> MX_HD static void scales(const T* W, T* sc) {
     T rho = tabs(W[0]);
     T p = tabs(W[2] + W[3] + W[4]) * T(1.0 / 3.0);
-    T c = msqrt(mdiv(p, rho));
-    T c3 = rho * c * c * c;
+    T T0 = p * mrcp(rho);
+    T c = T0 * mrsqrt(T0);
     sc[0] = rho;
     sc[1] = c;
     sc[2] = sc[3] = sc[4] = p;
-    sc[5] = c3;
-    sc[6] = c3 * c;
+    sc[5] = p * c;
+    sc[6] = p * T0;
   }
 
   // components odd under reflection of x

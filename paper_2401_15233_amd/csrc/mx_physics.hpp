@@ -400,19 +400,19 @@ struct Sys14 {
     return spd_ok(rho, P);
   }
 
-  // natural scale of each primitive (rho, c, p, rho c^3, rho c^4) for the neutral-variable
+  // natural scale of each primitive (rho, c, p, rho c^3 = p c, rho c^4 = p^2 / rho) for the neutral-variable
   // test of the common limiter
   template <class T> MX_HD static void scales(const T* W, T* sc) {
     T rho = tabs(W[0]);
     T p = tabs(W[4] + W[7] + W[9]) * T(1.0 / 3.0);
-    T c = msqrt(mdiv(p, rho));
-    T c3 = rho * c * c * c;
+    T T0 = p * mrcp(rho);
+    T c = T0 * mrsqrt(T0);
     sc[0] = rho;
     sc[1] = sc[2] = sc[3] = c;
 #pragma unroll
     for (int k = 4; k < 10; ++k) sc[k] = p;
-    sc[10] = sc[11] = sc[12] = c3;
-    sc[13] = c3 * c;
+    sc[10] = sc[11] = sc[12] = p * c;
+    sc[13] = p * T0;
   }
 
   // components odd under reflection of axis d
@@ -871,8 +871,9 @@ struct Sys5 {
   template <class T> MX_HD static void scales(const T* W, T* sc) {
     T rho = tabs(W[0]);
     T p = tabs(W[2]);
-    T c = msqrt(mdiv(p, rho));
-    sc[0] = rho; sc[1] = c; sc[2] = p; sc[3] = rho * c * c * c; sc[4] = sc[3] * c;
+    T T0 = p * mrcp(rho);
+    T c = T0 * mrsqrt(T0);
+    sc[0] = rho; sc[1] = c; sc[2] = p; sc[3] = p * c; sc[4] = p * T0;
   }
 
   MX_HD static constexpr bool odd(int v, int) { return v == 1 || v == 3; }

@@ -91,13 +91,13 @@ struct Sys14P {
   template <class T> MX_HD static void scales(const T* W, T* sc) {
     T rho = tabs(W[0]);
     T p = tabs(W[3] + W[5] + W[6]) * T(1.0 / 3.0);
-    T c = msqrt(mdiv(p, rho));
-    T c3 = rho * c * c * c;
+    T T0 = p * mrcp(rho);
+    T c = T0 * mrsqrt(T0);
     sc[0] = rho;
     sc[1] = sc[2] = c;
     sc[3] = sc[4] = sc[5] = sc[6] = p;
-    sc[7] = sc[8] = c3;
-    sc[9] = c3 * c;
+    sc[7] = sc[8] = p * c;
+    sc[9] = p * T0;
   }
 
   // components odd under reflection of axis d (x or y)

@@ -91,6 +91,8 @@ struct maxent_solver {
   TapeState* tape = nullptr;
   int adj_mode = MAXENT_ADJ_EXACT;
   int asym = mx::ASYM_Z | mx::ASYM_Y;  // symmetry of the loaded state (set by the ingest)
+  bool us_dirty = false;                // a full 14-moment kernel has run: the planes that the
+                                        // reduced kernels leave out may be non-zero in U or Us
   bool reduced_on = true;               // maxent_set_reduced
   std::string err;
   // the 14-moment stage kernels carry only the moments the state's symmetry leaves non-zero:
@@ -345,6 +347,29 @@ static hipError_t run_cfl(maxent_solver* s) {
   return mx::launch_cfl(s->prob.system, s->prob.dim, c, s->stream);
 }
 
+static mx::IngestParams ingest_params(const maxent_solver* s, int repr, const double* src) {
+  mx::IngestParams g;
+  std::memset(&g, 0, sizeof(g));
+  g.src = src; g.U = s->U; g.repr = repr;
+  g.nx = s->prob.nx; g.ny = s->prob.ny; g.pitch = s->pitch;
+  g.dx = (s->prob.x1 - s->prob.x0) / s->prob.nx;
+  g.dy = s->prob.dim == 2 ? (s->prob.y1 - s->prob.y0) / s->prob.ny : 1.0;
+  g.sigma_lim = s->num.sigma_lim; g.kws = s->num.k_ws;
+  g.ctrl = s->ctrl;
+  return g;
+}
+
+// whether kernels of the solver's device may read or write the caller's buffer in place:
+// device memory of that device (anything else goes through the staging buffer and a copy)
+static bool local_pointer(const maxent_solver* s, const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == s->device;
+}
+
 static int read_ctrl(maxent_solver* s) {
   HIP_TRY(s, hipMemcpyAsync(s->ctrl_host, s->ctrl, sizeof(DevCtrl), hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(s, hipStreamSynchronize(s->stream));
@@ -378,7 +403,6 @@ static mx::BatchParams batch_params(maxent_solver* s) {
   p.act_inst = b->d_act_inst;
   p.act_tile0 = b->d_act_tile0;
   p.bctrl = b->d_ctrl;
-  p.cell_inst = b->d_cell_inst;
   p.bc_lo = s->prob.bc[0];
   p.bc_hi = s->prob.bc[1];
   p.tau_mode = s->prob.tau_mode;
@@ -393,14 +417,9 @@ static mx::BatchParams batch_params(maxent_solver* s) {
   return p;
 }
 
-// restore the per-instance records to t = 0 and reduce each instance's first CFL rate
-static int batch_reset(maxent_solver* s) {
+// the instance queue from the first CFL rates, which the ingest left in the instances' records
+static int batch_order(maxent_solver* s) {
   BatchState* b = s->batch;
-  HIP_TRY(s, hipMemcpyAsync(b->d_inst, b->init.data(), b->init.size() * sizeof(mx::BatchInst),
-                            hipMemcpyHostToDevice, s->stream));
-  mx::BatchParams p = batch_params(s);
-  p.Ub = s->U;
-  HIP_TRY(s, mx::launch_batch_cfl(p, b->total, s->stream));
   // instance queue: estimated work = cells x steps to t_end at the initial CFL rate
   HIP_TRY(s, hipMemcpyAsync(b->h_inst, b->d_inst, b->n_inst * sizeof(mx::BatchInst), hipMemcpyDeviceToHost,
                             s->stream));
@@ -433,21 +452,33 @@ extern "C" int maxent_init_state(maxent_solver* s, int repr, const double* src, 
     return fail(s, MAXENT_E_INVAL, "repr must be PRIMITIVE or CONSERVED");
   if (!std::isfinite(t0)) return fail(s, MAXENT_E_INVAL, "t0 must be finite");
   free_tape(s);
-  size_t flat = (size_t)s->nv * s->prob.nx * s->prob.ny * sizeof(double);
-  HIP_TRY(s, hipMemcpyAsync(s->stage, src, flat,
-                            src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
+  if (!src_on_device || !local_pointer(s, src)) {
+    const size_t flat = (size_t)s->nv * s->prob.nx * s->prob.ny * sizeof(double);
+    HIP_TRY(s, hipMemcpyAsync(s->stage, src, flat,
+                              src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
+    src = s->stage;
+  }
   HIP_TRY(s, mx::launch_ctrl_reset(s->ctrl, t0, s->stream));
-  HIP_TRY(s, mx::launch_ingest(s->prob.system, repr, s->stage, s->U, s->prob.nx, s->prob.ny,
-                               s->pitch, s->ctrl, s->stream));
+  mx::IngestParams g = ingest_params(s, repr, src);
+  if (BatchState* b = s->batch) {
+    // the instances' records at t = 0, their rates zero
+    HIP_TRY(s, hipMemcpyAsync(b->d_inst, b->init.data(), b->init.size() * sizeof(mx::BatchInst),
+                              hipMemcpyHostToDevice, s->stream));
+    g.cell_inst = b->d_cell_inst;
+    g.inst = b->d_inst;
+  }
+  HIP_TRY(s, mx::launch_ingest(s->prob.system, s->prob.dim, g, s->stream));
   if (s->batch) {
-    int rc = batch_reset(s);
+    int rc = batch_order(s);
     if (rc) return rc;
-  } else {
-    HIP_TRY(s, run_cfl(s));
   }
   // the reduced kernels never write the moments they leave out: the stage / ping-pong buffer
-  // starts from zeros there, so that a forward-Euler swap hands back a symmetric state
-  HIP_TRY(s, mx::launch_zero_planes(s->Us, s->plane, s->nv, s->stream));
+  // holds zeros there, so that a forward-Euler swap hands back a symmetric state (it starts so;
+  // only a full kernel writes those planes)
+  if (s->us_dirty) {
+    HIP_TRY(s, mx::launch_zero_planes(s->Us, s->plane, s->nv, s->stream));
+    s->us_dirty = false;
+  }
   int rc = read_ctrl(s);
   if (rc) return rc;
   s->asym = s->ctrl_host->asym;
@@ -473,6 +504,7 @@ static hipError_t enqueue_steps(maxent_solver* s, int n, double dt, double tau_r
   TapeState* tape = s->tape;
   const size_t field_bytes = (size_t)s->nv * s->plane * sizeof(double);
   const bool cfl_mode = !(dt > 0);
+  if (!s->reduced()) s->us_dirty = true;
   mx::StageParams p = stage_params(s, tau_ref);
   const int sys = s->prob.system, dim = s->prob.dim, ord = s->num.order;
   const double dx = (s->prob.x1 - s->prob.x0) / s->prob.nx;
@@ -604,13 +636,13 @@ extern "C" int maxent_step_noalloc(const maxent_problem* problem, const maxent_n
   t.ctrl = (DevCtrl*)base;
   t.U = U;
   t.Us = (double*)((unsigned char*)base + 256);
-  t.rate_valid = false;
   static_assert(sizeof(DevCtrl) <= 256, "the control block fits its scratch slot");
   // the control block starts from zero (a kernel, not a memset); the input state is checked
   // in place (conserved in, the same values out) and its first CFL rate reduced
+  t.rate_valid = true;
   e = mx::launch_ctrl_reset(t.ctrl, t0, t.stream);
   if (e == hipSuccess)
-    e = mx::launch_ingest(nv, MAXENT_CONSERVED, U, U, problem->nx, problem->ny, problem->nx, t.ctrl, t.stream);
+    e = mx::launch_ingest(nv, problem->dim, ingest_params(&t, MAXENT_CONSERVED, U), t.stream);
   // symmetry of a 14-moment state: read the ingest's flags, and give the scratch state zero
   // planes where a reduced kernel writes none
   if (e == hipSuccess && nv == 14) {
@@ -673,11 +705,12 @@ extern "C" int maxent_get_moments(maxent_solver* s, int repr, double* dst, int d
   size_t comps = (size_t)s->nv;
   if (repr == MAXENT_SIGMA) comps = 1;
   if (repr == MAXENT_CLOSING) comps = s->nv == 14 ? MAXENT_CLOSING_COMPONENTS_14 : 1;
-  size_t bytes = comps * cells * sizeof(double);
-  HIP_TRY(s, mx::launch_egress(s->prob.system, repr, s->U, s->stage, s->prob.nx, s->prob.ny,
+  const bool direct = dst_on_device && local_pointer(s, dst);
+  HIP_TRY(s, mx::launch_egress(s->prob.system, repr, s->U, direct ? dst : s->stage, s->prob.nx, s->prob.ny,
                                s->pitch, s->num.sigma_lim, s->stream));
-  HIP_TRY(s, hipMemcpyAsync(dst, s->stage, bytes,
-                            dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
+  if (!direct)
+    HIP_TRY(s, hipMemcpyAsync(dst, s->stage, comps * cells * sizeof(double),
+                              dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(s, hipStreamSynchronize(s->stream));
   return MAXENT_OK;
 }
@@ -833,14 +866,17 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
                               s->stream));
   // lambda <- dJ/dU_final
   const size_t flat = (size_t)s->nv * nx * ny * sizeof(double);
-  HIP_TRY(s, hipMemcpyAsync(s->stage, dJ_dU, flat,
-                            dJ_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
+  if (!dJ_on_device || !local_pointer(s, dJ_dU)) {
+    HIP_TRY(s, hipMemcpyAsync(s->stage, dJ_dU, flat,
+                              dJ_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
+    dJ_dU = s->stage;
+  }
   // planar run: planar-symmetric recorded states (the planar kernels ran them) and a
   // planar-symmetric dJ/dU keep the z-odd adjoint components at zero
   int nonplanar = 1;
   if (s->planar()) {
     HIP_TRY(s, mx::launch_ctrl_reset(t->actrl, 0.0, s->stream));
-    HIP_TRY(s, mx::launch_check_planar(s->stage, (long long)nx * ny, t->actrl, s->stream));
+    HIP_TRY(s, mx::launch_check_planar(dJ_dU, (long long)nx * ny, t->actrl, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&nonplanar, &t->actrl->asym, sizeof(int), hipMemcpyDeviceToHost,
                               s->stream));
   }
@@ -851,7 +887,7 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
   double* lamC = t->lam[2];
   if (pl)  // never written in a planar run: they start (and stay) zero
     for (double* l : {lamA, lamB, lamC}) HIP_TRY(s, mx::launch_zero_planes(l, s->plane, 14, s->stream));
-  HIP_TRY(s, mx::launch_pad_copy(s->stage, lamA, s->nv, nx, ny, s->pitch, 1, s->stream));
+  HIP_TRY(s, mx::launch_pad_copy(dJ_dU, lamA, s->nv, nx, ny, s->pitch, 1, s->stream));
   HIP_TRY(s, hipMemsetAsync(t->part, 0, (size_t)3 * mx::adjoint_update_blocks(nx, ny) * sizeof(double),
                             s->stream));
 
@@ -946,9 +982,11 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
   }
   HIP_TRY(s, mx::launch_adjoint_reduce(a, s->stream));
   if (dJ_dU0) {
-    HIP_TRY(s, mx::launch_pad_copy(lamA, s->stage, s->nv, nx, ny, s->pitch, 0, s->stream));
-    HIP_TRY(s, hipMemcpyAsync(dJ_dU0, s->stage, flat,
-                              dU0_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
+    const bool direct = dU0_on_device && local_pointer(s, dJ_dU0);
+    HIP_TRY(s, mx::launch_pad_copy(lamA, direct ? dJ_dU0 : s->stage, s->nv, nx, ny, s->pitch, 0, s->stream));
+    if (!direct)
+      HIP_TRY(s, hipMemcpyAsync(dJ_dU0, s->stage, flat,
+                                dU0_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
   }
   double g[3] = {0.0, 0.0, 0.0};
   HIP_TRY(s, hipMemcpyAsync(g, t->grad, sizeof(g), hipMemcpyDeviceToHost, s->stream));
@@ -1080,6 +1118,7 @@ extern "C" int maxent_create_batch(const maxent_problem* common, const maxent_nu
 // enqueue `steps` batched steps on stream st
 static hipError_t batch_enqueue(maxent_solver* s, int steps, hipStream_t st) {
   BatchState* b = s->batch;
+  if (!s->reduced()) s->us_dirty = true;
   mx::BatchParams p = batch_params(s);
   const int grid = b->wg_per_cu * b->n_cu;
   const bool mid = s->num.integrator == MAXENT_MIDPOINT;

@@ -329,23 +329,6 @@ void batch_stage_kernel(BatchParams p) {
   }
 }
 
-
-// CFL rate of every instance's current state (after init)
-template <class SYS>
-__global__ __launch_bounds__(256) void batch_cfl_kernel(BatchParams p, long long total) {
-  constexpr int NV = SYS::NV;
-  for (long long g = (long long)blockIdx.x * 256 + threadIdx.x; g < total;
-       g += (long long)gridDim.x * 256) {
-    int inst = p.cell_inst[g];
-    double U[NV], W[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) U[v] = p.Ub[v * p.plane + g];
-    SYS::cons_to_prim(U, W);
-    double r = SYS::template cell_lambda<0>(W, p.sigma_lim, p.kws);
-    atomicMax(&p.inst[inst].maxrate, (unsigned long long)__double_as_longlong(r));
-  }
-}
-
 template <class SYS, int PREC, int NT, int CPT>
 static hipError_t launch_bs(const BatchParams& p, int grid, hipStream_t s) {
   hipLaunchKernelGGL((batch_stage_kernel<SYS, 2, PREC, NT, CPT>), dim3(grid), dim3(NT), 0, s, p);
@@ -381,13 +364,6 @@ hipError_t launch_batch_finalize(BatchInst* in, const int* order, int n_inst, do
   if (stage_grid < 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL(batch_finalize_kernel, dim3(1), dim3(1024), 0, s, in, order, n_inst, cfl, tile_w,
                      act_inst, act_tile0, bc, stage_grid);
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_cfl(const BatchParams& p, long long total, hipStream_t s) {
-  long long g = (total + 255) / 256;
-  int grid = (int)(g > 8192 ? 8192 : g);
-  hipLaunchKernelGGL((batch_cfl_kernel<Sys14>), dim3(grid), dim3(256), 0, s, p, total);
   return hipGetLastError();
 }
 

@@ -33,7 +33,6 @@ struct BatchParams {
   const int* act_inst;           // instances that advance, in queue order
   const int* act_tile0;          // first work-list tile of each; [n_active] = n_tiles
   const BatchCtrl* bctrl;        // n_active and n_tiles of the current step
-  const int* cell_inst;          // instance of every cell (CFL initialisation)
   int bc_lo, bc_hi;
   int tau_mode;
   double rho_ref, T_ref;
@@ -54,6 +53,5 @@ hipError_t launch_batch_stage(int precision, bool reduced, int nt, int cpt, cons
 hipError_t launch_batch_finalize(BatchInst* in, const int* order, int n_inst, double cfl, int tile_w,
                                  int* act_inst, int* act_tile0, BatchCtrl* bc, int stage_grid,
                                  hipStream_t s);
-hipError_t launch_batch_cfl(const BatchParams& p, long long total, hipStream_t s);
 
 }  // namespace mx

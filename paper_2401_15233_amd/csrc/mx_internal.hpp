@@ -70,6 +70,20 @@ struct CflParams {
   DevCtrl* ctrl;
 };
 
+struct BatchInst;
+// src: unpadded [nv][ny][nx], primitive (repr 0) or conserved (1); U: padded [nv][ny][pitch]
+struct IngestParams {
+  const double* src;
+  double* U;
+  int repr;
+  int nx, ny, pitch;
+  double dx, dy;
+  double sigma_lim, kws;
+  DevCtrl* ctrl;
+  const int* cell_inst;    // batched tubes: the tube of every cell, and the tubes' records
+  BatchInst* inst;         // (their maxrate, zero before); null otherwise
+};
+
 // launchers (mx_kernels.hip)
 // reduced (14 moments): the state is symmetric and the stage carries only the moments that can
 // be non-zero -- 2D planar (u_z = P_xz = P_yz = q_z = 0; ten moments, Sys14P), 1D axial (also
@@ -84,9 +98,10 @@ hipError_t launch_ctrl_reset(DevCtrl* c, double t0, hipStream_t s);
 // P_yz, q_y, q_z) of a 14-moment field of `plane` doubles per plane (a kernel, no memset);
 // nothing for nv != 14
 hipError_t launch_zero_planes(double* U, long long plane, int nv, hipStream_t s);
-// src/dst: unpadded [nv][ny][nx]; U: padded [nv][ny][pitch]
-hipError_t launch_ingest(int system, int repr, const double* src, double* U, int nx, int ny,
-                         int pitch, DevCtrl* c, hipStream_t s);
+// loads a field into U, checks it, and reduces its CFL rate into ctrl->maxrate (or the tubes'
+// records); ctrl is reset before
+hipError_t launch_ingest(int system, int dim, const IngestParams& p, hipStream_t s);
+// dst: unpadded [components][ny][nx]
 // repr 0 primitive, 1 conserved, 2 sigma, 3 closing moments (19 values per 14-moment cell)
 hipError_t launch_egress(int system, int repr, const double* U, double* dst, int nx, int ny,
                          int pitch, double sigma_lim, hipStream_t s);

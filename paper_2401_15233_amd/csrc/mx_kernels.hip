@@ -15,7 +15,10 @@
 // The 2D tile is 16 x 15 cells for 256 threads: 255 x-faces and 256 y-faces, one of each
 // per thread.  The 1D tile is 60 cells for one 64-wide wavefront: cells plus halo fill the
 // wavefront exactly.
+#include <algorithm>
+
 #include "mx_internal.hpp"
+#include "mx_batch.hpp"
 #include "mx_physics.hpp"
 #include "mx_scheme.hpp"
 #include "mx_bc.hpp"
@@ -364,33 +367,59 @@ void stage_kernel(StageParams p) {
   }
 }
 
-// ------------------------------------------------------------------ CFL rate of a state
-template <class SYS, int DIM>
-__global__ __launch_bounds__(256) void cfl_kernel(CflParams p) {
-  constexpr int NV = SYS::NV;
+// ------------------------------------------------------------------ whole-field kernels
+// Cell k of an nx x ny field in a plane of row pitch `pitch`.  A field holds at most 2^31
+// cells, so the division is a 32-bit one, and a field without row padding needs none.
+__device__ __forceinline__ long long padded_index(unsigned k, unsigned nx, int ny, int pitch) {
+  if (ny == 1 || (unsigned)pitch == nx) return k;
+  const unsigned j = k / nx;
+  return (long long)j * pitch + (k - j * nx);
+}
+
+// Workgroups of a whole-field kernel: eight per CU (256 CUs), each striding over the field, so
+// that the reductions at their ends cost at most 2048 atomics.
+static int field_grid(long long n) { return (int)std::min<long long>((n + 255) / 256, 2048); }
+
+// maximum of a workgroup's rates (256 threads), then one atomic on the bit pattern
+__device__ __forceinline__ void block_max_rate(double rate, unsigned long long* maxrate) {
   __shared__ double sRed[4];
-  long long n = (long long)p.nx * p.ny;
-  double rate = 0.0;
-  for (long long c = (long long)blockIdx.x * 256 + threadIdx.x; c < n; c += (long long)gridDim.x * 256) {
-    int i = (int)(c % p.nx), j = (int)(c / p.nx);
-    long long off = (long long)j * p.pitch + i;
-    double U[NV], W[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) U[v] = p.U[v * p.plane + off];
-    SYS::cons_to_prim(U, W);
-    double r;
-    if constexpr (DIM == 1) r = SYS::template cell_lambda<0>(W, p.sigma_lim, p.kws);
-    else
-      r = SYS::cell_rate2d(W, p.sigma_lim, p.kws, p.dx, p.dy);
-    rate = fmax(rate, r);
-  }
   rate = wave_max(rate);
   if ((threadIdx.x & 63) == 0) sRed[threadIdx.x >> 6] = rate;
   __syncthreads();
   if (threadIdx.x == 0) {
-    double m = fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]));
-    atomicMax(&p.ctrl->maxrate, (unsigned long long)__double_as_longlong(m));
+    const double m = fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]));
+    atomicMax(maxrate, (unsigned long long)__double_as_longlong(m));
   }
+}
+
+// set bits of a status word, once: most wavefronts find them set already, and a load is
+// cheaper than queueing on one address (65536 wavefronts of a 2048 x 2048 field took 0.2 ms)
+__device__ __forceinline__ void or_status(int* word, int bits) {
+  if (bits && (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bits) != bits)
+    atomicOr(word, bits);
+}
+
+// ------------------------------------------------------------------ CFL rate of a state
+template <class SYS, int DIM>
+__device__ __forceinline__ double cell_rate(const double* W, double sigma_lim, double kws, double dx, double dy) {
+  if constexpr (DIM == 1) return SYS::template cell_lambda<0>(W, sigma_lim, kws);
+  else return SYS::cell_rate2d(W, sigma_lim, kws, dx, dy);
+}
+
+template <class SYS, int DIM>
+__global__ __launch_bounds__(256) void cfl_kernel(CflParams p) {
+  constexpr int NV = SYS::NV;
+  const unsigned n = (unsigned)p.nx * (unsigned)p.ny;
+  double rate = 0.0;
+  for (unsigned c = blockIdx.x * 256 + threadIdx.x; c < n; c += gridDim.x * 256) {
+    const long long off = padded_index(c, p.nx, p.ny, p.pitch);
+    double U[NV], W[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) U[v] = p.U[v * p.plane + off];
+    SYS::cons_to_prim(U, W);
+    rate = fmax(rate, cell_rate<SYS, DIM>(W, p.sigma_lim, p.kws, p.dx, p.dy));
+  }
+  block_max_rate(rate, &p.ctrl->maxrate);
 }
 
 // ------------------------------------------------------------------ time control
@@ -447,49 +476,73 @@ __global__ __launch_bounds__(256) void zero_planes_kernel(double* U, long long p
 }
 
 // ------------------------------------------------------------------ state in / out
-template <class SYS>
-__global__ void ingest_kernel(int repr, const double* src, double* U, int nx, int ny, int pitch,
-                              DevCtrl* c) {
+// Load a field: conserved moments, the checks of every cell, the symmetry of a 14-moment state
+// and the first CFL rate, in one pass (bound by HBM: the source read once, the state written
+// once).  The rate of a batch goes to each tube's own record: the lanes of a wavefront that
+// share a tube reduce among themselves first (nearly all wavefronts lie in one tube).
+template <class SYS, int DIM, bool BATCH>
+__global__ __launch_bounds__(256) void ingest_kernel(IngestParams p) {
   constexpr int NV = SYS::NV;
-  long long n = (long long)nx * ny;
-  long long plane = (long long)ny * pitch;
+  const unsigned n = (unsigned)p.nx * (unsigned)p.ny;
+  const long long plane = (long long)p.ny * p.pitch;
   int bad = 0, np = 0;
-  for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < n;
-       k += (long long)gridDim.x * blockDim.x) {
-    int i = (int)(k % nx), j = (int)(k / nx);
-    double A[NV], Uc[NV], W[NV];
+  double rate = 0.0;
+  // whole wavefronts stay in the loop (the batch reduces across their lanes)
+  for (unsigned w = blockIdx.x * 256 + (threadIdx.x & ~63u); w < n; w += gridDim.x * 256) {
+    const unsigned k = w + (threadIdx.x & 63);
+    const bool in = k < n;
+    double r = 0.0;
+    int inst = 0;
+    if (in) {
+      const long long off = padded_index(k, p.nx, p.ny, p.pitch);
+      double A[NV], Uc[NV], W[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) A[v] = src[v * n + k];
-    if (repr == 0) {
-      SYS::prim_to_cons(A, Uc);
+      for (int v = 0; v < NV; ++v) A[v] = p.src[(long long)v * n + k];
+      if (p.repr == 0) {
+        SYS::prim_to_cons(A, Uc);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) W[v] = A[v];
+        for (int v = 0; v < NV; ++v) W[v] = A[v];
+      } else {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Uc[v] = A[v];
+        SYS::cons_to_prim(Uc, W);
+      }
+      bool fin = true;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        fin = fin && isfinite(Uc[v]);
+        p.U[v * plane + off] = Uc[v];
+      }
+      if (!fin) bad |= ST_NONFINITE;
+      else if (!SYS::admissible(W)) bad |= ST_UNREALIZABLE;
+      // symmetry (14 moments): z-odd moments u_z, P_xz, P_yz, q_z and y-odd moments u_y, P_xy,
+      // P_yz, q_y exactly zero
+      if constexpr (NV == 14) {
+        if (Uc[3] != 0.0 || Uc[6] != 0.0 || Uc[8] != 0.0 || Uc[12] != 0.0) np |= ASYM_Z;
+        if (Uc[2] != 0.0 || Uc[5] != 0.0 || Uc[8] != 0.0 || Uc[11] != 0.0) np |= ASYM_Y;
+      }
+      r = fmax(cell_rate<SYS, DIM>(W, p.sigma_lim, p.kws, p.dx, p.dy), 0.0);
+      if constexpr (BATCH) inst = p.cell_inst[k];
+    }
+    if constexpr (BATCH) {
+      const int first = __builtin_amdgcn_readfirstlane(inst);   // lane 0 is inside the field
+      if (__all(!in || inst == first)) {
+        const double m = wave_max(r);
+        if ((threadIdx.x & 63) == 0) atomicMax(&p.inst[first].maxrate, (unsigned long long)__double_as_longlong(m));
+      } else if (in) {
+        atomicMax(&p.inst[inst].maxrate, (unsigned long long)__double_as_longlong(r));
+      }
     } else {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Uc[v] = A[v];
-      SYS::cons_to_prim(Uc, W);
-    }
-    bool fin = true;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      fin = fin && isfinite(Uc[v]);
-      U[v * plane + (long long)j * pitch + i] = Uc[v];
-    }
-    if (!fin) bad |= ST_NONFINITE;
-    else if (!SYS::admissible(W)) bad |= ST_UNREALIZABLE;
-    // symmetry (14 moments): z-odd moments u_z, P_xz, P_yz, q_z and y-odd moments u_y, P_xy,
-    // P_yz, q_y exactly zero
-    if constexpr (NV == 14) {
-      if (Uc[3] != 0.0 || Uc[6] != 0.0 || Uc[8] != 0.0 || Uc[12] != 0.0) np |= ASYM_Z;
-      if (Uc[2] != 0.0 || Uc[5] != 0.0 || Uc[8] != 0.0 || Uc[11] != 0.0) np |= ASYM_Y;
+      rate = fmax(rate, r);
     }
   }
   bad = wave_or(bad);
-  if ((threadIdx.x & 63) == 0 && bad) atomicOr(&c->status, bad);
+  if ((threadIdx.x & 63) == 0) or_status(&p.ctrl->status, bad);
   if constexpr (NV == 14) {
     np = wave_or(np);
-    if ((threadIdx.x & 63) == 0 && np) atomicOr(&c->asym, np);
+    if ((threadIdx.x & 63) == 0) or_status(&p.ctrl->asym, np);
   }
+  if constexpr (!BATCH) block_max_rate(rate, &p.ctrl->maxrate);
 }
 
 // Closing moments of a cell state (dimensional, at sigma_bar = max(sigma, sigma_lim)):
@@ -515,33 +568,35 @@ MX_HD void closing14(const double* W, double sigma_lim, double* out) {
   out[18] = S;
 }
 
-template <class SYS>
-__global__ void egress_kernel(int repr, const double* U, double* dst, int nx, int ny, int pitch,
-                              double sigma_lim) {
+// Read a field back in one representation (0 primitive, 1 conserved, 2 sigma, 3 closing
+// moments): one kernel each, so that none carries another's registers (one kernel for all four
+// spilled, and ran the plain copies at half the wavefronts).
+template <class SYS, int REPR>
+__global__ __launch_bounds__(256) void egress_kernel(const double* U, double* dst, int nx, int ny, int pitch,
+                                                     double sigma_lim) {
   constexpr int NV = SYS::NV;
-  long long n = (long long)nx * ny;
-  long long plane = (long long)ny * pitch;
-  for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < n;
-       k += (long long)gridDim.x * blockDim.x) {
-    int i = (int)(k % nx), j = (int)(k / nx);
+  const unsigned n = (unsigned)nx * (unsigned)ny;
+  const long long plane = (long long)ny * pitch;
+  for (unsigned k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
+    const long long off = padded_index(k, nx, ny, pitch);
     double Uc[NV], W[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Uc[v] = U[v * plane + (long long)j * pitch + i];
-    if (repr == 1) {
+    for (int v = 0; v < NV; ++v) Uc[v] = U[v * plane + off];
+    if constexpr (REPR == 1) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) dst[v * n + k] = Uc[v];
+      for (int v = 0; v < NV; ++v) dst[(long long)v * n + k] = Uc[v];
     } else {
       SYS::cons_to_prim(Uc, W);
-      if (repr == 0) {
+      if constexpr (REPR == 0) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) dst[v * n + k] = W[v];
-      } else if (repr == 2) {
+        for (int v = 0; v < NV; ++v) dst[(long long)v * n + k] = W[v];
+      } else if constexpr (REPR == 2) {
         dst[k] = SYS::sigma(W);
       } else if constexpr (NV == 14) {
         double c[NCLOSE14];
         closing14(W, sigma_lim, c);
 #pragma unroll
-        for (int m = 0; m < NCLOSE14; ++m) dst[m * n + k] = c[m];
+        for (int m = 0; m < NCLOSE14; ++m) dst[(long long)m * n + k] = c[m];
       } else {
         typename SYS::template Core<double> kc;
         SYS::core(W, sigma_lim, kc);
@@ -558,14 +613,14 @@ __global__ __launch_bounds__(256) void count_sigma_limited_kernel(const double* 
                                                                   int pitch, double sigma_lim,
                                                                   DevCtrl* c) {
   constexpr int NV = SYS::NV;
-  long long n = (long long)nx * ny;
-  long long plane = (long long)ny * pitch;
+  const unsigned n = (unsigned)nx * (unsigned)ny;
+  const long long plane = (long long)ny * pitch;
   int cnt = 0;
-  for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < n; k += (long long)gridDim.x * 256) {
-    int i = (int)(k % nx), j = (int)(k / nx);
+  for (unsigned k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
+    const long long off = padded_index(k, nx, ny, pitch);
     double Uc[NV], W[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Uc[v] = U[v * plane + (long long)j * pitch + i];
+    for (int v = 0; v < NV; ++v) Uc[v] = U[v * plane + off];
     SYS::cons_to_prim(Uc, W);
     cnt += (SYS::sigma(W) < sigma_lim) ? 1 : 0;
   }
@@ -611,9 +666,7 @@ hipError_t launch_stage(int system, int dim, int order, int precision, bool redu
 }
 
 hipError_t launch_cfl(int system, int dim, const CflParams& p, hipStream_t s) {
-  long long n = (long long)p.nx * p.ny;
-  int grid = (int)((n + 255) / 256);
-  if (grid > 4096) grid = 4096;
+  const int grid = field_grid((long long)p.nx * p.ny);
   if (system == 5) hipLaunchKernelGGL((cfl_kernel<Sys5, 1>), dim3(grid), dim3(256), 0, s, p);
   else if (dim == 1) hipLaunchKernelGGL((cfl_kernel<Sys14, 1>), dim3(grid), dim3(256), 0, s, p);
   else hipLaunchKernelGGL((cfl_kernel<Sys14, 2>), dim3(grid), dim3(256), 0, s, p);
@@ -644,33 +697,35 @@ hipError_t launch_zero_planes(double* U, long long plane, int nv, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t launch_ingest(int system, int repr, const double* src, double* U, int nx, int ny,
-                         int pitch, DevCtrl* c, hipStream_t s) {
-  long long n = (long long)nx * ny;
-  int grid = (int)((n + 255) / 256);
-  if (grid > 8192) grid = 8192;
-  if (system == 5) hipLaunchKernelGGL((ingest_kernel<Sys5>), dim3(grid), dim3(256), 0, s, repr, src, U, nx, ny, pitch, c);
-  else hipLaunchKernelGGL((ingest_kernel<Sys14>), dim3(grid), dim3(256), 0, s, repr, src, U, nx, ny, pitch, c);
+hipError_t launch_ingest(int system, int dim, const IngestParams& p, hipStream_t s) {
+  const int grid = field_grid((long long)p.nx * p.ny);
+  if (p.inst) hipLaunchKernelGGL((ingest_kernel<Sys14, 1, true>), dim3(grid), dim3(256), 0, s, p);
+  else if (system == 5) hipLaunchKernelGGL((ingest_kernel<Sys5, 1, false>), dim3(grid), dim3(256), 0, s, p);
+  else if (dim == 1) hipLaunchKernelGGL((ingest_kernel<Sys14, 1, false>), dim3(grid), dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((ingest_kernel<Sys14, 2, false>), dim3(grid), dim3(256), 0, s, p);
+  return hipGetLastError();
+}
+
+template <class SYS>
+static hipError_t launch_egress_t(int repr, const double* U, double* dst, int nx, int ny, int pitch,
+                                  double sigma_lim, hipStream_t s) {
+  const dim3 grid(field_grid((long long)nx * ny)), wg(256);
+  if (repr == 0) hipLaunchKernelGGL((egress_kernel<SYS, 0>), grid, wg, 0, s, U, dst, nx, ny, pitch, sigma_lim);
+  else if (repr == 1) hipLaunchKernelGGL((egress_kernel<SYS, 1>), grid, wg, 0, s, U, dst, nx, ny, pitch, sigma_lim);
+  else if (repr == 2) hipLaunchKernelGGL((egress_kernel<SYS, 2>), grid, wg, 0, s, U, dst, nx, ny, pitch, sigma_lim);
+  else hipLaunchKernelGGL((egress_kernel<SYS, 3>), grid, wg, 0, s, U, dst, nx, ny, pitch, sigma_lim);
   return hipGetLastError();
 }
 
 hipError_t launch_egress(int system, int repr, const double* U, double* dst, int nx, int ny,
                          int pitch, double sigma_lim, hipStream_t s) {
-  long long n = (long long)nx * ny;
-  int grid = (int)((n + 255) / 256);
-  if (grid > 8192) grid = 8192;
-  if (system == 5)
-    hipLaunchKernelGGL((egress_kernel<Sys5>), dim3(grid), dim3(256), 0, s, repr, U, dst, nx, ny, pitch, sigma_lim);
-  else
-    hipLaunchKernelGGL((egress_kernel<Sys14>), dim3(grid), dim3(256), 0, s, repr, U, dst, nx, ny, pitch, sigma_lim);
-  return hipGetLastError();
+  return system == 5 ? launch_egress_t<Sys5>(repr, U, dst, nx, ny, pitch, sigma_lim, s)
+                     : launch_egress_t<Sys14>(repr, U, dst, nx, ny, pitch, sigma_lim, s);
 }
 
 hipError_t launch_count_sigma_limited(int system, const double* U, int nx, int ny, int pitch,
                                       double sigma_lim, DevCtrl* c, hipStream_t s) {
-  long long n = (long long)nx * ny;
-  int grid = (int)((n + 255) / 256);
-  if (grid > 4096) grid = 4096;
+  const int grid = field_grid((long long)nx * ny);
   if (system == 5)
     hipLaunchKernelGGL((count_sigma_limited_kernel<Sys5>), dim3(grid), dim3(256), 0, s, U, nx, ny, pitch, sigma_lim, c);
   else

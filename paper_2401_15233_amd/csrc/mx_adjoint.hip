@@ -546,10 +546,6 @@ __global__ __launch_bounds__(ADJ_NT) void adj_reduce_kernel(const double* part, 
 }
 
 // ------------------------------------------------------------------ tape helpers
-__global__ void tape_dt_kernel(const DevCtrl* c, double* slot) {
-  if (threadIdx.x == 0) *slot = c->dt;
-}
-
 __global__ void pad_copy_kernel(const double* src, double* dst, int nv, int nx, int ny, int pitch,
                                 int to_padded) {
   const long long n = (long long)nx * ny;
@@ -594,25 +590,20 @@ hipError_t launch_adjoint_stage(int dim, int order, bool planar, AdjParams& a, h
   return order == 2 ? launch_adj_t<1, 2, false>(a, s) : launch_adj_t<1, 1, false>(a, s);
 }
 
-// nonzero z-odd component (3, 6, 8, 12) in a flat 14-moment field of n cells: ctrl->asym
+// nonzero z-odd component (3, 6, 8, 12) in a flat 14-moment field of n cells: ctrl->asym_z
 __global__ __launch_bounds__(256) void check_planar_kernel(const double* f, long long n, DevCtrl* c) {
   int np = 0;
   for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < n; k += (long long)gridDim.x * 256)
     np |= (f[3 * n + k] != 0.0 || f[6 * n + k] != 0.0 || f[8 * n + k] != 0.0 || f[12 * n + k] != 0.0);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) np |= __shfl_xor(np, o, 64);
-  if ((threadIdx.x & 63) == 0 && np) atomicOr(&c->asym, ASYM_Z);
+  if ((threadIdx.x & 63) == 0 && np) c->asym_z = 1;
 }
 
 hipError_t launch_check_planar(const double* f, long long n, DevCtrl* c, hipStream_t s) {
   int grid = (int)((n + 255) / 256);
   if (grid > 4096) grid = 4096;
   hipLaunchKernelGGL(check_planar_kernel, dim3(grid), dim3(256), 0, s, f, n, c);
-  return hipGetLastError();
-}
-
-hipError_t launch_tape_dt(const DevCtrl* c, double* slot, hipStream_t s) {
-  hipLaunchKernelGGL(tape_dt_kernel, dim3(1), dim3(64), 0, s, c, slot);
   return hipGetLastError();
 }
 

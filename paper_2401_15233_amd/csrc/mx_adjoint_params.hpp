@@ -42,13 +42,12 @@ struct AdjParams {
 // planar: the recorded states and dJ/dU are planar-symmetric (2D only): the z-odd adjoint
 // components are zero and are neither read nor written
 hipError_t launch_adjoint_stage(int dim, int order, bool planar, AdjParams& a, hipStream_t s);
-// sets ASYM_Z in ctrl->asym when a z-odd component of the flat 14-moment field f (n cells) is
+// sets ctrl->asym_z when a z-odd component of the flat 14-moment field f (n cells) is
 // nonzero
 hipError_t launch_check_planar(const double* f, long long n, DevCtrl* c, hipStream_t s);
 // grad[m] = sum over the workgroups of part[m] (fixed order)
 hipError_t launch_adjoint_reduce(const AdjParams& a, hipStream_t s);
 int adjoint_update_blocks(int nx, int ny);
-hipError_t launch_tape_dt(const DevCtrl* c, double* slot, hipStream_t s);
 hipError_t launch_pad_copy(const double* src, double* dst, int nv, int nx, int ny, int pitch,
                            int to_padded, hipStream_t s);
 }  // namespace mx

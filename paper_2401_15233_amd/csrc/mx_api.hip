@@ -90,7 +90,9 @@ struct maxent_solver {
   BatchState* batch = nullptr;
   TapeState* tape = nullptr;
   int adj_mode = MAXENT_ADJ_EXACT;
-  int asym = mx::ASYM_Z | mx::ASYM_Y;  // symmetry of the loaded state (set by the ingest)
+  bool asym_z = true, asym_y = true;    // symmetry of the loaded state (set by the ingest)
+  unsigned slot = 0;                    // steps enqueued since the control block's reset, modulo
+                                        // six: picks the slots of the next step
   bool us_dirty = false;                // a full 14-moment kernel has run: the planes that the
                                         // reduced kernels leave out may be non-zero in U or Us
   bool reduced_on = true;               // maxent_set_reduced
@@ -99,7 +101,7 @@ struct maxent_solver {
   // 2D planar (no z-odd moment; ten moments), 1D axial (no y- or z-odd moment; seven)
   bool reduced() const {
     if (!reduced_on || prob.system != 14) return false;
-    return prob.dim == 2 ? (asym & mx::ASYM_Z) == 0 : asym == 0;
+    return !asym_z && (prob.dim == 2 || !asym_y);
   }
   bool planar() const { return reduced() && prob.dim == 2; }
 };
@@ -338,12 +340,18 @@ static hipError_t collect_profile(maxent_solver* s) {
   return hipSuccess;
 }
 
+// the control block at time t0, no step taken; the next step uses slot 0
+static hipError_t reset_ctrl(maxent_solver* s, double t0) {
+  s->slot = 0;
+  return mx::launch_ctrl_reset(s->ctrl, t0, s->stream);
+}
+
 static hipError_t run_cfl(maxent_solver* s) {
   mx::CflParams c;
   c.U = s->U; c.nx = s->prob.nx; c.ny = s->prob.ny; c.pitch = s->pitch; c.plane = s->plane;
   c.dx = (s->prob.x1 - s->prob.x0) / s->prob.nx;
   c.dy = s->prob.dim == 2 ? (s->prob.y1 - s->prob.y0) / s->prob.ny : 1.0;
-  c.sigma_lim = s->num.sigma_lim; c.kws = s->num.k_ws; c.ctrl = s->ctrl;
+  c.sigma_lim = s->num.sigma_lim; c.kws = s->num.k_ws; c.maxrate = &s->ctrl->maxrate[s->slot % 3];
   return mx::launch_cfl(s->prob.system, s->prob.dim, c, s->stream);
 }
 
@@ -376,12 +384,12 @@ static int read_ctrl(maxent_solver* s) {
   return MAXENT_OK;
 }
 
-static void fill_info(maxent_solver* s, maxent_info* info) {
+// the report of a control block read back from the device
+static void fill_info(const maxent_solver* s, const DevCtrl& c, maxent_info* info) {
   if (!info) return;
-  const DevCtrl& c = *s->ctrl_host;
-  info->t = c.t;
+  info->t = c.t[s->slot & 1];
   info->dt_last = c.dt_last;
-  info->steps = c.step;
+  info->steps = c.step[s->slot & 1];
   info->n_fallback = c.n_fallback;
   info->fail_step = (c.fail_step == 0x7fffffff) ? 0 : c.fail_step;
   info->fail_code = c.status;
@@ -458,7 +466,7 @@ extern "C" int maxent_init_state(maxent_solver* s, int repr, const double* src, 
                               src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
     src = s->stage;
   }
-  HIP_TRY(s, mx::launch_ctrl_reset(s->ctrl, t0, s->stream));
+  HIP_TRY(s, reset_ctrl(s, t0));
   mx::IngestParams g = ingest_params(s, repr, src);
   if (BatchState* b = s->batch) {
     // the instances' records at t = 0, their rates zero
@@ -481,13 +489,14 @@ extern "C" int maxent_init_state(maxent_solver* s, int repr, const double* src, 
   }
   int rc = read_ctrl(s);
   if (rc) return rc;
-  s->asym = s->ctrl_host->asym;
+  s->asym_z = s->ctrl_host->asym_z != 0;
+  s->asym_y = s->ctrl_host->asym_y != 0;
   s->ready = true;
   s->rate_valid = true;
   int st = s->ctrl_host->status;
   if (st) {
     // keep the loaded state but clear the status so that the caller may inspect it
-    HIP_TRY(s, mx::launch_ctrl_reset(s->ctrl, t0, s->stream));
+    HIP_TRY(s, reset_ctrl(s, t0));
     if (!s->batch) HIP_TRY(s, run_cfl(s));
     s->ready = false;
     if (st & mx::ST_NONFINITE) return fail(s, MAXENT_E_NONFINITE, "initial state has non-finite values");
@@ -496,10 +505,10 @@ extern "C" int maxent_init_state(maxent_solver* s, int repr, const double* src, 
   return MAXENT_OK;
 }
 
-// Enqueue n steps on the solver's stream (no host synchronisation, no allocation): the
-// control block sets dt (fixed or CFL) and t_end; each step is the finalize kernel, then one
-// stage kernel (FE) or two (SSP-RK2, midpoint); with a tape, each step's dt and tau_ref are
-// kept and a checkpoint every K steps.  FE ping-pongs between U and Us (the pointers swap).
+// Enqueue n steps on the solver's stream (no host synchronisation, no allocation).  Each step is
+// one stage kernel (FE) or two (SSP-RK2, midpoint), the first of which works out dt (fixed or
+// CFL, clipped to t_end); with a tape, each step's dt and tau_ref are kept and a checkpoint
+// every K steps.  FE ping-pongs between U and Us (the pointers swap).
 static hipError_t enqueue_steps(maxent_solver* s, int n, double dt, double tau_ref, double t_end) {
   TapeState* tape = s->tape;
   const size_t field_bytes = (size_t)s->nv * s->plane * sizeof(double);
@@ -507,16 +516,16 @@ static hipError_t enqueue_steps(maxent_solver* s, int n, double dt, double tau_r
   if (!s->reduced()) s->us_dirty = true;
   mx::StageParams p = stage_params(s, tau_ref);
   const int sys = s->prob.system, dim = s->prob.dim, ord = s->num.order;
-  const double dx = (s->prob.x1 - s->prob.x0) / s->prob.nx;
-  hipError_t e = mx::launch_ctrl_set(s->ctrl, cfl_mode ? 0.0 : dt, t_end > 0 ? t_end : 0.0, s->stream);
-  if (e != hipSuccess) return e;
+  p.dt_fixed = cfl_mode ? 0.0 : dt;
+  p.t_end = t_end > 0 ? t_end : 0.0;
+  p.cfl = s->num.cfl;
+  hipError_t e = hipSuccess;
   if (cfl_mode && !s->rate_valid && (e = run_cfl(s)) != hipSuccess) return e;
   for (int k = 0; k < n; ++k) {
-    if ((e = mx::launch_finalize(s->ctrl, dim, s->num.cfl, dx, s->stream)) != hipSuccess) return e;
-    if (tape) {
-      if ((e = mx::launch_tape_dt(s->ctrl, tape->d_dt + tape->n, s->stream)) != hipSuccess) return e;
-      tape->tau.push_back(tau_ref);   // capacity reserved by maxent_record
-    }
+    p.slot = s->slot;
+    p.head = 1;
+    p.tape_dt = tape ? tape->d_dt + tape->n : nullptr;
+    if (tape) tape->tau.push_back(tau_ref);   // capacity reserved by maxent_record
     if (s->num.integrator == MAXENT_FE) {
       p.Ub = s->U; p.Ua = s->U; p.Uout = s->Us;
       p.mode = mx::MODE_EULER; p.cdt = 1.0; p.do_cfl = cfl_mode; p.copy_on_idle = 1;
@@ -530,12 +539,14 @@ static hipError_t enqueue_steps(maxent_solver* s, int n, double dt, double tau_r
       p.cdt = (s->num.integrator == MAXENT_MIDPOINT) ? 0.5 : 1.0;
       p.do_cfl = 0;
       if ((e = stage(s, sys, dim, ord, p)) != hipSuccess) return e;
+      p.head = 0;
       p.Ub = s->Us; p.Ua = s->U; p.Uout = s->U;
       p.mode = (s->num.integrator == MAXENT_MIDPOINT) ? mx::MODE_MID2 : mx::MODE_HEUN2;
       p.cdt = 1.0;
       p.do_cfl = cfl_mode;
       if ((e = stage(s, sys, dim, ord, p)) != hipSuccess) return e;
     }
+    s->slot = (s->slot + 1) % 6;   // the slots repeat every two and every three steps
     if (tape && ++tape->n % tape->K == 0) {
       e = hipMemcpyAsync(tape->ckpt[tape->n / tape->K], s->U, field_bytes, hipMemcpyDeviceToDevice,
                          s->stream);
@@ -563,7 +574,7 @@ extern "C" int maxent_step(maxent_solver* s, int n, double dt, double tau_ref, d
   if (rc) return rc;
   if (s->prof) HIP_TRY(s, collect_profile(s));
   if (n > 0) s->rate_valid = cfl_mode;  // the last stage reduced the rate of the new state
-  fill_info(s, info);
+  fill_info(s, *s->ctrl_host, info);
   int st = s->ctrl_host->status;
   if (st && tape) tape->failed = true;
   if (st & mx::ST_NONFINITE) return fail(s, MAXENT_E_NONFINITE, "non-finite cell state");
@@ -640,16 +651,16 @@ extern "C" int maxent_step_noalloc(const maxent_problem* problem, const maxent_n
   // the control block starts from zero (a kernel, not a memset); the input state is checked
   // in place (conserved in, the same values out) and its first CFL rate reduced
   t.rate_valid = true;
-  e = mx::launch_ctrl_reset(t.ctrl, t0, t.stream);
+  e = reset_ctrl(&t, t0);
   if (e == hipSuccess)
     e = mx::launch_ingest(nv, problem->dim, ingest_params(&t, MAXENT_CONSERVED, U), t.stream);
   // symmetry of a 14-moment state: read the ingest's flags, and give the scratch state zero
   // planes where a reduced kernel writes none
   if (e == hipSuccess && nv == 14) {
-    int asym = mx::ASYM_Z | mx::ASYM_Y;
-    e = hipMemcpyAsync(&asym, &t.ctrl->asym, sizeof(int), hipMemcpyDeviceToHost, t.stream);
+    int asym[2] = {1, 1};
+    e = hipMemcpyAsync(asym, &t.ctrl->asym_z, sizeof(asym), hipMemcpyDeviceToHost, t.stream);
     if (e == hipSuccess) e = hipStreamSynchronize(t.stream);
-    if (e == hipSuccess) t.asym = asym;
+    if (e == hipSuccess) { t.asym_z = asym[0] != 0; t.asym_y = asym[1] != 0; }
     if (e == hipSuccess && t.reduced()) e = mx::launch_zero_planes(t.Us, t.plane, nv, t.stream);
   }
   if (e == hipSuccess) e = enqueue_steps(&t, n, dt, tau_ref, t_end);
@@ -660,21 +671,7 @@ extern "C" int maxent_step_noalloc(const maxent_problem* problem, const maxent_n
   if (e == hipSuccess) e = hipMemcpyAsync(&host, t.ctrl, sizeof(DevCtrl), hipMemcpyDeviceToHost, t.stream);
   if (e == hipSuccess) e = hipStreamSynchronize(t.stream);
   if (e != hipSuccess) return noalloc_fail(MAXENT_E_DEVICE, "maxent_step_noalloc", e);
-  if (info) {
-    info->t = host.t;
-    info->dt_last = host.dt_last;
-    info->steps = host.step;
-    info->n_fallback = host.n_fallback;
-    info->fail_step = (host.fail_step == 0x7fffffff) ? 0 : host.fail_step;
-    info->fail_code = host.status;
-    info->n_fp64_states = host.n_fp64;
-    info->n_face_states = host.n_states;
-    info->n_sigma_limited = -1;
-    info->fp64_fraction = host.n_states > 0 ? (double)host.n_fp64 / (double)host.n_states
-                                            : (numerics->precision == MAXENT_FP64 ? 1.0 : 0.0);
-    info->reduced = t.reduced() ? (problem->dim == 2 ? 1 : 2) : 0;
-    info->reserved = 0;
-  }
+  fill_info(&t, host, info);
   if (host.status & mx::ST_NONFINITE) return noalloc_fail(MAXENT_E_NONFINITE, "non-finite cell state");
   if (host.status & mx::ST_UNREALIZABLE)
     return noalloc_fail(MAXENT_E_UNREALIZABLE, "rho <= 0 or P not SPD at a cell");
@@ -690,7 +687,7 @@ extern "C" int maxent_get_info(maxent_solver* s, maxent_info* info) {
   }
   int rc = read_ctrl(s);
   if (rc) return rc;
-  fill_info(s, info);
+  fill_info(s, *s->ctrl_host, info);
   info->n_sigma_limited = (s->ready || s->batch) ? s->ctrl_host->n_sigma_limited : 0;
   return MAXENT_OK;
 }
@@ -877,7 +874,7 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
   if (s->planar()) {
     HIP_TRY(s, mx::launch_ctrl_reset(t->actrl, 0.0, s->stream));
     HIP_TRY(s, mx::launch_check_planar(dJ_dU, (long long)nx * ny, t->actrl, s->stream));
-    HIP_TRY(s, hipMemcpyAsync(&nonplanar, &t->actrl->asym, sizeof(int), hipMemcpyDeviceToHost,
+    HIP_TRY(s, hipMemcpyAsync(&nonplanar, &t->actrl->asym_z, sizeof(int), hipMemcpyDeviceToHost,
                               s->stream));
   }
   HIP_TRY(s, hipStreamSynchronize(s->stream));
@@ -1314,7 +1311,7 @@ extern "C" int maxent_autotune_batch(maxent_solver* s, int trial_steps, int* thr
   b->wg_per_cu = bw;
   b->graph_valid = false;
   // counters polluted by the trials
-  HIP_TRY(s, mx::launch_ctrl_reset(s->ctrl, 0.0, s->stream));
+  HIP_TRY(s, reset_ctrl(s, 0.0));
   if (threads) *threads = bt;
   if (cells_per_thread) *cells_per_thread = bc;
   if (wg_per_cu) *wg_per_cu = bw;

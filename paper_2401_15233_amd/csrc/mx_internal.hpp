@@ -5,26 +5,34 @@
 namespace mx {
 
 // Device-resident control block: time step, time and status live on the device so that a
-// sequence of steps needs no host round trip.
+// sequence of steps needs no host round trip, and every step's first stage launch works out the
+// step's dt itself (no launch of its own: the separate one-wavefront kernel that did it cost 2 to
+// 4 us and a launch gap per step, 9.9 us against 5.9 for a step of 1000 cells).  What a step reads and what it leaves for the next
+// one stand in different slots, picked by the host's step counter `slot`, because the
+// workgroups of one launch read and write in any order:
+//   t, step      read from [slot & 1], written to [(slot + 1) & 1] by one workgroup of the first
+//                stage
+//   maxrate      read from [slot % 3]; the last stage reduces the new state's rate into
+//                [(slot + 1) % 3], which the step before had cleared; the first stage clears
+//                [(slot + 2) % 3]
+//   fail_step    a step runs while no earlier step failed: a failure of the running step does
+//                not stop its own later workgroups
 struct DevCtrl {
-  double dt;                     // time step of the current step (0: step is a no-op)
-  double t;                      // time after the current step's update
-  double t_end;                  // > 0: clip to t_end
-  double dt_fixed;               // > 0: fixed time step
+  double dt;                     // time step of the running step (0: the step is a no-op), for
+                                 // its second stage
   double dt_last;
-  unsigned long long maxrate;    // bit pattern of the max CFL rate (positive double)
-  long long step;                // steps taken (1-based index of the current step)
+  double t[2];                   // time
+  long long step[2];             // steps taken
+  unsigned long long maxrate[3]; // bit pattern of the max CFL rate (positive double)
   long long n_fallback;          // positivity fallbacks
   int status;                    // bit 1 non-finite, bit 2 unrealizable
-  int fail_step;                 // first failing step (0: none)
+  int fail_step;                 // first failing step (1-based; 0: the loaded state; INT_MAX: none)
   long long n_fp64;              // mixed precision: face states re-evaluated in FP64
   long long n_states;            // mixed precision: face states evaluated
   long long n_sigma_limited;     // cells with sigma < sigma_lim (set by the counting kernel)
-  int asym;                      // set by the ingest kernel: bit 1 a z-odd moment (u_z, P_xz,
-                                 // P_yz, q_z) is non-zero somewhere, bit 2 a y-odd one (u_y,
-                                 // P_xy, P_yz, q_y)
+  int asym_z, asym_y;            // set to 1 by the ingest kernel: a z-odd moment (u_z, P_xz, P_yz,
+                                 // q_z) / a y-odd one (u_y, P_xy, P_yz, q_y) is non-zero somewhere
 };
-enum { ASYM_Z = 1, ASYM_Y = 2 };
 
 // 1D tiles: a workgroup of NT threads owns NT - 4 cells, so that the cells plus the two-cell
 // halo on each side (NT), the limiter items (NT - 2) and the faces (NT - 3) each take a single
@@ -57,7 +65,11 @@ struct StageParams {
   int copy_on_idle;        // dt == 0: copy Ub to Uout (forward-Euler ping-pong) instead of skipping
   int ntx, nty;            // tile grid
   int nblk;                // real number of tiles
-  double dt_replay;        // > 0: the step's dt (a replayed recorded step); else ctrl->dt
+  double dt_replay;        // > 0: the step's dt (a replayed recorded step)
+  int head;                // this launch is its step's first stage: it works out dt
+  unsigned slot;           // the step's slots in the control block
+  double dt_fixed, t_end, cfl;   // head: fixed dt (> 0) or CFL, end time (> 0)
+  double* tape_dt;         // head: where to record the step's dt (null: nowhere)
   DevCtrl* ctrl;
 };
 
@@ -67,7 +79,7 @@ struct CflParams {
   long long plane;
   double dx, dy;
   double sigma_lim, kws;
-  DevCtrl* ctrl;
+  unsigned long long* maxrate;
 };
 
 struct BatchInst;
@@ -91,15 +103,13 @@ struct IngestParams {
 hipError_t launch_stage(int system, int dim, int order, int precision, bool reduced,
                         const StageParams& p, hipStream_t s);
 hipError_t launch_cfl(int system, int dim, const CflParams& p, hipStream_t s);
-hipError_t launch_finalize(DevCtrl* c, int dim, double cfl, double dx, hipStream_t s);
-hipError_t launch_ctrl_set(DevCtrl* c, double dt_fixed, double t_end, hipStream_t s);
 hipError_t launch_ctrl_reset(DevCtrl* c, double t0, hipStream_t s);
 // zero the planes a reduced kernel never writes (2, 3, 5, 6, 8, 11, 12: u_y, u_z, P_xy, P_xz,
 // P_yz, q_y, q_z) of a 14-moment field of `plane` doubles per plane (a kernel, no memset);
 // nothing for nv != 14
 hipError_t launch_zero_planes(double* U, long long plane, int nv, hipStream_t s);
-// loads a field into U, checks it, and reduces its CFL rate into ctrl->maxrate (or the tubes'
-// records); ctrl is reset before
+// loads a field into U, checks it, and reduces its CFL rate into ctrl->maxrate[0] (or the
+// tubes' records); ctrl is reset before
 hipError_t launch_ingest(int system, int dim, const IngestParams& p, hipStream_t s);
 // dst: unpadded [components][ny][nx]
 // repr 0 primitive, 1 conserved, 2 sigma, 3 closing moments (19 values per 14-moment cell)

@@ -45,6 +45,52 @@ __device__ __forceinline__ int wave_sum(int v) {
   return v;
 }
 
+// raise a maximum kept as the bit pattern of a non-negative double.  Device-wide atomics on one
+// address take their turn; a load first leaves out those that would change nothing, which is
+// nearly all of them once the largest rates have been seen.
+__device__ __forceinline__ void raise_max(unsigned long long* word, double m) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(m);
+  if (b > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(word, b);
+}
+
+// The time step of a step from the control block (its first stage launch; every workgroup
+// comes to the same value): fixed or CFL, clipped to t_end; 0 once the end time is reached or
+// an earlier step failed.
+__device__ __forceinline__ double step_dt(const StageParams& p, int dim) {
+  const DevCtrl* c = p.ctrl;
+  const double t = c->t[p.slot & 1];
+  double dt = 0.0;
+  if ((long long)c->fail_step > c->step[p.slot & 1]) {
+    if (p.dt_fixed > 0.0) {
+      dt = p.dt_fixed;
+    } else {
+      const double m = __longlong_as_double((long long)c->maxrate[p.slot % 3]);
+      dt = (dim == 1) ? p.cfl * p.dx / m : p.cfl / m;
+      if (!(m > 0.0)) dt = 0.0;
+    }
+    if (p.t_end > 0.0) {
+      if (t >= p.t_end * (1.0 - 1e-14)) dt = 0.0;
+      else dt = fmin(dt, p.t_end - t);
+    }
+  }
+  return dt;
+}
+
+// what the step leaves for the next one (one thread of its first stage launch); a step that
+// does nothing hands time, step count and rate on
+__device__ __forceinline__ void step_advance(const StageParams& p, double dt) {
+  DevCtrl* c = p.ctrl;
+  const unsigned now = p.slot & 1, next = now ^ 1;
+  const bool go = dt > 0.0;
+  c->t[next] = go ? c->t[now] + dt : c->t[now];
+  c->step[next] = c->step[now] + (go ? 1 : 0);
+  c->dt = dt;
+  if (go) c->dt_last = dt;
+  else c->maxrate[(p.slot + 1) % 3] = c->maxrate[p.slot % 3];
+  c->maxrate[(p.slot + 2) % 3] = 0ull;
+  if (p.tape_dt) *p.tape_dt = dt;
+}
+
 // ------------------------------------------------------------------ stage kernel
 // Waves per SIMD the kernel is compiled for.  The planar 2D kernel (ten moments) fits three
 // 256-thread workgroups per CU in LDS (45 KB each, with part of the x-face fluxes kept in
@@ -97,7 +143,15 @@ void stage_kernel(StageParams p) {
   const int j0 = (tile / p.ntx) * TY;
   const int t = threadIdx.x;
 
-  const double dt = p.dt_replay > 0.0 ? p.dt_replay : p.ctrl->dt;
+  double dt;
+  if (p.dt_replay > 0.0) {
+    dt = p.dt_replay;
+  } else if (p.head) {
+    dt = step_dt(p, DIM);
+    if (b == 0 && t == 0) step_advance(p, dt);
+  } else {
+    dt = p.ctrl->dt;
+  }
   if (!(dt > 0.0)) {  // uniform: time end reached or a failure stopped the run
     if (p.copy_on_idle && t < TX * TY) {
       int gi = i0 + t % TX, gj = j0 + t / TX;
@@ -114,7 +168,6 @@ void stage_kernel(StageParams p) {
   }
   if (t < 3) sFlag[t] = 0;
   int n64 = 0;      // FP64 re-evaluations of face states (mixed precision)
-  int nstates = 0;  // face states evaluated
 
   // 1. tile + halo -> primitives in LDS
   // (a thread issues the loads of all its cells before it converts any)
@@ -191,7 +244,6 @@ void stage_kernel(StageParams p) {
     if constexpr (PREC == 0) face_flux<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh);
     else if constexpr (PREC == 1) face_flux_mixed<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh, n64);
     else face_flux_fp32<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh);
-    nstates += 2;
     if constexpr (XREG) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -225,8 +277,7 @@ void stage_kernel(StageParams p) {
         else if constexpr (PREC == 1) face_flux_mixed<SYS, 1>(WL, WR, p.sigma_lim, p.kws, p.flux, Fy, n64);
         else face_flux_fp32<SYS, 1>(WL, WR, p.sigma_lim, p.kws, p.flux, Fy);
       }
-      nstates += 2;
-    }
+      }
   }
   // 3c. the update's inputs, gathered before the barriers so that the global loads overlap
   // the waits: the cell's stage input and (second-stage combinations) U^n from memory, its
@@ -336,7 +387,6 @@ void stage_kernel(StageParams p) {
   flag = wave_or(flag);
   nfb = wave_sum(nfb);
   if constexpr (PREC == 1) n64 = wave_sum(n64);
-  nstates = wave_sum(nstates);
   const int lane = t & 63, wid = t >> 6;
   if (lane == 0) {
     if (flag) atomicOr(&sFlag[0], flag);
@@ -351,18 +401,20 @@ void stage_kernel(StageParams p) {
   if (t == 0) {
     if (sFlag[0]) {
       atomicOr(&p.ctrl->status, sFlag[0]);
-      atomicMin(&p.ctrl->fail_step, (int)p.ctrl->step);
+      // this step's 1-based index, from whichever slot holds it
+      atomicMin(&p.ctrl->fail_step, (int)(p.head ? p.ctrl->step[p.slot & 1] + 1 : p.ctrl->step[(p.slot + 1) & 1]));
     }
     if (sFlag[1]) atomicAdd((unsigned long long*)&p.ctrl->n_fallback, (unsigned long long)sFlag[1]);
     if (PREC != 0) {
       if (sFlag[2]) atomicAdd((unsigned long long*)&p.ctrl->n_fp64, (unsigned long long)sFlag[2]);
-      atomicAdd((unsigned long long*)&p.ctrl->n_states,
-                (unsigned long long)(2 * (NFX + NFY)));
+      // every tile evaluates the same number of face states: counted once per launch
+      if (b == 0)
+        atomicAdd((unsigned long long*)&p.ctrl->n_states, (unsigned long long)p.nblk * (2 * (NFX + NFY)));
     }
     if (p.do_cfl) {
       double m = sRed[0];
       for (int k = 1; k < NT / 64; ++k) m = fmax(m, sRed[k]);
-      atomicMax(&p.ctrl->maxrate, (unsigned long long)__double_as_longlong(m));
+      raise_max(&p.ctrl->maxrate[(p.slot + 1) % 3], m);
     }
   }
 }
@@ -380,23 +432,13 @@ __device__ __forceinline__ long long padded_index(unsigned k, unsigned nx, int n
 // that the reductions at their ends cost at most 2048 atomics.
 static int field_grid(long long n) { return (int)std::min<long long>((n + 255) / 256, 2048); }
 
-// maximum of a workgroup's rates (256 threads), then one atomic on the bit pattern
+// maximum of a workgroup's rates (256 threads)
 __device__ __forceinline__ void block_max_rate(double rate, unsigned long long* maxrate) {
   __shared__ double sRed[4];
   rate = wave_max(rate);
   if ((threadIdx.x & 63) == 0) sRed[threadIdx.x >> 6] = rate;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const double m = fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]));
-    atomicMax(maxrate, (unsigned long long)__double_as_longlong(m));
-  }
-}
-
-// set bits of a status word, once: most wavefronts find them set already, and a load is
-// cheaper than queueing on one address (65536 wavefronts of a 2048 x 2048 field took 0.2 ms)
-__device__ __forceinline__ void or_status(int* word, int bits) {
-  if (bits && (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bits) != bits)
-    atomicOr(word, bits);
+  if (threadIdx.x == 0) raise_max(maxrate, fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3])));
 }
 
 // ------------------------------------------------------------------ CFL rate of a state
@@ -419,47 +461,16 @@ __global__ __launch_bounds__(256) void cfl_kernel(CflParams p) {
     SYS::cons_to_prim(U, W);
     rate = fmax(rate, cell_rate<SYS, DIM>(W, p.sigma_lim, p.kws, p.dx, p.dy));
   }
-  block_max_rate(rate, &p.ctrl->maxrate);
+  block_max_rate(rate, p.maxrate);
 }
 
-// ------------------------------------------------------------------ time control
-__global__ void finalize_kernel(DevCtrl* c, int dim, double cfl, double dx) {
-  if (threadIdx.x != 0) return;
-  double dt = 0.0;
-  if (c->status == 0) {
-    if (c->dt_fixed > 0.0) {
-      dt = c->dt_fixed;
-    } else {
-      double m = __longlong_as_double((long long)c->maxrate);
-      dt = (dim == 1) ? cfl * dx / m : cfl / m;
-      if (!(m > 0.0)) dt = 0.0;
-    }
-    if (c->t_end > 0.0) {
-      if (c->t >= c->t_end * (1.0 - 1e-14)) dt = 0.0;
-      else dt = fmin(dt, c->t_end - c->t);
-    }
-  }
-  c->dt = dt;
-  c->maxrate = 0ull;
-  if (dt > 0.0) {
-    c->t += dt;
-    c->step += 1;
-    c->dt_last = dt;
-  }
-}
-
-__global__ void ctrl_set_kernel(DevCtrl* c, double dt_fixed, double t_end) {
-  if (threadIdx.x == 0) {
-    c->dt_fixed = dt_fixed;
-    c->t_end = t_end;
-  }
-}
-
+// ------------------------------------------------------------------ control block
 __global__ void ctrl_reset_kernel(DevCtrl* c, double t0) {
   if (threadIdx.x == 0) {
-    c->dt = 0.0; c->t = t0; c->t_end = 0.0; c->dt_fixed = 0.0; c->dt_last = 0.0;
-    c->maxrate = 0ull; c->step = 0; c->n_fallback = 0; c->status = 0; c->fail_step = 0x7fffffff;
-    c->n_fp64 = 0; c->n_states = 0; c->n_sigma_limited = 0; c->asym = 0;
+    DevCtrl z = {};
+    z.t[0] = t0;
+    z.fail_step = 0x7fffffff;
+    *c = z;
   }
 }
 
@@ -518,8 +529,8 @@ __global__ __launch_bounds__(256) void ingest_kernel(IngestParams p) {
       // symmetry (14 moments): z-odd moments u_z, P_xz, P_yz, q_z and y-odd moments u_y, P_xy,
       // P_yz, q_y exactly zero
       if constexpr (NV == 14) {
-        if (Uc[3] != 0.0 || Uc[6] != 0.0 || Uc[8] != 0.0 || Uc[12] != 0.0) np |= ASYM_Z;
-        if (Uc[2] != 0.0 || Uc[5] != 0.0 || Uc[8] != 0.0 || Uc[11] != 0.0) np |= ASYM_Y;
+        if (Uc[3] != 0.0 || Uc[6] != 0.0 || Uc[8] != 0.0 || Uc[12] != 0.0) np |= 1;
+        if (Uc[2] != 0.0 || Uc[5] != 0.0 || Uc[8] != 0.0 || Uc[11] != 0.0) np |= 2;
       }
       r = fmax(cell_rate<SYS, DIM>(W, p.sigma_lim, p.kws, p.dx, p.dy), 0.0);
       if constexpr (BATCH) inst = p.cell_inst[k];
@@ -537,12 +548,20 @@ __global__ __launch_bounds__(256) void ingest_kernel(IngestParams p) {
     }
   }
   bad = wave_or(bad);
-  if ((threadIdx.x & 63) == 0) or_status(&p.ctrl->status, bad);
+  if ((threadIdx.x & 63) == 0 && bad) {
+    atomicOr(&p.ctrl->status, bad);
+    p.ctrl->fail_step = 0;   // no step runs from a state that failed its check
+  }
+  // plain stores of one value: any number of wavefronts may set a flag (an atomic each took
+  // their turn at one address, 0.2 ms for a 2048 x 2048 field)
   if constexpr (NV == 14) {
     np = wave_or(np);
-    if ((threadIdx.x & 63) == 0) or_status(&p.ctrl->asym, np);
+    if ((threadIdx.x & 63) == 0) {
+      if (np & 1) p.ctrl->asym_z = 1;
+      if (np & 2) p.ctrl->asym_y = 1;
+    }
   }
-  if constexpr (!BATCH) block_max_rate(rate, &p.ctrl->maxrate);
+  if constexpr (!BATCH) block_max_rate(rate, &p.ctrl->maxrate[0]);
 }
 
 // Closing moments of a cell state (dimensional, at sigma_bar = max(sigma, sigma_lim)):
@@ -670,16 +689,6 @@ hipError_t launch_cfl(int system, int dim, const CflParams& p, hipStream_t s) {
   if (system == 5) hipLaunchKernelGGL((cfl_kernel<Sys5, 1>), dim3(grid), dim3(256), 0, s, p);
   else if (dim == 1) hipLaunchKernelGGL((cfl_kernel<Sys14, 1>), dim3(grid), dim3(256), 0, s, p);
   else hipLaunchKernelGGL((cfl_kernel<Sys14, 2>), dim3(grid), dim3(256), 0, s, p);
-  return hipGetLastError();
-}
-
-hipError_t launch_finalize(DevCtrl* c, int dim, double cfl, double dx, hipStream_t s) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(64), 0, s, c, dim, cfl, dx);
-  return hipGetLastError();
-}
-
-hipError_t launch_ctrl_set(DevCtrl* c, double dt_fixed, double t_end, hipStream_t s) {
-  hipLaunchKernelGGL(ctrl_set_kernel, dim3(1), dim3(64), 0, s, c, dt_fixed, t_end);
   return hipGetLastError();
 }
 

@@ -282,7 +282,9 @@ int maxent_autotune_batch(maxent_solver* s, int trial_steps, int* threads, int* 
  * at most max_steps steps can be recorded (a maxent_step call that would exceed it fails with
  * INVAL before doing anything).  Device memory: (max_steps / checkpoint_every + 1) states for
  * the checkpoints; the adjoint adds 2 checkpoint_every + 3 states plus face and cell
- * workspaces (about 6 states in 2D).  maxent_init_state and maxent_destroy end the tape.
+ * workspaces (about 6 states in 2D).  maxent_init_state and maxent_destroy end the tape; after
+ * maxent_init_state (or another maxent_record) up to 1 GiB of its buffers stay with the solver
+ * for its next tape, until checkpoint_every = 0 or maxent_destroy.
  * Errors: INVAL (sizes), STATE (no valid state, batch solver), NOMEM. */
 int maxent_record(maxent_solver* s, int checkpoint_every, int max_steps);
 

@@ -23,9 +23,9 @@ class MaxEntSteps(torch.autograd.Function):
         if not isinstance(solver, MaxEntSolver):
             raise TypeError('solver must be a MaxEntSolver')
         p = params.detach().to('cpu', torch.float64)
-        solver.record(0, 1)
-        solver.set_inflow(float(p[0]), float(p[1]))
+        # loading the state ends an earlier tape, whose buffers serve the next one
         solver.init_state(U0.detach(), repr='conserved')
+        solver.set_inflow(float(p[0]), float(p[1]))
         solver.record(checkpoint_every, max(int(n), 1))
         solver.step(int(n), dt=float(dt), tau_ref=float(p[2]))
         ctx.solver = solver

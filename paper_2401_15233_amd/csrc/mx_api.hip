@@ -41,12 +41,20 @@ struct BatchState {
   bool graph_valid = false;
 };
 
+// a device allocation and its size
+struct DevBlock {
+  void* p;
+  size_t bytes;
+};
+
 // recorded run for the discrete adjoint, and the adjoint's workspace
 struct TapeState {
   int K = 0;                             // checkpoint every K steps
   int max_steps = 0;
   long long n = 0;                       // steps recorded
   bool failed = false;
+  std::vector<DevBlock> held;            // device blocks of the tape ...
+  std::vector<DevBlock> work;            // ... and of the adjoint's workspace
   std::vector<double*> ckpt;             // states at steps 0, K, 2K, ... (padded SoA)
   double* d_dt = nullptr;                // time step of every recorded step (device)
   std::vector<double> tau;               // tau_ref of every recorded step
@@ -89,6 +97,8 @@ struct maxent_solver {
   long long prof_n = 0;
   BatchState* batch = nullptr;
   TapeState* tape = nullptr;
+  std::vector<DevBlock> spare;          // blocks of an ended tape, for the next one (bounded)
+  size_t spare_bytes = 0;
   int adj_mode = MAXENT_ADJ_EXACT;
   bool asym_z = true, asym_y = true;    // symmetry of the loaded state (set by the ingest)
   unsigned slot = 0;                    // steps enqueued since the control block's reset, modulo
@@ -190,25 +200,85 @@ extern "C" const char* maxent_last_error(const maxent_solver* s) {
 
 extern "C" int maxent_num_vars(const maxent_solver* s) { return s ? s->nv : 0; }
 
-static void free_tape(maxent_solver* s) {
+// Blocks of an ended tape stay with the solver for its next tape, up to this many bytes: a
+// training loop records, reverses and loads a new state every time, and at 256^2 the allocations
+// and frees of a pass took more than twice as long as its kernels (2.8 of 4.0 ms).  Larger tapes
+// are freed as they end (their kernels take far longer than their allocation), and
+// maxent_record(0), maxent_destroy and a failing allocation give everything back.
+constexpr size_t SPARE_LIMIT = 1ull << 30;
+
+static void free_spare(maxent_solver* s) {
+  for (const DevBlock& b : s->spare) (void)hipFree(b.p);   // hipFree waits for work in flight
+  s->spare.clear();
+  s->spare_bytes = 0;
+}
+
+// a device block, from the spare ones if one has just this size (work that still uses it is
+// earlier on the solver's stream); recorded in `owner`
+static hipError_t take_block(maxent_solver* s, std::vector<DevBlock>& owner, void** out, size_t bytes) {
+  try {
+    owner.reserve(owner.size() + 1);
+  } catch (const std::bad_alloc&) {
+    return hipErrorOutOfMemory;
+  }
+  for (size_t k = 0; k < s->spare.size(); ++k) {
+    if (s->spare[k].bytes != bytes) continue;
+    *out = s->spare[k].p;
+    owner.push_back(s->spare[k]);
+    s->spare_bytes -= bytes;
+    s->spare[k] = s->spare.back();
+    s->spare.pop_back();
+    return hipSuccess;
+  }
+  hipError_t e = hipMalloc(out, bytes);
+  if (e != hipSuccess && !s->spare.empty()) {
+    (void)hipGetLastError();
+    free_spare(s);
+    e = hipMalloc(out, bytes);
+  }
+  if (e == hipSuccess) owner.push_back({*out, bytes});
+  return e;
+}
+template <class T>
+static hipError_t take_block(maxent_solver* s, std::vector<DevBlock>& owner, T** out, size_t bytes) {
+  void* p = nullptr;
+  const hipError_t e = take_block(s, owner, &p, bytes);
+  *out = (T*)p;
+  return e;
+}
+
+static void give_blocks(maxent_solver* s, std::vector<DevBlock>& owner, bool keep) {
+  for (const DevBlock& b : owner) {
+    bool kept = false;
+    if (keep && s->spare_bytes + b.bytes <= SPARE_LIMIT) {
+      try {
+        s->spare.push_back(b);
+        s->spare_bytes += b.bytes;
+        kept = true;
+      } catch (const std::bad_alloc&) {
+      }
+    }
+    if (!kept) (void)hipFree(b.p);
+  }
+  owner.clear();
+}
+
+// end the tape; keep: its blocks may serve the solver's next one
+static void free_tape(maxent_solver* s, bool keep) {
   TapeState* t = s->tape;
-  if (!t) return;
-  (void)hipStreamSynchronize(s->stream);
-  for (double* p : t->ckpt) if (p) (void)hipFree(p);
-  for (double* p : t->seg) if (p) (void)hipFree(p);
-  for (double* p : t->lam) if (p) (void)hipFree(p);
-  double* bufs[] = {t->d_dt, t->fbx, t->fby, t->wb, t->wext, t->phix, t->phiy, t->part, t->grad};
-  for (double* p : bufs) if (p) (void)hipFree(p);
-  if (t->vsx) (void)hipFree(t->vsx);
-  if (t->vsy) (void)hipFree(t->vsy);
-  if (t->actrl) (void)hipFree(t->actrl);
-  delete t;
-  s->tape = nullptr;
+  if (t) {
+    if (!keep) (void)hipStreamSynchronize(s->stream);
+    give_blocks(s, t->held, keep);
+    give_blocks(s, t->work, keep);
+    delete t;
+    s->tape = nullptr;
+  }
+  if (!keep) free_spare(s);
 }
 
 extern "C" void maxent_destroy(maxent_solver* s) {
   if (!s) return;
-  free_tape(s);
+  free_tape(s, false);
   (void)hipStreamSynchronize(s->stream);
   if (s->U) (void)hipFree(s->U);
   if (s->Us) (void)hipFree(s->Us);
@@ -459,7 +529,7 @@ extern "C" int maxent_init_state(maxent_solver* s, int repr, const double* src, 
   if (repr != MAXENT_PRIMITIVE && repr != MAXENT_CONSERVED)
     return fail(s, MAXENT_E_INVAL, "repr must be PRIMITIVE or CONSERVED");
   if (!std::isfinite(t0)) return fail(s, MAXENT_E_INVAL, "t0 must be finite");
-  free_tape(s);
+  free_tape(s, true);
   if (!src_on_device || !local_pointer(s, src)) {
     const size_t flat = (size_t)s->nv * s->prob.nx * s->prob.ny * sizeof(double);
     HIP_TRY(s, hipMemcpyAsync(s->stage, src, flat,
@@ -717,7 +787,7 @@ extern "C" int maxent_record(maxent_solver* s, int checkpoint_every, int max_ste
   if (!s) return MAXENT_E_INVAL;
   if (checkpoint_every < 0) return fail(s, MAXENT_E_INVAL, "checkpoint_every must be >= 0");
   if (checkpoint_every == 0) {
-    free_tape(s);
+    free_tape(s, false);
     return MAXENT_OK;
   }
   if (max_steps < 1) return fail(s, MAXENT_E_INVAL, "max_steps must be >= 1");
@@ -727,7 +797,7 @@ extern "C" int maxent_record(maxent_solver* s, int checkpoint_every, int max_ste
   if (s->num.source_implicit)
     return fail(s, MAXENT_E_INVAL, "the adjoint needs the explicit BGK source (source_implicit = 0)");
   if (!s->ready) return fail(s, MAXENT_E_STATE, "record before a valid init_state");
-  free_tape(s);
+  free_tape(s, true);
   TapeState* t = new (std::nothrow) TapeState();
   if (!t) return fail(s, MAXENT_E_NOMEM, "host allocation failed");
   s->tape = t;
@@ -739,14 +809,14 @@ extern "C" int maxent_record(maxent_solver* s, int checkpoint_every, int max_ste
     t->ckpt.assign(n_ck, nullptr);
     t->tau.reserve(max_steps);   // maxent_step appends one entry per step, up to max_steps
   } catch (const std::bad_alloc&) {
-    free_tape(s);
+    free_tape(s, false);
     return fail(s, MAXENT_E_NOMEM, "host allocation failed");
   }
-  hipError_t e = hipMalloc(&t->d_dt, (size_t)max_steps * sizeof(double));
-  for (int k = 0; k < n_ck && e == hipSuccess; ++k) e = hipMalloc(&t->ckpt[k], field);
+  hipError_t e = take_block(s, t->held, &t->d_dt, (size_t)max_steps * sizeof(double));
+  for (int k = 0; k < n_ck && e == hipSuccess; ++k) e = take_block(s, t->held, &t->ckpt[k], field);
   if (e == hipSuccess) e = hipMemcpyAsync(t->ckpt[0], s->U, field, hipMemcpyDeviceToDevice, s->stream);
   if (e != hipSuccess) {
-    free_tape(s);
+    free_tape(s, false);
     return fail(s, e == hipErrorOutOfMemory ? MAXENT_E_NOMEM : MAXENT_E_DEVICE,
                 std::string("tape allocation failed: ") + hipGetErrorString(e));
   }
@@ -800,25 +870,25 @@ static hipError_t adjoint_workspace(maxent_solver* s) {
     return hipErrorOutOfMemory;
   }
   for (auto& p : t->seg)
-    if (e == hipSuccess) e = hipMalloc(&p, field);
+    if (e == hipSuccess) e = take_block(s, t->work, &p, field);
   for (auto& p : t->lam)
-    if (e == hipSuccess) e = hipMalloc(&p, field);
-  if (e == hipSuccess) e = hipMalloc(&t->fbx, (size_t)28 * nfx * sizeof(double));
-  if (e == hipSuccess && nfy) e = hipMalloc(&t->fby, (size_t)28 * nfy * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&t->wb, (size_t)14 * eplane * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&t->wext, (size_t)14 * eplane * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&t->phix, (size_t)eplane * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&t->phiy, (size_t)eplane * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&t->vsx, (size_t)eplane * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc(&t->vsy, (size_t)eplane * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc(&t->part, (size_t)3 * nb * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&t->grad, 3 * sizeof(double));
+    if (e == hipSuccess) e = take_block(s, t->work, &p, field);
+  if (e == hipSuccess) e = take_block(s, t->work, &t->fbx, (size_t)28 * nfx * sizeof(double));
+  if (e == hipSuccess && nfy) e = take_block(s, t->work, &t->fby, (size_t)28 * nfy * sizeof(double));
+  if (e == hipSuccess) e = take_block(s, t->work, &t->wb, (size_t)14 * eplane * sizeof(double));
+  if (e == hipSuccess) e = take_block(s, t->work, &t->wext, (size_t)14 * eplane * sizeof(double));
+  if (e == hipSuccess) e = take_block(s, t->work, &t->phix, (size_t)eplane * sizeof(double));
+  if (e == hipSuccess) e = take_block(s, t->work, &t->phiy, (size_t)eplane * sizeof(double));
+  if (e == hipSuccess) e = take_block(s, t->work, &t->vsx, (size_t)eplane * sizeof(int));
+  if (e == hipSuccess) e = take_block(s, t->work, &t->vsy, (size_t)eplane * sizeof(int));
+  if (e == hipSuccess) e = take_block(s, t->work, &t->part, (size_t)3 * nb * sizeof(double));
+  if (e == hipSuccess) e = take_block(s, t->work, &t->grad, 3 * sizeof(double));
   for (auto& p : t->lam)
     if (e == hipSuccess) e = hipMemsetAsync(p, 0, field, s->stream);
   // the recomputed stage states: the reduced kernels leave the moments they drop as they are
   for (auto& p : t->seg)
     if (e == hipSuccess) e = hipMemsetAsync(p, 0, field, s->stream);
-  if (e == hipSuccess) e = hipMalloc(&t->actrl, sizeof(DevCtrl));
+  if (e == hipSuccess) e = take_block(s, t->work, &t->actrl, sizeof(DevCtrl));
   if (e == hipSuccess) e = mx::launch_ctrl_reset(t->actrl, 0.0, s->stream);
   return e;
 }
@@ -833,13 +903,7 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
   hipError_t e = adjoint_workspace(s);
   if (e != hipSuccess) {
     // leave the tape usable for the forward run; drop the partial workspace
-    for (auto& p : t->seg) { if (p) (void)hipFree(p); p = nullptr; }
-    for (auto& p : t->lam) { if (p) (void)hipFree(p); p = nullptr; }
-    double** bufs[] = {&t->fbx, &t->fby, &t->wb, &t->wext, &t->phix, &t->phiy, &t->part, &t->grad};
-    for (double** p : bufs) { if (*p) (void)hipFree(*p); *p = nullptr; }
-    int** ibufs[] = {&t->vsx, &t->vsy};
-    for (int** p : ibufs) { if (*p) (void)hipFree(*p); *p = nullptr; }
-    if (t->actrl) (void)hipFree(t->actrl);
+    give_blocks(s, t->work, false);
     t->actrl = nullptr;
     t->seg.clear();
     return fail(s, e == hipErrorOutOfMemory ? MAXENT_E_NOMEM : MAXENT_E_DEVICE,

@@ -48,8 +48,8 @@ PLANAR_BYTES_PER_CELL_STAGE = {1: 160.0, 2: 240.0}
 # counted by running the library's own templated device code with a counting scalar:
 # paper_2401_15233_amd/csrc/flopcount.cpp (tests/test_flopcount.py keeps these in sync); the
 # planar kernel's own count beside it
-FLOPS_PER_CELL_STAGE = {1: 3247, 2: 3568}
-PLANAR_FLOPS_PER_CELL_STAGE = {1: 2053, 2: 2287}
+FLOPS_PER_CELL_STAGE = {1: 3275, 2: 3596}
+PLANAR_FLOPS_PER_CELL_STAGE = {1: 2073, 2: 2307}
 SOURCES_FOR_TRAFFIC = ('paper_2401_15233_amd/csrc/mx_kernels.hip',
                        'paper_2401_15233_amd/csrc/mx_physics.hpp',
                        'paper_2401_15233_amd/csrc/mx_planar.hpp',

@@ -91,15 +91,32 @@ __device__ __forceinline__ void step_advance(const StageParams& p, double dt) {
   if (p.tape_dt) *p.tape_dt = dt;
 }
 
-// ------------------------------------------------------------------ stage kernel
-// Waves per SIMD the kernel is compiled for.  The planar 2D kernel (ten moments) fits three
-// 256-thread workgroups per CU in LDS (45 KB each, with part of the x-face fluxes kept in
-// registers); asking for three waves per SIMD caps it at 168 VGPRs, a few of them spilled,
-// which measured faster than two waves without spills.  The full 14-moment kernel needs two.
-constexpr int stage_min_waves(int nv, int dim) { return (nv <= 10 && dim == 2) ? 3 : 1; }
+// CFL rate of a cell state
+template <class SYS, int DIM>
+__device__ __forceinline__ double cell_rate(const double* W, double sigma_lim, double kws, double dx, double dy) {
+  if constexpr (DIM == 1) return SYS::template cell_lambda<0>(W, sigma_lim, kws);
+  else return SYS::cell_rate2d(W, sigma_lim, kws, dx, dy);
+}
 
-template <class SYS, int DIM, int ORDER, int PREC, int TX, int TY, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(stage_min_waves(SYS::NV, DIM))))
+// ------------------------------------------------------------------ stage kernel
+// One stage of a tile: primitives of the tile and its halo in LDS, limiter factors, face fluxes,
+// update, checks and (last stage) the CFL rate of the new state.  Bound by FP64 VALU work; the
+// planar system runs 3330 VALU instructions per cell and stage on large grids at 75 per cent
+// of the issue rate (2048 x 2048: 0.50 ms first stage, 0.60 ms second).  LPF lanes share a face:
+// one, or (grids that leave the chip partly idle, where a tile's latency is the time of the
+// stage) two, each with the state of one side, in twice as many threads.
+//
+// Waves per SIMD the kernel is compiled for.  Planar 2D (ten moments), one lane per face: three
+// 256-thread workgroups per CU fit in LDS (52 KB each), so three, which caps the kernel at 168
+// VGPRs without spills.  Two lanes per face: a 512-thread workgroup is two waves per SIMD, and
+// four (two workgroups per CU) still leave it the 128 VGPRs it needs.
+constexpr int stage_min_waves(int nv, int dim, int lanes) {
+  if (dim == 1) return 1;
+  return lanes == 2 ? 4 : (nv <= 10 ? 3 : 1);
+}
+
+template <class SYS, int DIM, int ORDER, int PREC, int TX, int TY, int NT, int LPF>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(stage_min_waves(SYS::NV, DIM, LPF))))
 void stage_kernel(StageParams p) {
   constexpr int NV = SYS::NV;
   constexpr int G = (ORDER == 2) ? 2 : 1;
@@ -110,64 +127,82 @@ void stage_kernel(StageParams p) {
   constexpr int NFY = (DIM == 2) ? TX * (TY + 1) : 0;
   constexpr int NPX = (ORDER == 2) ? (TX + 2) * TY : 1;
   constexpr int NPY = (ORDER == 2 && DIM == 2) ? TX * (TY + 2) : 1;
-  // planar 2D (XREG): no separate x-flux array.  The x-flux components v >= XK go to LDS at
-  // once, past the primitive tile (free during the face phases); the first XK stay in
-  // registers through the y-face phase, and all of them overwrite the primitive tile after a
-  // barrier.  XK = 1: the largest LDS footprint that still fits three workgroups per CU
-  // (52 KB each; all ten components would take 54 KB); each component held in registers
-  // instead costs two VGPRs at the kernel's peak, which the three-wavefront build spills
-  constexpr bool XREG = (DIM == 2 && NV <= 10);
+  // Where the fluxes go.  SEP (two lanes per face, planar): x and y fluxes in arrays of their
+  // own beside the primitive tile, one barrier between faces and update (76 KB, two 512-thread
+  // workgroups per CU).  XREG (one lane per face, planar): no separate x-flux array; the
+  // x-flux components v >= XK go to LDS at once, past the primitive tile (free during the face
+  // phases); the first XK stay in registers through the y-face phase, and all of them
+  // overwrite the primitive tile after a barrier.  XK = 1: the largest LDS footprint that still
+  // fits three 256-thread workgroups per CU (52 KB each; all ten components would take 54 KB).
+  // Otherwise (14 moments in 2D) x fluxes have their array and y fluxes stay in registers until
+  // they overwrite the primitive tile.
+  constexpr bool SEP = (DIM == 2 && NV <= 10 && LPF == 2);
+  constexpr bool XREG = (DIM == 2 && NV <= 10 && LPF == 1);
   constexpr int NFL = XREG ? NV * (NFX + NFY) : NV * NFY;
   constexpr int XK = XREG ? 1 : NV;
   constexpr int NW0 = XREG ? NV * NL + (NV - XK) * NFX : NV * NL;
-  constexpr int NW = (NW0 > NFL) ? NW0 : NFL;
+  constexpr int NW = (SEP || NW0 > NFL) ? NW0 : NFL;
   constexpr int XH = NW - (NV - XK) * NFX;      // where the LDS-held x-flux components start
   static_assert(!XREG || XH >= NV * NL, "x-flux slots past the primitive tile");
   static_assert(!XREG || XK * NFX + NV * NFY <= XH, "fluxes after the barrier fit below them");
-  static_assert(NFX <= NT || DIM == 1, "one x-face per thread");
+  static_assert(LPF * NFX <= NT, "one x-face (side) per thread");
+  static_assert(LPF * NFY <= NT, "one y-face (side) per thread");
 
   __shared__ double sW[NW];        // primitives of the tile + halo; later the face fluxes
   __shared__ double sFx[XREG ? 1 : NV * NFX];
+  __shared__ double sFyOwn[SEP ? NV * NFY : 1];
   __shared__ double sPx[NPX];
   __shared__ double sPy[NPY];
   __shared__ double sRed[NT / 64];
   __shared__ int sFlag[3];
 
-  // XCD-aware tile order: hardware deals consecutive workgroups round-robin to the 8
-  // XCDs; give each XCD a contiguous band of tiles so halos are shared in its L2.
-  const int nb8 = (p.nblk + 7) / 8;
   const int b = blockIdx.x;
-  const int tile = (b % 8) * nb8 + b / 8;
-  if (tile >= p.nblk) return;
-  const int i0 = (tile % p.ntx) * TX;
-  const int j0 = (tile / p.ntx) * TY;
-  const int t = threadIdx.x;
-
   double dt;
   if (p.dt_replay > 0.0) {
     dt = p.dt_replay;
   } else if (p.head) {
     dt = step_dt(p, DIM);
-    if (b == 0 && t == 0) step_advance(p, dt);
+    if (b == 0 && threadIdx.x == 0) step_advance(p, dt);
   } else {
     dt = p.ctrl->dt;
   }
-  if (!(dt > 0.0)) {  // uniform: time end reached or a failure stopped the run
-    if (p.copy_on_idle && t < TX * TY) {
-      int gi = i0 + t % TX, gj = j0 + t / TX;
-      if (gi < p.nx && gj < p.ny) {
-        long long off = (long long)gj * p.pitch + gi;
+  const bool idle = !(dt > 0.0);   // uniform: time end reached or a failure stopped the run
+  if (idle && !p.copy_on_idle) return;
+  if (threadIdx.x < 3) sFlag[threadIdx.x] = 0;
+  int n64 = 0;      // FP64 re-evaluations of face states (mixed precision)
+  int nfb = 0;      // positivity fallbacks
+  int flag = 0;     // failed checks of the new state
+  double rate = 0.0;
+
+  // XCD-aware tile order: hardware deals consecutive workgroups round-robin to the 8 XCDs;
+  // give each XCD a contiguous band of tiles so halos are shared in its L2.
+  const int nb8 = (p.nblk + 7) / 8;
+  const int tile = (b % 8) * nb8 + b / 8;
+  if (b / 8 >= nb8 || tile >= p.nblk) return;
+  const int t = threadIdx.x;
+  const int i0 = (tile % p.ntx) * TX;
+  const int j0 = (tile / p.ntx) * TY;
+  // Which wavefronts have work in a phase is a scalar test on their first thread; inside, spare
+  // lanes repeat the phase's last item (same values to the same place, or not stored), so the
+  // phases hold no divergent branch.
+  const int t0 = __builtin_amdgcn_readfirstlane(t);
+  // the cell this thread updates
+  constexpr int NC = TX * TY;
+  const int cc = min(t, NC - 1);
+  const int ci = cc % TX, cj = cc / TX;
+  const int gi = min(i0 + ci, p.nx - 1), gj = min(j0 + cj, p.ny - 1);
+  const bool own = (t < NC) && (i0 + ci < p.nx) && (j0 + cj < p.ny);
+  const long long off = (long long)gj * p.pitch + gi;
+  if (idle) {
+    if (own) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const long long o = SYS::plane_of(v) * p.plane + off;
-          p.Uout[o] = p.Ub[o];
-        }
+      for (int v = 0; v < NV; ++v) {
+        const long long o = SYS::plane_of(v) * p.plane + off;
+        p.Uout[o] = p.Ub[o];
       }
     }
     return;
   }
-  if (t < 3) sFlag[t] = 0;
-  int n64 = 0;      // FP64 re-evaluations of face states (mixed precision)
 
   // 1. tile + halo -> primitives in LDS
   // (a thread issues the loads of all its cells before it converts any)
@@ -177,16 +212,16 @@ void stage_kernel(StageParams p) {
     HaloSrc hs[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      const int c = t + r * NT;
-      if (c < NL) {
+      if (t0 + r * NT < NL) {
+        const int c = min(t + r * NT, NL - 1);
         const int li = c % LX, lj = c / LX;
         hs[r] = load_cons<SYS>(p, p.Ub, i0 + li - G, (DIM == 2) ? j0 + lj - G : 0, Uh[r]);
       }
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      const int c = t + r * NT;
-      if (c < NL) {
+      if (t0 + r * NT < NL) {
+        const int c = min(t + r * NT, NL - 1);
         const int li = c % LX, lj = c / LX;
         double W[NV];
         finish_prims<SYS>(p, hs[r], i0 + li - G, (DIM == 2) ? j0 + lj - G : 0, Uh[r], W);
@@ -205,52 +240,69 @@ void stage_kernel(StageParams p) {
 
   // 2. common limiter factors, x and y items in one sweep (542 items on 256 threads take
   // three rounds; two separate loops would take four)
-  int nfb = 0;
   if constexpr (ORDER == 2) {
     constexpr int NPT = (DIM == 2) ? NPX + NPY : NPX;
-    for (int c = t; c < NPT; c += NT) {
+#pragma unroll 1
+    for (int r0 = 0; t0 + r0 < NPT; r0 += NT) {
+      const int c = min(t + r0, NPT - 1);
       const bool isx = c < NPX;
-      int ti, tj, di, dj;
-      if (isx) { ti = c % (TX + 2) - 1; tj = c / (TX + 2); di = 1; dj = 0; }
-      else { const int cy = c - NPX; ti = cy % TX; tj = cy / TX - 1; di = 0; dj = 1; }
+      const int cy = c - NPX;
+      const int ti = isx ? c % (TX + 2) - 1 : cy % TX, tj = isx ? c / (TX + 2) : cy / TX - 1;
+      const int di = isx ? 1 : 0, dj = isx ? 0 : 1;
       double Wm[NV], Wc[NV], Wp[NV];
       lds(ti - di, tj - dj, Wm); lds(ti, tj, Wc); lds(ti + di, tj + dj, Wp);
       double phi = limiter_factor<SYS>(Wm, Wc, Wp, p.limiter);
       if (p.fallback && phi > 0.0 && !faces_admissible<SYS>(Wm, Wc, Wp, phi)) {
         phi = 0.0;
-        const bool own = isx ? (ti >= 0 && ti < TX) : (tj >= 0 && tj < TY);
-        if (own && i0 + ti < p.nx && j0 + tj < p.ny) ++nfb;
+        const bool mine = isx ? (ti >= 0 && ti < TX) : (tj >= 0 && tj < TY);
+        if (mine && t + r0 < NPT && i0 + ti < p.nx && j0 + tj < p.ny) ++nfb;
       }
       if (isx) sPx[c] = phi;
-      else sPy[c - NPX] = phi;
+      else sPy[cy] = phi;
     }
     __syncthreads();
   }
 
   // 3a. x faces: face f lies between tile cells (fi-1, fj) and (fi, fj)
   double Fx[NV];
-  for (int f = t; f < NFX; f += NT) {
-    int fi = f % (TX + 1), fj = f / (TX + 1);
-    double WL[NV], WR[NV];
-    if constexpr (ORDER == 2) {
-      double A[NV], B[NV], C[NV], D[NV];
-      lds(fi - 2, fj, A); lds(fi - 1, fj, B); lds(fi, fj, C); lds(fi + 1, fj, D);
-      face_state<SYS>(A, B, C, sPx[fj * (TX + 2) + fi], 1.0, WL);
-      face_state<SYS>(B, C, D, sPx[fj * (TX + 2) + fi + 1], -1.0, WR);
-    } else {
-      lds(fi - 1, fj, WL); lds(fi, fj, WR);
-    }
+  if (t0 < LPF * NFX) {
+    const int f = min(t / LPF, NFX - 1);
+    const int fi = f % (TX + 1), fj = f / (TX + 1);
     double Fh[NV];
-    if constexpr (PREC == 0) face_flux<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh);
-    else if constexpr (PREC == 1) face_flux_mixed<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh, n64);
-    else face_flux_fp32<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh);
+    if constexpr (LPF == 2) {
+      const int side = t & 1;
+      double W[NV];
+      if constexpr (ORDER == 2) {
+        double A[NV], B[NV], C[NV];
+        lds(fi - 2 + side, fj, A); lds(fi - 1 + side, fj, B); lds(fi + side, fj, C);
+        face_state<SYS>(A, B, C, sPx[fj * (TX + 2) + fi + side], side ? -1.0 : 1.0, W);
+      } else {
+        lds(fi - 1 + side, fj, W);
+      }
+      face_flux_pair<SYS, 0>(W, side != 0, p.sigma_lim, p.kws, p.flux, Fh);
+    } else {
+      double WL[NV], WR[NV];
+      if constexpr (ORDER == 2) {
+        double A[NV], B[NV], C[NV], D[NV];
+        lds(fi - 2, fj, A); lds(fi - 1, fj, B); lds(fi, fj, C); lds(fi + 1, fj, D);
+        face_state<SYS>(A, B, C, sPx[fj * (TX + 2) + fi], 1.0, WL);
+        face_state<SYS>(B, C, D, sPx[fj * (TX + 2) + fi + 1], -1.0, WR);
+      } else {
+        lds(fi - 1, fj, WL); lds(fi, fj, WR);
+      }
+      const int n64_before = n64;
+      if constexpr (PREC == 0) face_flux<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh);
+      else if constexpr (PREC == 1) face_flux_mixed<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh, n64);
+      else face_flux_fp32<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh);
+      if (PREC == 1 && t >= NFX) n64 = n64_before;
+    }
     if constexpr (XREG) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         if (v < XK) Fx[v] = Fh[v];
         else sW[XH + (v - XK) * NFX + f] = Fh[v];
       }
-    } else {
+    } else if (LPF == 1 || (t & 1) == 1) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) sFx[v * NFX + f] = Fh[v];
     }
@@ -258,37 +310,51 @@ void stage_kernel(StageParams p) {
 
   // 3b. y faces: face f lies between tile cells (fi, fj-1) and (fi, fj)
   double Fy[NV];
-  const bool has_y = (DIM == 2) && (t < NFY);
+  const int fy = min(t / LPF, NFY > 0 ? NFY - 1 : 0);
   if constexpr (DIM == 2) {
-    static_assert(NFY <= NT, "one y-face per thread");
-    if (has_y) {
-      int fi = t % TX, fj = t / TX;
-      double WL[NV], WR[NV];
-      if constexpr (ORDER == 2) {
-        double A[NV], B[NV], C[NV], D[NV];
-        lds(fi, fj - 2, A); lds(fi, fj - 1, B); lds(fi, fj, C); lds(fi, fj + 1, D);
-        face_state<SYS>(A, B, C, sPy[fj * TX + fi], 1.0, WL);
-        face_state<SYS>(B, C, D, sPy[(fj + 1) * TX + fi], -1.0, WR);
+    static_assert((LPF * NFY) % 64 == 0, "whole wavefronts of y faces");
+    if (t0 < LPF * NFY) {
+      const int fi = fy % TX, fj = fy / TX;
+      if constexpr (LPF == 2) {
+        const int side = t & 1;
+        double W[NV];
+        if constexpr (ORDER == 2) {
+          double A[NV], B[NV], C[NV];
+          lds(fi, fj - 2 + side, A); lds(fi, fj - 1 + side, B); lds(fi, fj + side, C);
+          face_state<SYS>(A, B, C, sPy[(fj + side) * TX + fi], side ? -1.0 : 1.0, W);
+        } else {
+          lds(fi, fj - 1 + side, W);
+        }
+        face_flux_pair<SYS, 1>(W, side != 0, p.sigma_lim, p.kws, p.flux, Fy);
+        if constexpr (SEP) {
+          if (side == 1) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) sFyOwn[v * NFY + fy] = Fy[v];
+          }
+        }
       } else {
-        lds(fi, fj - 1, WL); lds(fi, fj, WR);
-      }
-      {
+        double WL[NV], WR[NV];
+        if constexpr (ORDER == 2) {
+          double A[NV], B[NV], C[NV], D[NV];
+          lds(fi, fj - 2, A); lds(fi, fj - 1, B); lds(fi, fj, C); lds(fi, fj + 1, D);
+          face_state<SYS>(A, B, C, sPy[fj * TX + fi], 1.0, WL);
+          face_state<SYS>(B, C, D, sPy[(fj + 1) * TX + fi], -1.0, WR);
+        } else {
+          lds(fi, fj - 1, WL); lds(fi, fj, WR);
+        }
         if constexpr (PREC == 0) face_flux<SYS, 1>(WL, WR, p.sigma_lim, p.kws, p.flux, Fy);
         else if constexpr (PREC == 1) face_flux_mixed<SYS, 1>(WL, WR, p.sigma_lim, p.kws, p.flux, Fy, n64);
         else face_flux_fp32<SYS, 1>(WL, WR, p.sigma_lim, p.kws, p.flux, Fy);
       }
-      }
+    }
   }
   // 3c. the update's inputs, gathered before the barriers so that the global loads overlap
   // the waits: the cell's stage input and (second-stage combinations) U^n from memory, its
   // primitives from the tile in LDS (converted by the load phase, so no second primitive
   // recovery) and the BGK source at the cell centre
-  const int ci = t % TX, cj = t / TX;
-  const bool own = (t < TX * TY) && (i0 + ci < p.nx) && (j0 + cj < p.ny);
-  const long long off = (long long)(j0 + cj) * p.pitch + (i0 + ci);
   const bool implicit_src = p.use_source && p.src_implicit;
   double Ub[NV], Ua[NV], Cs[NV];
-  if (own) {
+  if (t0 < NC) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) Ub[v] = p.Ub[SYS::plane_of(v) * p.plane + off];
     if (p.mode != MODE_EULER) {
@@ -308,79 +374,79 @@ void stage_kernel(StageParams p) {
     }
   }
   __syncthreads();
-  // y-face fluxes (and, planar, the x-face fluxes) over the primitive tile
+  // y-face fluxes (XREG: and the x-face fluxes) over the primitive tile
   constexpr int Y0 = XREG ? XK * NFX : 0;
-  if constexpr (DIM == 2) {
+  if constexpr (DIM == 2 && !SEP) {
     if constexpr (XREG) {
-      static_assert(NFX <= NT, "one x-face per thread");
-      if (t < NFX) {
+      const int f = min(t, NFX - 1);
 #pragma unroll
-        for (int v = 0; v < XK; ++v) sW[v * NFX + t] = Fx[v];
-      }
+      for (int v = 0; v < XK; ++v) sW[v * NFX + f] = Fx[v];
     }
-    if (has_y) {
+    if (t0 < LPF * NFY && (LPF == 1 || (t & 1) == 1)) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sW[Y0 + v * NFY + t] = Fy[v];
+      for (int v = 0; v < NV; ++v) sW[Y0 + v * NFY + fy] = Fy[v];
     }
     __syncthreads();
   }
+  const double* sFy = SEP ? sFyOwn : sW + Y0;
 
   // 4. update
-  int flag = 0;
-  double rate = 0.0;
-  if (own) {
-    {
-      double Un[NV];
+  if (t0 < NC) {
+    double Un[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const double* fx = XREG ? sW : sFx;
-        const int xb = (XREG && v >= XK) ? XH + (v - XK) * NFX : v * NFX;
-        double L = -(fx[xb + cj * (TX + 1) + ci + 1] - fx[xb + cj * (TX + 1) + ci]) * p.inv_dx;
-        if constexpr (DIM == 2)
-          L = L - (sW[Y0 + v * NFY + (cj + 1) * TX + ci] - sW[Y0 + v * NFY + cj * TX + ci]) * p.inv_dy;
-        L = L + Cs[v];
-        double o;
-        if (p.mode == MODE_EULER) o = Ub[v] + (p.cdt * dt) * L;
-        else if (p.mode == MODE_HEUN2) o = 0.5 * Ua[v] + 0.5 * (Ub[v] + dt * L);
-        else o = Ua[v] + dt * L;
-        Un[v] = o;
-        if (!implicit_src) p.Uout[SYS::plane_of(v) * p.plane + off] = o;
-      }
-      if (implicit_src) {
-        // backward-Euler BGK relaxation of the transported state (forward-Euler stages only):
-        // the source keeps rho, rho u and the energy, so the Maxwellian and tau of the new
-        // state are those of the transported state, and U_new = (U_t + h U_eq) / (1 + h),
-        // h = dt / tau
-        double Wt[NV], We[NV], Ue[NV];
-        SYS::cons_to_prim(Un, Wt);
-        const double rho = Wt[0];
-        const double T = SYS::pressure(Wt) / rho;
-        const double tau = (p.tau_mode == 0) ? p.tau_ref * (p.rho_ref / rho) * sqrt(p.T_ref / T) : p.tau_ref;
-        const double h = (p.cdt * dt) / tau;
-        const double w = 1.0 / (1.0 + h);
-        SYS::equilibrium(Wt, We);
-        SYS::prim_to_cons(We, Ue);
+    for (int v = 0; v < NV; ++v) {
+      const double* fx = XREG ? sW : sFx;
+      const int xb = (XREG && v >= XK) ? XH + (v - XK) * NFX : v * NFX;
+      double L = -(fx[xb + cj * (TX + 1) + ci + 1] - fx[xb + cj * (TX + 1) + ci]) * p.inv_dx;
+      if constexpr (DIM == 2)
+        L = L - (sFy[v * NFY + (cj + 1) * TX + ci] - sFy[v * NFY + cj * TX + ci]) * p.inv_dy;
+      L = L + Cs[v];
+      double o;
+      if (p.mode == MODE_EULER) o = Ub[v] + (p.cdt * dt) * L;
+      else if (p.mode == MODE_HEUN2) o = 0.5 * Ua[v] + 0.5 * (Ub[v] + dt * L);
+      else o = Ua[v] + dt * L;
+      Un[v] = o;
+    }
+    if (implicit_src) {
+      // backward-Euler BGK relaxation of the transported state (forward-Euler stages only):
+      // the source keeps rho, rho u and the energy, so the Maxwellian and tau of the new
+      // state are those of the transported state, and U_new = (U_t + h U_eq) / (1 + h),
+      // h = dt / tau
+      double Wt[NV], We[NV], Ue[NV];
+      SYS::cons_to_prim(Un, Wt);
+      const double rho = Wt[0];
+      const double T = SYS::pressure(Wt) / rho;
+      const double tau = (p.tau_mode == 0) ? p.tau_ref * (p.rho_ref / rho) * sqrt(p.T_ref / T) : p.tau_ref;
+      const double h = (p.cdt * dt) / tau;
+      const double w = 1.0 / (1.0 + h);
+      SYS::equilibrium(Wt, We);
+      SYS::prim_to_cons(We, Ue);
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          Un[v] = (Un[v] + h * Ue[v]) * w;
-          p.Uout[SYS::plane_of(v) * p.plane + off] = Un[v];
-        }
-      }
-      bool fin = true;
+      for (int v = 0; v < NV; ++v) Un[v] = (Un[v] + h * Ue[v]) * w;
+    }
+    bool fin = true;
 #pragma unroll
-      for (int v = 0; v < NV; ++v) fin = fin && isfinite(Un[v]);
-      if (!fin) {
-        flag |= ST_NONFINITE;
-      } else if (p.do_cfl) {
-        // the last stage of a step: the new state's primitives also give its CFL rate
-        double Wn[NV];
-        SYS::cons_to_prim(Un, Wn);
-        if (!SYS::admissible(Wn)) flag |= ST_UNREALIZABLE;
-        else if constexpr (DIM == 1) rate = SYS::template cell_lambda<0>(Wn, p.sigma_lim, p.kws);
-        else rate = SYS::cell_rate2d(Wn, p.sigma_lim, p.kws, p.dx, p.dy);
-      } else if (!SYS::admissible_cons(Un)) {
-        flag |= ST_UNREALIZABLE;
-      }
+    for (int v = 0; v < NV; ++v) fin = fin && isfinite(Un[v]);
+    if (own) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) p.Uout[SYS::plane_of(v) * p.plane + off] = Un[v];
+    }
+    int bad = 0;
+    double r = 0.0;
+    if (p.do_cfl) {
+      // the last stage of a step: the new state's primitives also give its CFL rate
+      double Wn[NV];
+      SYS::cons_to_prim(Un, Wn);
+      if (!SYS::admissible(Wn)) bad = ST_UNREALIZABLE;
+      r = cell_rate<SYS, DIM>(Wn, p.sigma_lim, p.kws, p.dx, p.dy);
+    } else if (!SYS::admissible_cons(Un)) {
+      bad = ST_UNREALIZABLE;
+    }
+    if (!fin) bad = ST_NONFINITE;
+    // a failed cell's rate does not count; a NaN is passed over, as by the maximum before
+    if (own) {
+      flag |= bad;
+      rate = fmax(rate, bad ? 0.0 : r);
     }
   }
   // block reductions: status, fallback count, CFL rate
@@ -442,12 +508,6 @@ __device__ __forceinline__ void block_max_rate(double rate, unsigned long long* 
 }
 
 // ------------------------------------------------------------------ CFL rate of a state
-template <class SYS, int DIM>
-__device__ __forceinline__ double cell_rate(const double* W, double sigma_lim, double kws, double dx, double dy) {
-  if constexpr (DIM == 1) return SYS::template cell_lambda<0>(W, sigma_lim, kws);
-  else return SYS::cell_rate2d(W, sigma_lim, kws, dx, dy);
-}
-
 template <class SYS, int DIM>
 __global__ __launch_bounds__(256) void cfl_kernel(CflParams p) {
   constexpr int NV = SYS::NV;
@@ -649,15 +709,34 @@ __global__ __launch_bounds__(256) void count_sigma_limited_kernel(const double* 
 }
 
 // ------------------------------------------------------------------ launchers
+template <class SYS, int DIM, int ORDER, int PREC, int LPF>
+static hipError_t launch_stage_l(const StageParams& p, hipStream_t s) {
+  const int grid = ((p.nblk + 7) / 8) * 8;
+  constexpr int TX = DIM == 2 ? 16 : tile_1d(64), TY = DIM == 2 ? 15 : 1, NT = (DIM == 2 ? 256 : 64) * LPF;
+  hipLaunchKernelGGL((stage_kernel<SYS, DIM, ORDER, PREC, TX, TY, NT, LPF>), dim3(grid), dim3(NT), 0, s, p);
+  return hipGetLastError();
+}
+
+// Tiles up to which two lanes share a face: while the doubled workgroups all run at once.  2D
+// planar: two 512-thread workgroups on each of the 256 CUs (two stages and their gaps, one
+// lane -> two: 64 x 64 30.5 -> 27.7 us, 224 x 224 33.0 -> 30.4, 320 x 320 42.4 -> 40.8; beyond,
+// 352 x 352 51.9 -> 57.8, 768 x 768 159 -> 172).  2D with all 14 moments: one (76 KB of LDS each and
+// twice the registers; 64 x 64 37.1 -> 34.9, 192 x 192 39.2 -> 38.1, but 256 x 256 51.8 -> 54.1).
+// 1D: two-wave workgroups, eight waves per SIMD of the 1024 with seven moments or fewer (1000
+// cells of 5 moments 13.4 -> 12.7, 64000 25.3 -> 20.3, 256000 37.9 -> 33.4; axial 16.0 -> 14.8,
+// 26.7 -> 23.4, 43.1 -> 42.7), two with 14 (1000 cells 21.6 -> 19.7, 48000 27.8 -> 26.6, but 96000
+// 36.9 -> 43.8).
+constexpr int two_lane_tiles(int nv, int dim) {
+  if (dim == 1) return nv <= 7 ? 4096 : 1024;
+  return nv <= 10 ? 512 : 256;
+}
+
 template <class SYS, int DIM, int ORDER, int PREC>
 static hipError_t launch_stage_t(const StageParams& p, hipStream_t s) {
-  int grid = ((p.nblk + 7) / 8) * 8;
-  if constexpr (DIM == 2) {
-    hipLaunchKernelGGL((stage_kernel<SYS, DIM, ORDER, PREC, 16, 15, 256>), dim3(grid), dim3(256), 0, s, p);
-  } else {
-    hipLaunchKernelGGL((stage_kernel<SYS, DIM, ORDER, PREC, tile_1d(64), 1, 64>), dim3(grid), dim3(64), 0, s, p);
+  if constexpr (PREC == 0) {
+    if (p.nblk <= two_lane_tiles(SYS::NV, DIM)) return launch_stage_l<SYS, DIM, ORDER, PREC, 2>(p, s);
   }
-  return hipGetLastError();
+  return launch_stage_l<SYS, DIM, ORDER, PREC, 1>(p, s);
 }
 
 template <int PREC>

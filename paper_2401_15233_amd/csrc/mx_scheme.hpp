@@ -86,12 +86,37 @@ MX_HD bool faces_admissible(const T* Wm, const T* Wc, const T* Wp, T phi) {
   return SYS::admissible(Wu) && SYS::admissible(Wd);
 }
 
-// Interface flux of two face states: HLL (Davis speeds) or Rusanov, in one form
-//   Fh = cL FL + cR FR + d (UR - UL).
+// Interface flux of two face states: HLL (Davis speeds) or Rusanov, in one form, the left
+// side's share and then the right side's
+//   Fh = (cL FL - d UL) + (cR FR + d UR).
 // HLL: S- = min(SL, 0), S+ = max(SR, 0), cL = S+ / (S+ - S-), cR = -S- / (S+ - S-),
 // d = S- S+ / (S+ - S-): the upwind fluxes of the supersonic cases follow from S- = 0 or
 // S+ = 0 without a branch or a select per component.  Rusanov: cL = cR = 1/2, d = -a*/2.  A NaN
-// wave speed of either side reaches every component through d.
+// wave speed of either side reaches every component through d.  (d U is at most
+// CFL dx U / (2 dt), so rounding d UL and d UR apart moves the update by no more than its own
+// rounding.)
+template <class T> struct FaceCoef { T cL, cR, d; };
+template <class T>
+MX_HD FaceCoef<T> face_coef(T lminL, T lmaxL, T lminR, T lmaxR, int flux_kind) {
+  FaceCoef<T> k;
+  if (flux_kind == 0) {
+    const T Sm = cmin(tmin(lminL, lminR), T(0)), Sp = cmax(tmax(lmaxL, lmaxR), T(0));
+    const T inv = mrcp(Sp - Sm);
+    k.cL = Sp * inv;
+    k.cR = -Sm * inv;
+    k.d = Sm * k.cL + T(0) * (lminL + lminR);
+  } else {
+    const T am = tmax(tmax(tabs(lminL), tabs(lmaxL)), tmax(tabs(lminR), tabs(lmaxR)));
+    k.cL = k.cR = T(0.5);
+    k.d = T(-0.5) * am;
+  }
+  return k;
+}
+// a component: the left side's share, and the flux from that and the right side (the same
+// roundings in one lane or two)
+template <class T> MX_HD T share_left(const FaceCoef<T>& k, T F, T U) { return tfma(k.cL, F, -(k.d * U)); }
+template <class T> MX_HD T add_right(const FaceCoef<T>& k, T F, T U, T left) { return tfma(k.cR, F, tfma(k.d, U, left)); }
+
 template <class SYS, int D, class T>
 MX_HD void face_flux(const T* WL, const T* WR, T sigma_lim, T kws, int flux_kind, T* Fh) {
   constexpr int NV = SYS::NV;
@@ -99,20 +124,37 @@ MX_HD void face_flux(const T* WL, const T* WR, T sigma_lim, T kws, int flux_kind
   T lminL, lmaxL, lminR, lmaxR;
   SYS::template face_terms<D>(WL, sigma_lim, kws, UL, FL, lminL, lmaxL);
   SYS::template face_terms<D>(WR, sigma_lim, kws, UR, FR, lminR, lmaxR);
-  T cL, cR, d;
-  if (flux_kind == 0) {
-    const T Sm = cmin(tmin(lminL, lminR), T(0)), Sp = cmax(tmax(lmaxL, lmaxR), T(0));
-    const T inv = mrcp(Sp - Sm);
-    cL = Sp * inv;
-    cR = -Sm * inv;
-    d = Sm * cL + T(0) * (lminL + lminR);
-  } else {
-    const T am = tmax(tmax(tabs(lminL), tabs(lmaxL)), tmax(tabs(lminR), tabs(lmaxR)));
-    cL = cR = T(0.5);
-    d = T(-0.5) * am;
-  }
+  const FaceCoef<T> k = face_coef(lminL, lmaxL, lminR, lmaxR, flux_kind);
 #pragma unroll
-  for (int v = 0; v < NV; ++v) Fh[v] = cL * FL[v] + (cR * FR[v] + d * (UR[v] - UL[v]));
+  for (int v = 0; v < NV; ++v) Fh[v] = add_right(k, FR[v], UR[v], share_left(k, FL[v], UL[v]));
+}
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// a value of the neighbouring lane (lane ^ 1)
+__device__ __forceinline__ double lane_xor1(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, 0xB1, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0xB1, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+#else
+__device__ inline double lane_xor1(double x) { return x; }
+#endif
+
+// The same flux by two neighbouring lanes, each with one face state W (right: the right one);
+// the right one gets the flux.  A lane evaluates one closure and pair of wave speeds, not two,
+// so a face takes half as long and needs about half the registers.
+template <class SYS, int D>
+__device__ __forceinline__ void face_flux_pair(const double* W, bool right, double sigma_lim, double kws,
+                                               int flux_kind, double* Fh) {
+  constexpr int NV = SYS::NV;
+  double U[NV], F[NV], lmin, lmax;
+  SYS::template face_terms<D>(W, sigma_lim, kws, U, F, lmin, lmax);
+  const double omin = lane_xor1(lmin), omax = lane_xor1(lmax);
+  const FaceCoef<double> k = face_coef(right ? omin : lmin, right ? omax : lmax, right ? lmin : omin,
+                                       right ? lmax : omax, flux_kind);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) Fh[v] = add_right(k, F[v], U[v], lane_xor1(share_left(k, F[v], U[v])));
 }
 
 // Mixed precision (Section 3.3: the dimensionless closure is robust in single precision).

@@ -97,10 +97,7 @@ static void cell_stage(bool last) {
   }
   // update: flux differences, BGK source with local tau, Heun combination, admissibility
   CD C[NV], Un[NV], Wn[NV];
-  CD rho = Wc[0];
-  CD T = SYS::pressure(Wc) / rho;
-  CD tau = CD(0.006) * (CD(1.0) / rho) * msqrt(CD(1.0) / T);
-  SYS::source(Wc, CD(1.0) / tau, C);
+  SYS::source(Wc, mx::inv_tau<SYS>(Wc, 0, CD(1.0 / 0.006)), C);
   for (int v = 0; v < NV; ++v) {
     CD L = -(U[v] - Wc[v]) * CD(2048.0);
     L = L - (U[v] - W[1][v]) * CD(2048.0);

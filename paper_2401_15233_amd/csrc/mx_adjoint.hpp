@@ -16,19 +16,6 @@
 
 namespace mx {
 
-// Hides a value's origin from the device compiler; no instruction is emitted and host code
-// is unchanged.  A reverse that reads the laundered copy recomputes the forward intermediates
-// it needs where it needs them, instead of the compiler sharing them with an earlier forward
-// evaluation (or hoisting them) and keeping them live across the whole reverse.  Compile-time
-// constants (the z-odd zeros of a planar run) are left as they are, so that they still fold.
-template <class T> MX_HD void opaque(T& x) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  if (!__builtin_constant_p(x)) asm volatile("" : "+v"(x));
-#else
-  (void)x;
-#endif
-}
-
 // symmetric (stored) y = S x: reverse
 template <class T> MX_HD void symv_vjp(const T* S, const T* x, const T* yb, T* Sb, T* xb) {
 #pragma unroll
@@ -564,7 +551,7 @@ struct Adj14 {
     const T Carg = T(3) * f.om * P;
     const T C = msqrt_pos(Carg);
     const T E = T(0.8) * C;
-    const T pref = T(0.5) * (a + b * f.isw);
+    const T pref = T(0.5) * tfma(b, f.isw, a);
     const T kc = kws * k.c;
     const T dBE = f.sB - E;
     const T D = f.sw2 * dBE;

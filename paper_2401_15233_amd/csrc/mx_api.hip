@@ -364,6 +364,7 @@ static mx::StageParams stage_params(maxent_solver* s, double tau_ref) {
   p.use_source = (tau_ref > 0 && std::isfinite(tau_ref)) ? 1 : 0;
   p.src_implicit = s->num.source_implicit;
   p.tau_mode = q.tau_mode; p.tau_ref = tau_ref; p.rho_ref = q.rho_ref; p.T_ref = q.T_ref;
+  p.inv_tau_ref = mx::inv_tau_constant(q.tau_mode, tau_ref, q.rho_ref, q.T_ref);
   p.sigma_lim = s->num.sigma_lim; p.kws = s->num.k_ws;
   p.limiter = s->num.limiter; p.flux = s->num.flux; p.fallback = s->num.positivity_fallback;
   if (q.dim == 2) { p.ntx = (q.nx + 15) / 16; p.nty = (q.ny + 14) / 15; }
@@ -484,8 +485,6 @@ static mx::BatchParams batch_params(maxent_solver* s) {
   p.bc_lo = s->prob.bc[0];
   p.bc_hi = s->prob.bc[1];
   p.tau_mode = s->prob.tau_mode;
-  p.rho_ref = s->prob.rho_ref;
-  p.T_ref = s->prob.T_ref;
   p.sigma_lim = s->num.sigma_lim;
   p.kws = s->num.k_ws;
   p.limiter = s->num.limiter;
@@ -1141,7 +1140,7 @@ extern "C" int maxent_create_batch(const maxent_problem* common, const maxent_nu
     r.t_end = inst[i].t_end;
     r.dx = (inst[i].x1 - inst[i].x0) / inst[i].n_cells;
     r.inv_dx = 1.0 / r.dx;
-    r.tau_ref = inst[i].tau_ref;
+    r.inv_tau_ref = inst[i].tau_ref > 0.0 ? mx::inv_tau_constant(p.tau_mode, inst[i].tau_ref, p.rho_ref, p.T_ref) : 0.0;
     r.off = off;
     r.n = inst[i].n_cells;
     r.fail_step = 0x7fffffff;
@@ -1176,12 +1175,23 @@ extern "C" int maxent_create_batch(const maxent_problem* common, const maxent_nu
   return MAXENT_OK;
 }
 
+// Workgroups of the batch's stage launches: wg_per_cu on every CU, but no more than run at once.
+// Each walks its own range of tiles, so a workgroup that starts when another ends adds no
+// balance, only a last round that fills part of the chip.
+static hipError_t batch_grid(const maxent_solver* s, int* grid) {
+  const BatchState* b = s->batch;
+  int resident = 0;
+  hipError_t e = mx::batch_stage_residency(s->num.precision == MAXENT_MIXED ? 1 : 0, s->reduced(), b->nt, b->cpt,
+                                           &resident);
+  *grid = std::min(b->wg_per_cu, std::max(resident, 1)) * b->n_cu;
+  return e;
+}
+
 // enqueue `steps` batched steps on stream st
-static hipError_t batch_enqueue(maxent_solver* s, int steps, hipStream_t st) {
+static hipError_t batch_enqueue(maxent_solver* s, int steps, int grid, hipStream_t st) {
   BatchState* b = s->batch;
   if (!s->reduced()) s->us_dirty = true;
   mx::BatchParams p = batch_params(s);
-  const int grid = b->wg_per_cu * b->n_cu;
   const bool mid = s->num.integrator == MAXENT_MIDPOINT;
   const int prec = s->num.precision == MAXENT_MIXED ? 1 : 0;
   for (int k = 0; k < steps; ++k) {
@@ -1206,8 +1216,10 @@ static int batch_capture(maxent_solver* s, int chunk) {
   if (b->exec) { (void)hipGraphExecDestroy(b->exec); b->exec = nullptr; }
   b->graph_valid = false;
   hipGraph_t g = nullptr;
+  int grid = 0;
+  HIP_TRY(s, batch_grid(s, &grid));
   HIP_TRY(s, hipStreamBeginCapture(b->gstream, hipStreamCaptureModeThreadLocal));
-  hipError_t e = batch_enqueue(s, chunk, b->gstream);
+  hipError_t e = batch_enqueue(s, chunk, grid, b->gstream);
   hipError_t e2 = hipStreamEndCapture(b->gstream, &g);
   if (e != hipSuccess || e2 != hipSuccess) {
     if (g) (void)hipGraphDestroy(g);
@@ -1338,11 +1350,13 @@ extern "C" int maxent_autotune_batch(maxent_solver* s, int trial_steps, int* thr
       b->nt = shapes[a][0];
       b->cpt = shapes[a][1];
       b->wg_per_cu = wgs[w];
-      e = batch_enqueue(s, 1, s->stream);  // warm-up step (first use of the shape)
+      int grid = 0;
+      e = batch_grid(s, &grid);
+      if (e == hipSuccess) e = batch_enqueue(s, 1, grid, s->stream);  // warm-up step (first use of the shape)
       if (e == hipSuccess) e = hipMemcpyAsync(s->U, saveU, field, hipMemcpyDeviceToDevice, s->stream);
       if (e == hipSuccess) e = hipMemcpyAsync(b->d_inst, saveI, recs, hipMemcpyDeviceToDevice, s->stream);
       if (e == hipSuccess) e = hipEventRecord(e0, s->stream);
-      if (e == hipSuccess) e = batch_enqueue(s, trial_steps, s->stream);
+      if (e == hipSuccess) e = batch_enqueue(s, trial_steps, grid, s->stream);
       if (e == hipSuccess) e = hipEventRecord(e1, s->stream);
       if (e == hipSuccess) e = hipMemcpyAsync(b->h_inst, b->d_inst, recs, hipMemcpyDeviceToHost, s->stream);
       if (e == hipSuccess) e = hipStreamSynchronize(s->stream);

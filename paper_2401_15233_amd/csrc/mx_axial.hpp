@@ -253,7 +253,7 @@ struct Sys14A {
     const T t1 = n.Ph[0] + n.Ph[1] + n.Ph[2];
     n.t2 = n.P2[0] + n.P2[1] + n.P2[2];
     const T D = n.h * (n.h * mrcp(n.Ph[0])) * ic2;
-    sigma_bar(T(2) * n.t2 + t1 * t1 - W[6] * (ic2 * ip), D, n.t2, sigma_lim, n.s);
+    sigma_bar(tfma(t1, t1, T(2) * n.t2) - W[6] * (ic2 * ip), D, n.t2, sigma_lim, n.s);
   }
   template <class T> MX_HD static void speeds(const Norm<T>& n, T ux, T& lmin, T& lmax) {
     SigmaFit<T> f;
@@ -271,12 +271,14 @@ struct Sys14A {
     const T v = q * mrcp(T(2) * A + n.t2);
     const T isb = n.s.isb;
     const T vs = v * isb;
-    // v z (P*^2)_xx = v h P*_xx, so the three terms of Q_xxl z_l are equal
-    const T R = T(3) * (vs * (a * n.h)) + (T(2) * (T(1) - n.s.sb) * n.pT * A + T(3) * n.T0 * Pxx);
+    // v z (P*^2)_xx = v h P*_xx, so the three terms of Q_xxl z_l are equal.  (Where a sum has two
+    // products, tfma says which one is fused: the single and the batched kernels then agree bit
+    // for bit, whichever way the compiler would have gone in each.)
+    const T R = T(3) * (vs * (a * n.h)) + tfma(T(2) * (T(1) - n.s.sb) * n.pT, A, T(3) * n.T0 * Pxx);
     const T det = a * n.Ph[1] * n.Ph[2];
-    const T Wq = v * (T(24) * n.t2 - T(54) + T(28) * det + ((T(12) * n.t2 - T(72)) * a + T(60) * A));
+    const T Wq = v * (T(24) * n.t2 - T(54) + T(28) * det + tfma(T(12) * n.t2 - T(72), a, T(60) * A));
     const T hs = n.h * isb;
-    const T S = T(3) * v * (hs * hs) + n.T0 * (T(6) * n.s.rsb * q + (T(1) - n.s.rsb) * Wq);
+    const T S = tfma(T(3) * v, hs * hs, n.T0 * tfma(T(6) * n.s.rsb, q, (T(1) - n.s.rsb) * Wq));
     const T Qx = T(3) * (v * A);
 
     const T uu = ux * ux;
@@ -295,9 +297,9 @@ struct Sys14A {
     const T Rq = R + Qu;
     F[0] = U[1];
     F[1] = U[2];
-    F[2] = ux * U[2] + (T(2) * Pu + Qx);
-    F[3] = ux * W[3] + v * n.P2[1];
-    F[4] = ux * W[4] + v * n.P2[2];
+    F[2] = ux * U[2] + tfma(T(2), Pu, Qx);
+    F[3] = tfma(ux, W[3], v * n.P2[1]);
+    F[4] = tfma(ux, W[4], v * n.P2[2]);
     F[5] = ux * U[5] + (ux * m + (uu * Pxx + (Rq + Qu)));
     F[6] = ux * U[6] + (T(2) * uu * m + (T(4) * (ux * Rq) + S));
     speeds(n, ux, lmin, lmax);

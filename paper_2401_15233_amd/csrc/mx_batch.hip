@@ -18,21 +18,12 @@
 
 namespace mx {
 
-__device__ __forceinline__ double bwave_max(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
+// a value that all lanes share, in scalar registers
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ long long uniform(long long x) {
+  return ((long long)uniform((int)(x >> 32)) << 32) | (unsigned)uniform((int)x);
 }
-__device__ __forceinline__ int bwave_or(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ int bwave_sum(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
+__device__ __forceinline__ double uniform(double x) { return __longlong_as_double(uniform(__double_as_longlong(x))); }
 
 __device__ __forceinline__ int bmap(int g, int n, int lo, int hi, int& refl) {
   if (g < 0) {
@@ -125,33 +116,40 @@ __global__ __launch_bounds__(1024) void batch_finalize_kernel(BatchInst* in, con
 }
 
 // Stage kernel: a workgroup of NT threads owns tiles of CPT * NT - 4 cells (CPT cells per
-// thread), so the tile plus its two-cell halos fills whole rounds over the threads.  The
+// thread), so the tile plus its two-cell halos is CPT whole rounds over the threads.  The
 // step's tile list (active instances in queue order, each cut into tiles) is split into
 // contiguous ranges, one per workgroup, with an XCD-aware order of the ranges; a workgroup
 // finds its first tile by a binary search over the tile prefix and then walks forward.
-// Two waves per SIMD: the register budget is 256 per lane.
-template <class SYS, int ORDER, int PREC, int NT, int CPT>
+//
+// Bound by FP64 VALU work, with the loads of each tile exposed where nothing else runs; so a
+// workgroup reduces status, counters and CFL rate once for the tiles of an instance in its range
+// instead of for each tile, and (PIPE: one cell per thread, seven moments, FP64: where the
+// registers hold it) a thread updates the cell that it loaded, and loads U^n of the second
+// stage and the next tile's cell before the tile's faces.  512 tubes of 512 to 32768 cells (4.0 M
+// cells, 256 threads): 20 steps with load and read 13.2 -> 9.6 ms, with the grid held to the
+// workgroups that run at once.
+template <class SYS, int PREC, int NT, int CPT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(SYS::NV <= 7 ? 3 : 2)))
 void batch_stage_kernel(BatchParams p) {
   constexpr int NV = SYS::NV;
+  constexpr int G = 2;
   constexpr int TX = tile_1d(CPT * NT);
-  constexpr int G = (ORDER == 2) ? 2 : 1;
   constexpr int LX = TX + 2 * G;
   constexpr int NFX = TX + 1;
-  constexpr int NPX = (ORDER == 2) ? TX + 2 : 1;
+  constexpr int NPX = TX + 2;
+  constexpr bool PIPE = CPT == 1 && NV <= 7 && PREC == 0;
+  static_assert(LX == CPT * NT, "tile and halo are whole rounds over the threads");
   __shared__ double sW[NV * LX];
   __shared__ double sFx[NV * NFX];
   __shared__ double sPx[NPX];
-  __shared__ double sRed[NT / 64];
-  __shared__ int sFlag[3];
   const int t = threadIdx.x;
-  const int lane = t & 63, wid = t >> 6;
+  const int lane = t & 63;
 
-  const int n_tiles = p.bctrl->n_tiles;
-  const int n_act = p.bctrl->n_active;
+  const int n_tiles = uniform(p.bctrl->n_tiles);
+  const int n_act = uniform(p.bctrl->n_active);
   // this workgroup's range of the tile list (split and XCD bands set by the finalize kernel)
-  const int per = p.bctrl->per;
-  const int band = p.bctrl->band;
+  const int per = uniform(p.bctrl->per);
+  const int band = uniform(p.bctrl->band);
   int slot = blockIdx.x;
   if (band > 0) {
     const int kx = blockIdx.x >> 3;
@@ -165,39 +163,63 @@ void batch_stage_kernel(BatchParams p) {
     int hi = n_act - 1;  // last active instance whose first tile is <= k0
     while (j < hi) {
       const int mid = (j + hi + 1) >> 1;
-      if (p.act_tile0[mid] <= k0) j = mid;
+      if (uniform(p.act_tile0[mid]) <= k0) j = mid;
       else hi = mid - 1;
     }
   }
-  int first = p.act_tile0[j], next = p.act_tile0[j + 1];
-
-  for (int k = k0; k < k1; ++k) {
-    if (k >= next) {  // every active instance has at least one tile
-      ++j;
-      first = next;
-      next = p.act_tile0[j + 1];
-    }
-    const int inst = p.act_inst[j];
-    const int i0 = (k - first) * TX;
-    BatchInst* c = p.inst + inst;
-    const double dt = c->dt;
-    if (!(dt > 0.0)) continue;  // uniform; not reached for a listed instance
-    const int n = c->n;
-    const long long off = c->off;
-    const double inv_dx = c->inv_dx;
-    __syncthreads();            // LDS of the previous tile is no longer read
-    if (t < 3) sFlag[t] = 0;
-    int n64 = 0;
-
-    // 1. tile + halo -> primitives
-    for (int cc = t; cc < LX; cc += NT) {
-      int rx = 0;
-      int si = bmap(i0 + cc - G, n, p.bc_lo, p.bc_hi, rx);
-      double Uc[NV], W[NV];
+  // the tile in work: its instance and first cell (the record's constants of a step)
+  struct Tile {
+    BatchInst* c;
+    int next;         // first tile of the next instance
+    int n, i0;
+    long long off;
+    double dt, inv_dx, inv_tau_ref;
+  };
+  auto open_instance = [&](int k) {   // every active instance has at least one tile
+    Tile m;
+    m.c = p.inst + uniform(p.act_inst[j]);
+    m.next = uniform(p.act_tile0[j + 1]);
+    m.n = uniform(m.c->n);
+    m.i0 = (k - uniform(p.act_tile0[j])) * TX;
+    m.off = uniform(m.c->off);
+    m.dt = uniform(m.c->dt);
+    m.inv_dx = uniform(m.c->inv_dx);
+    m.inv_tau_ref = uniform(m.c->inv_tau_ref);
+    return m;
+  };
+  // stage input of tile cell cc (interior or ghost source); refl: mirrored at a wall
+  auto load_cell = [&](const Tile& m, int cc, double* U, int& refl) {
+    refl = 0;
+    const long long o = m.off + bmap(m.i0 + cc - G, m.n, p.bc_lo, p.bc_hi, refl);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) Uc[v] = p.Ub[SYS::plane_of(v) * p.plane + off + si];
+    for (int v = 0; v < NV; ++v) U[v] = p.Ub[SYS::plane_of(v) * p.plane + o];
+  };
+  auto lds = [&](int ti, double* W) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) W[v] = sW[v * LX + ti + G];
+  };
+
+  Tile cur = open_instance(k0);
+  double Uown[NV];       // PIPE: the stage input of this thread's cell
+  int refl = 0;
+  if constexpr (PIPE) load_cell(cur, t, Uown, refl);
+  double rate = 0.0;     // of the instance's tiles so far
+  int n64 = 0, nfb = 0;
+  for (int k = k0; k < k1; ++k) {
+    const double dt = cur.dt;
+    // 1. tile + halo -> primitives
+#pragma unroll 1
+    for (int r = 0; r < CPT; ++r) {
+      const int cc = t + r * NT;
+      double Uc[NV], W[NV];
+      if constexpr (PIPE) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Uc[v] = Uown[v];
+      } else {
+        load_cell(cur, cc, Uc, refl);
+      }
       SYS::cons_to_prim(Uc, W);
-      if (rx) {
+      if (refl) {
 #pragma unroll
         for (int v = 0; v < NV; ++v)
           if (SYS::odd(v, 0)) W[v] = -W[v];
@@ -206,144 +228,173 @@ void batch_stage_kernel(BatchParams p) {
       for (int v = 0; v < NV; ++v) sW[v * LX + cc] = W[v];
     }
     __syncthreads();
-    auto lds = [&](int ti, double* W) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) W[v] = sW[v * LX + ti + G];
-    };
 
-    // 2. common limiter factors
-    int nfb = 0;
-    if constexpr (ORDER == 2) {
-      for (int cc = t; cc < NPX; cc += NT) {
-        int ti = cc - 1;
-        double Wm[NV], Wc[NV], Wp[NV];
-        lds(ti - 1, Wm); lds(ti, Wc); lds(ti + 1, Wp);
-        double phi = limiter_factor<SYS>(Wm, Wc, Wp, p.limiter);
-        if (p.fallback && phi > 0.0) {
-          const bool ok = faces_admissible<SYS>(Wm, Wc, Wp, phi);
-          if (!ok) {
-            phi = 0.0;
-            if (ti >= 0 && ti < TX && i0 + ti < n) ++nfb;
-          }
-        }
-        sPx[cc] = phi;
+    // 2. common limiter factors (a spare thread repeats the last item)
+#pragma unroll 1
+    for (int r = 0; r < CPT; ++r) {
+      const int cc = min(t + r * NT, NPX - 1);
+      const int ti = cc - 1;
+      double Wm[NV], Wc[NV], Wp[NV];
+      lds(ti - 1, Wm); lds(ti, Wc); lds(ti + 1, Wp);
+      double phi = limiter_factor<SYS>(Wm, Wc, Wp, p.limiter);
+      if (p.fallback && phi > 0.0 && !faces_admissible<SYS>(Wm, Wc, Wp, phi)) {
+        phi = 0.0;
+        if (t + r * NT < NPX && ti >= 0 && ti < TX && cur.i0 + ti < cur.n) ++nfb;
       }
-      __syncthreads();
-    }
-
-    // 3. faces: face fi lies between tile cells fi - 1 and fi
-    for (int fi = t; fi < NFX; fi += NT) {
-      double WL[NV], WR[NV];
-      if constexpr (ORDER == 2) {
-        double A[NV], B[NV], C[NV], D[NV];
-        lds(fi - 2, A); lds(fi - 1, B); lds(fi, C); lds(fi + 1, D);
-        face_state<SYS>(A, B, C, sPx[fi], 1.0, WL);
-        face_state<SYS>(B, C, D, sPx[fi + 1], -1.0, WR);
-      } else {
-        lds(fi - 1, WL); lds(fi, WR);
-      }
-      double Fh[NV];
-      if constexpr (PREC == 0) face_flux<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh);
-      else face_flux_mixed<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh, n64);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) sFx[v * NFX + fi] = Fh[v];
+      sPx[cc] = phi;
     }
     __syncthreads();
 
-    // 4. update
-    int flag = 0;
-    double rate = 0.0;
-    for (int ci = t; ci < TX; ci += NT) {
-      if (i0 + ci >= n) break;
-      long long g = off + i0 + ci;
-      double Ub[NV], W[NV];
+    Tile nxt = cur;
+    if (k + 1 < k1) {
+      nxt.i0 += TX;
+      if (k + 1 >= cur.next) {
+        ++j;
+        nxt = open_instance(k + 1);
+      }
+    }
+    // PIPE: U^n of the second stage and the next tile's cell, in flight during the faces
+    const int ci0 = t - G;
+    double Ua[NV], Unext[NV];
+    int refl_next = 0;
+    if constexpr (PIPE) {
+      const int own = min(max(cur.i0 + ci0, 0), cur.n - 1);
+      if (p.mode != MODE_EULER) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) Ub[v] = p.Ub[SYS::plane_of(v) * p.plane + g];
-      SYS::cons_to_prim(Ub, W);
-      double Cs[NV];
-      const double tau_ref = c->tau_ref;
-      if (tau_ref > 0.0) {
-        double rho = W[0];
-        double T = SYS::pressure(W) / rho;
-        double tau = (p.tau_mode == 0) ? tau_ref * (p.rho_ref / rho) * sqrt(p.T_ref / T) : tau_ref;
-        SYS::source(W, 1.0 / tau, Cs);
+        for (int v = 0; v < NV; ++v) Ua[v] = p.Ua[SYS::plane_of(v) * p.plane + cur.off + own];
+      }
+      load_cell(nxt, t, Unext, refl_next);
+    }
+
+    // 3. faces: face fi lies between tile cells fi - 1 and fi.  (Mixed precision: the loop
+    // stays a loop for CPT = 1 too, so that the compiler fuses products and sums there as it does
+    // in the other kernels.)
+    int rounds = CPT;
+    if constexpr (PREC != 0) asm volatile("" : "+s"(rounds));
+#pragma unroll 1
+    for (int r = 0; r < rounds; ++r) {
+      const int fi = min(t + r * NT, NFX - 1);
+      double WL[NV], WR[NV], A[NV], B[NV], C[NV], D[NV];
+      lds(fi - 2, A); lds(fi - 1, B); lds(fi, C); lds(fi + 1, D);
+      face_state<SYS>(A, B, C, sPx[fi], 1.0, WL);
+      face_state<SYS>(B, C, D, sPx[fi + 1], -1.0, WR);
+      double Fh[NV];
+      const int before = n64;
+      if constexpr (PREC == 0) face_flux<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh);
+      else face_flux_mixed<SYS, 0>(WL, WR, p.sigma_lim, p.kws, p.flux, Fh, n64);
+      if (PREC != 0 && t + r * NT >= NFX) n64 = before;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) sFx[v * NFX + fi] = Fh[v];
+    }
+    auto source = [&](int ci, double* Cs) {
+      if (cur.inv_tau_ref > 0.0) {
+        double W[NV];
+        lds(ci, W);
+        SYS::source(W, inv_tau<SYS>(W, p.tau_mode, cur.inv_tau_ref), Cs);
       } else {
 #pragma unroll
         for (int v = 0; v < NV; ++v) Cs[v] = 0.0;
       }
-      double Un[NV];
+    };
+    __syncthreads();
+
+    // 4. update.  PIPE: of the thread's own cell, and of the primitive tile only that cell is
+    // still read, which the same thread overwrites for the next tile: no barrier between
+    int flag = 0;
+#pragma unroll 1
+    for (int r = 0; r < CPT; ++r) {
+      const int ci = PIPE ? min(max(ci0, 0), TX - 1) : min(t + r * NT, TX - 1);
+      const bool own = (PIPE ? ci == ci0 : t + r * NT < TX) && cur.i0 + ci < cur.n;
+      const long long g = cur.off + min(cur.i0 + ci, cur.n - 1);
+      double Ub[NV], Cs[NV], Un[NV];
+      if constexpr (PIPE) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        double L = -(sFx[v * NFX + ci + 1] - sFx[v * NFX + ci]) * inv_dx;
-        L = L + Cs[v];
-        double o;
-        if (p.mode == MODE_EULER) o = Ub[v] + (p.cdt * dt) * L;
-        else if (p.mode == MODE_HEUN2) o = 0.5 * p.Ua[SYS::plane_of(v) * p.plane + g] + 0.5 * (Ub[v] + dt * L);
-        else o = p.Ua[SYS::plane_of(v) * p.plane + g] + dt * L;
-        Un[v] = o;
-        p.Uout[SYS::plane_of(v) * p.plane + g] = o;
+        for (int v = 0; v < NV; ++v) Ub[v] = Uown[v];
+      } else {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Ub[v] = p.Ub[SYS::plane_of(v) * p.plane + g];
+        if (p.mode != MODE_EULER) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) Ua[v] = p.Ua[SYS::plane_of(v) * p.plane + g];
+        }
       }
+      source(ci, Cs);
       bool fin = true;
 #pragma unroll
-      for (int v = 0; v < NV; ++v) fin = fin && isfinite(Un[v]);
-      if (!fin) {
-        flag |= ST_NONFINITE;
-      } else if (p.do_cfl) {
+      for (int v = 0; v < NV; ++v) {
+        const double L = tfma(sFx[v * NFX + ci] - sFx[v * NFX + ci + 1], cur.inv_dx, Cs[v]);
+        const double o = stage_update(p.mode, p.cdt, dt, L, Ub[v], Ua[v]);
+        Un[v] = o;
+        fin = fin && isfinite(o);
+      }
+      if (own) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) p.Uout[SYS::plane_of(v) * p.plane + g] = Un[v];
+      }
+      int bad = 0;
+      double rc = 0.0;
+      if (p.do_cfl) {
         double Wn[NV];
         SYS::cons_to_prim(Un, Wn);
-        if (!SYS::admissible(Wn)) flag |= ST_UNREALIZABLE;
-        else rate = fmax(rate, SYS::template cell_lambda<0>(Wn, p.sigma_lim, p.kws));
+        if (!SYS::admissible(Wn)) bad = ST_UNREALIZABLE;
+        rc = SYS::template cell_lambda<0>(Wn, p.sigma_lim, p.kws);
       } else if (!SYS::admissible_cons(Un)) {
-        flag |= ST_UNREALIZABLE;
+        bad = ST_UNREALIZABLE;
+      }
+      if (!fin) bad = ST_NONFINITE;
+      if (own) {
+        flag |= bad;
+        rate = fmax(rate, bad ? 0.0 : rc);
       }
     }
-    flag = bwave_or(flag);
-    nfb = bwave_sum(nfb);
-    if constexpr (PREC != 0) n64 = bwave_sum(n64);
-    if (lane == 0) {
-      if (flag) atomicOr(&sFlag[0], flag);
-      if (nfb) atomicAdd(&sFlag[1], nfb);
-      if (PREC != 0 && n64) atomicAdd(&sFlag[2], n64);
-    }
-    if (p.do_cfl) {
-      rate = bwave_max(rate);
-      if (lane == 0) sRed[wid] = rate;
-    }
-    __syncthreads();
-    if (t == 0) {
-      if (sFlag[0]) {
-        atomicOr(&c->status, sFlag[0]);
-        atomicMin(&c->fail_step, (int)c->step);
-      }
-      if (sFlag[1]) atomicAdd((unsigned long long*)&p.ctrl->n_fallback, (unsigned long long)sFlag[1]);
-      if (PREC != 0) {
-        if (sFlag[2]) atomicAdd((unsigned long long*)&p.ctrl->n_fp64, (unsigned long long)sFlag[2]);
-        atomicAdd((unsigned long long*)&p.ctrl->n_states, (unsigned long long)(2 * NFX));
-      }
-      if (p.do_cfl) {
-        double m = sRed[0];
-        for (int w = 1; w < NT / 64; ++w) m = fmax(m, sRed[w]);
-        atomicMax(&c->maxrate, (unsigned long long)__double_as_longlong(m));
+    if (__any(flag)) {   // a failed tube stops; rare
+      flag = wave_or(flag);
+      if (lane == 0) {
+        atomicOr(&cur.c->status, flag);
+        atomicMin(&cur.c->fail_step, (int)cur.c->step);
       }
     }
+    // the instance's last tile of this range: its CFL rate
+    if (p.do_cfl && (k + 1 == k1 || k + 1 >= cur.next)) {
+      const double m = wave_max(rate);
+      if (lane == 0) raise_max(&cur.c->maxrate, m);
+      rate = 0.0;
+    }
+    if constexpr (PIPE) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) Uown[v] = Unext[v];
+      refl = refl_next;
+    } else {
+      __syncthreads();   // the update read the primitive tile
+    }
+    cur = nxt;
+  }
+  // counters, once for the range
+  nfb = wave_sum(nfb);
+  if (lane == 0 && nfb) atomicAdd((unsigned long long*)&p.ctrl->n_fallback, (unsigned long long)nfb);
+  if constexpr (PREC != 0) {
+    n64 = wave_sum(n64);
+    if (lane == 0 && n64) atomicAdd((unsigned long long*)&p.ctrl->n_fp64, (unsigned long long)n64);
+    if (t == 0) atomicAdd((unsigned long long*)&p.ctrl->n_states, (unsigned long long)(k1 - k0) * (2 * NFX));
   }
 }
 
-template <class SYS, int PREC, int NT, int CPT>
-static hipError_t launch_bs(const BatchParams& p, int grid, hipStream_t s) {
-  hipLaunchKernelGGL((batch_stage_kernel<SYS, 2, PREC, NT, CPT>), dim3(grid), dim3(NT), 0, s, p);
-  return hipGetLastError();
-}
-
-template <class SYS, int PREC>
-static hipError_t launch_bs_p(int nt, int cpt, const BatchParams& p, int grid, hipStream_t s) {
-  if (nt == 64 && cpt == 1) return launch_bs<SYS, PREC, 64, 1>(p, grid, s);
-  if (nt == 64 && cpt == 2) return launch_bs<SYS, PREC, 64, 2>(p, grid, s);
-  if (nt == 64 && cpt == 4) return launch_bs<SYS, PREC, 64, 4>(p, grid, s);
-  if (nt == 128 && cpt == 1) return launch_bs<SYS, PREC, 128, 1>(p, grid, s);
-  if (nt == 128 && cpt == 2) return launch_bs<SYS, PREC, 128, 2>(p, grid, s);
-  if (nt == 256 && cpt == 1) return launch_bs<SYS, PREC, 256, 1>(p, grid, s);
+// f(kernel) for the kernel of a launch shape
+template <class SYS, int PREC, class F>
+static hipError_t with_kernel_p(int nt, int cpt, F f) {
+  if (nt == 64 && cpt == 1) return f(batch_stage_kernel<SYS, PREC, 64, 1>);
+  if (nt == 64 && cpt == 2) return f(batch_stage_kernel<SYS, PREC, 64, 2>);
+  if (nt == 64 && cpt == 4) return f(batch_stage_kernel<SYS, PREC, 64, 4>);
+  if (nt == 128 && cpt == 1) return f(batch_stage_kernel<SYS, PREC, 128, 1>);
+  if (nt == 128 && cpt == 2) return f(batch_stage_kernel<SYS, PREC, 128, 2>);
+  if (nt == 256 && cpt == 1) return f(batch_stage_kernel<SYS, PREC, 256, 1>);
   return hipErrorInvalidValue;
+}
+template <class F>
+static hipError_t with_kernel(int precision, bool reduced, int nt, int cpt, F f) {
+  if (reduced)
+    return precision == 0 ? with_kernel_p<Sys14A, 0>(nt, cpt, f) : with_kernel_p<Sys14A, 1>(nt, cpt, f);
+  return precision == 0 ? with_kernel_p<Sys14, 0>(nt, cpt, f) : with_kernel_p<Sys14, 1>(nt, cpt, f);
 }
 
 bool batch_shape_supported(int nt, int cpt) {
@@ -353,9 +404,16 @@ bool batch_shape_supported(int nt, int cpt) {
 
 hipError_t launch_batch_stage(int precision, bool reduced, int nt, int cpt, const BatchParams& p, int grid,
                               hipStream_t s) {
-  if (reduced)
-    return precision == 0 ? launch_bs_p<Sys14A, 0>(nt, cpt, p, grid, s) : launch_bs_p<Sys14A, 1>(nt, cpt, p, grid, s);
-  return precision == 0 ? launch_bs_p<Sys14, 0>(nt, cpt, p, grid, s) : launch_bs_p<Sys14, 1>(nt, cpt, p, grid, s);
+  return with_kernel(precision, reduced, nt, cpt, [&](void (*kernel)(BatchParams)) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(nt), 0, s, p);
+    return hipGetLastError();
+  });
+}
+
+hipError_t batch_stage_residency(int precision, bool reduced, int nt, int cpt, int* workgroups) {
+  return with_kernel(precision, reduced, nt, cpt, [&](void (*kernel)(BatchParams)) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups, (const void*)kernel, nt, 0);
+  });
 }
 
 hipError_t launch_batch_finalize(BatchInst* in, const int* order, int n_inst, double cfl, int tile_w,

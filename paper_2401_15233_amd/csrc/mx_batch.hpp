@@ -7,7 +7,8 @@ namespace mx {
 
 struct BatchInst {
   double dt, t, t_end, dt_last;
-  double dx, inv_dx, tau_ref;
+  double dx, inv_dx;
+  double inv_tau_ref;            // inv_tau_constant; 0: no source
   unsigned long long maxrate;    // bit pattern of the max CFL rate (positive double)
   long long step;
   long long off;                 // first cell in the concatenated field
@@ -35,7 +36,6 @@ struct BatchParams {
   const BatchCtrl* bctrl;        // n_active and n_tiles of the current step
   int bc_lo, bc_hi;
   int tau_mode;
-  double rho_ref, T_ref;
   double sigma_lim, kws;
   int limiter, flux, fallback;
   int mode;
@@ -50,6 +50,8 @@ bool batch_shape_supported(int nt, int cpt);
 // and the stages carry the seven other moments (Sys14A)
 hipError_t launch_batch_stage(int precision, bool reduced, int nt, int cpt, const BatchParams& p, int grid,
                               hipStream_t s);
+// workgroups of that stage kernel that one CU holds at once
+hipError_t batch_stage_residency(int precision, bool reduced, int nt, int cpt, int* workgroups);
 hipError_t launch_batch_finalize(BatchInst* in, const int* order, int n_inst, double cfl, int tile_w,
                                  int* act_inst, int* act_tile0, BatchCtrl* bc, int stage_grid,
                                  hipStream_t s);

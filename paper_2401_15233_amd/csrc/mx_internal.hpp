@@ -1,5 +1,6 @@
 // Internal interface between the C-ABI runtime and the gfx950 kernels.
 #pragma once
+#include <cmath>
 #include <hip/hip_runtime.h>
 
 namespace mx {
@@ -39,8 +40,47 @@ struct DevCtrl {
 // round over the threads.
 constexpr int tile_1d(int nt) { return nt - 4; }
 
+// the factor of 1 / tau that a run keeps (inv_tau; mode 0: local tau, 1: constant)
+inline double inv_tau_constant(int mode, double tau_ref, double rho_ref, double T_ref) {
+  return mode == 0 ? 1.0 / (tau_ref * rho_ref * std::sqrt(T_ref)) : 1.0 / tau_ref;
+}
+
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  return v;
+}
+
+__device__ __forceinline__ int wave_or(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
+  return v;
+}
+
+__device__ __forceinline__ int wave_sum(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// raise a maximum kept as the bit pattern of a non-negative double.  Device-wide atomics on one
+// address take their turn; a load first leaves out those that would change nothing, which is
+// nearly all of them once the largest rates have been seen.
+__device__ __forceinline__ void raise_max(unsigned long long* word, double m) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(m);
+  if (b > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(word, b);
+}
+
 enum { MODE_EULER = 0, MODE_HEUN2 = 1, MODE_MID2 = 2 };
 enum { ST_NONFINITE = 1, ST_UNREALIZABLE = 2 };
+
+// New value of a component from its residual L (modes MODE_EULER, MODE_HEUN2, MODE_MID2): explicit
+// fused operations, so that every kernel rounds alike whatever surrounds the expression.
+__device__ __forceinline__ double stage_update(int mode, double cdt, double dt, double L, double Ub, double Ua) {
+  if (mode == MODE_EULER) return __builtin_fma(cdt * dt, L, Ub);
+  if (mode == MODE_HEUN2) return __builtin_fma(0.5, Ua, 0.5 * __builtin_fma(dt, L, Ub));
+  return __builtin_fma(dt, L, Ua);
+}
 
 struct StageParams {
   const double* Ub;        // stage input, read with its neighbourhood
@@ -57,6 +97,7 @@ struct StageParams {
   int use_source, tau_mode;
   int src_implicit;        // BGK source by backward Euler on the transported state (EULER mode)
   double tau_ref, rho_ref, T_ref;
+  double inv_tau_ref;      // inv_tau_constant of the three
   double sigma_lim, kws;
   int limiter, flux, fallback;
   int mode;

@@ -27,32 +27,6 @@
 
 namespace mx {
 
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
-__device__ __forceinline__ int wave_or(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
-  return v;
-}
-
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// raise a maximum kept as the bit pattern of a non-negative double.  Device-wide atomics on one
-// address take their turn; a load first leaves out those that would change nothing, which is
-// nearly all of them once the largest rates have been seen.
-__device__ __forceinline__ void raise_max(unsigned long long* word, double m) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(m);
-  if (b > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(word, b);
-}
-
 // The time step of a step from the control block (its first stage launch; every workgroup
 // comes to the same value): fixed or CFL, clipped to t_end; 0 once the end time is reached or
 // an earlier step failed.
@@ -364,10 +338,7 @@ void stage_kernel(StageParams p) {
     if (p.use_source && !implicit_src) {
       double W[NV];
       lds(ci, cj, W);
-      const double rho = W[0];
-      const double T = SYS::pressure(W) / rho;
-      const double tau = (p.tau_mode == 0) ? p.tau_ref * (p.rho_ref / rho) * sqrt(p.T_ref / T) : p.tau_ref;
-      SYS::source(W, 1.0 / tau, Cs);
+      SYS::source(W, inv_tau<SYS>(W, p.tau_mode, p.inv_tau_ref), Cs);
     } else {
 #pragma unroll
       for (int v = 0; v < NV; ++v) Cs[v] = 0.0;
@@ -397,15 +368,10 @@ void stage_kernel(StageParams p) {
     for (int v = 0; v < NV; ++v) {
       const double* fx = XREG ? sW : sFx;
       const int xb = (XREG && v >= XK) ? XH + (v - XK) * NFX : v * NFX;
-      double L = -(fx[xb + cj * (TX + 1) + ci + 1] - fx[xb + cj * (TX + 1) + ci]) * p.inv_dx;
-      if constexpr (DIM == 2)
-        L = L - (sFy[v * NFY + (cj + 1) * TX + ci] - sFy[v * NFY + cj * TX + ci]) * p.inv_dy;
-      L = L + Cs[v];
-      double o;
-      if (p.mode == MODE_EULER) o = Ub[v] + (p.cdt * dt) * L;
-      else if (p.mode == MODE_HEUN2) o = 0.5 * Ua[v] + 0.5 * (Ub[v] + dt * L);
-      else o = Ua[v] + dt * L;
-      Un[v] = o;
+      double L = Cs[v];
+      if constexpr (DIM == 2) L = tfma(sFy[v * NFY + cj * TX + ci] - sFy[v * NFY + (cj + 1) * TX + ci], p.inv_dy, L);
+      L = tfma(fx[xb + cj * (TX + 1) + ci] - fx[xb + cj * (TX + 1) + ci + 1], p.inv_dx, L);
+      Un[v] = stage_update(p.mode, p.cdt, dt, L, Ub[v], Ua[v]);
     }
     if (implicit_src) {
       // backward-Euler BGK relaxation of the transported state (forward-Euler stages only):
@@ -414,11 +380,8 @@ void stage_kernel(StageParams p) {
       // h = dt / tau
       double Wt[NV], We[NV], Ue[NV];
       SYS::cons_to_prim(Un, Wt);
-      const double rho = Wt[0];
-      const double T = SYS::pressure(Wt) / rho;
-      const double tau = (p.tau_mode == 0) ? p.tau_ref * (p.rho_ref / rho) * sqrt(p.T_ref / T) : p.tau_ref;
-      const double h = (p.cdt * dt) / tau;
-      const double w = 1.0 / (1.0 + h);
+      const double h = (p.cdt * dt) * inv_tau<SYS>(Wt, p.tau_mode, p.inv_tau_ref);
+      const double w = mrcp(1.0 + h);
       SYS::equilibrium(Wt, We);
       SYS::prim_to_cons(We, Ue);
 #pragma unroll

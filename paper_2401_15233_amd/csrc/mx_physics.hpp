@@ -37,6 +37,19 @@ namespace mx {
 
 #define MX_HD __host__ __device__ __forceinline__
 
+// Hides a value's origin from the device compiler; no instruction is emitted and host code
+// is unchanged.  A reverse that reads the laundered copy recomputes the forward intermediates
+// it needs where it needs them, instead of the compiler sharing them with an earlier forward
+// evaluation (or hoisting them) and keeping them live across the whole reverse.  Compile-time
+// constants (the z-odd zeros of a planar run) are left as they are, so that they still fold.
+template <class T> MX_HD void opaque(T& x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (!__builtin_constant_p(x)) asm volatile("" : "+v"(x));
+#else
+  (void)x;
+#endif
+}
+
 // storage index of symmetric (i, j): xx xy xz yy yz zz
 MX_HD constexpr int sidx(int i, int j) {
   return (i == j) ? (i == 0 ? 0 : (i == 1 ? 3 : 5))
@@ -289,26 +302,27 @@ MX_HD void wave_roots(const SigmaFit<T>& f, T pref, T E, T qd, T qt, T alpha, T 
   T base = D * D, zp = aq, zn = -aq;
   if constexpr (TRANSVERSE) {
     const T w = qt * alpha;
-    base = base + T(0.1) * (qt * qt);
+    base = tfma(T(0.1), qt * qt, base);
     zp = w + aq;
     zn = w - aq;
   }
-  const T hp = zp + msqrt_pos(zp * (zp - g) + base);
-  const T rest = base - zn * g;
-  const T sn = msqrt_pos(zn * zn + rest) + tabs(zn);
+  // (tfma: which products are fused must not depend on the kernel around)
+  const T hp = zp + msqrt_pos(tfma(zp, zp - g, base));
+  const T rest = tfma(-zn, g, base);
+  const T sn = msqrt_pos(tfma(zn, zn, rest)) + tabs(zn);
   T hn = mdiv(rest, sn);
   if constexpr (TRANSVERSE) hn = (zn >= T(0)) ? sn : hn;
-  const T Lp = pref * hp + E, Ln = pref * hn + E;
+  const T Lp = tfma(pref, hp, E), Ln = tfma(pref, hn, E);
   const bool fwd = qd >= T(0);
   const T Lmax = fwd ? Lp : Ln, Lmin = fwd ? Ln : Lp;
-  lmax = ud + kc * Lmax;
-  lmin = ud - kc * Lmin;
+  lmax = tfma(kc, Lmax, ud);
+  lmin = tfma(-kc, Lmin, ud);
 }
 template <bool TRANSVERSE, class T>
 MX_HD void wave_pair(const SigmaFit<T>& f, T P, T qd, T qt, T ud, T kc, T& lmin, T& lmax) {
   T a, b, P04;
   fit_ab(P, a, b, P04);
-  wave_roots<TRANSVERSE>(f, T(0.5) * (a + b * f.isw), T(0.8) * msqrt_pos(T(3) * f.om * P), qd, qt,
+  wave_roots<TRANSVERSE>(f, T(0.5) * tfma(b, f.isw, a), T(0.8) * msqrt_pos(T(3) * f.om * P), qd, qt,
                          T(0.6) * P * P - T(0.38) * P + T(0.35), ud, kc, lmin, lmax);
 }
 
@@ -316,7 +330,7 @@ MX_HD void wave_pair(const SigmaFit<T>& f, T P, T qd, T qt, T ud, T kc, T& lmin,
 // and square root
 template <class T> struct SigmaBar { T sig, sb, isb, rsb; };
 template <class T> MX_HD void sigma_bar(T A, T D, T t2, T sigma_lim, SigmaBar<T>& s) {
-  const T big = tabs(A) + msqrt(A * A + T(8) * (t2 * D));
+  const T big = tabs(A) + msqrt(tfma(A, A, T(8) * (t2 * D)));
   const bool pos = A >= T(0);
   s.sig = mdiv(pos ? big : T(2) * D, pos ? T(4) * t2 : big);
   s.sb = cmax(s.sig, sigma_lim);
@@ -657,7 +671,7 @@ struct Sys14 {
 #pragma unroll
     for (int i = 0; i < 3; ++i) n.z[i] = y[i] * idet;
     const T D = (n.h[0] * n.z[0] + n.h[1] * n.z[1] + n.h[2] * n.z[2]) * ic2;
-    sigma_bar(T(2) * n.t2 + t1 * t1 - W[13] * (ic2 * ip), D, n.t2, sigma_lim, n.s);
+    sigma_bar(tfma(t1, t1, T(2) * n.t2) - W[13] * (ic2 * ip), D, n.t2, sigma_lim, n.s);
   }
   template <int d, class T>
   MX_HD static void speeds(const Norm<T>& n, const SigmaFit<T>& f, T ud, T& lmin, T& lmax) {

@@ -321,7 +321,7 @@ struct Sys14P {
     n.z[0] = (n.Ph[2] * n.h[0] - n.Ph[1] * n.h[1]) * idet;
     n.z[1] = (n.Ph[0] * n.h[1] - n.Ph[1] * n.h[0]) * idet;
     const T D = (n.h[0] * n.z[0] + n.h[1] * n.z[1]) * ic2;
-    sigma_bar(T(2) * n.t2 + t1 * t1 - W[9] * (ic2 * ip), D, n.t2, sigma_lim, n.s);
+    sigma_bar(tfma(t1, t1, T(2) * n.t2) - W[9] * (ic2 * ip), D, n.t2, sigma_lim, n.s);
   }
   template <int d, class T>
   MX_HD static void speeds(const Norm<T>& n, const SigmaFit<T>& f, T ud, T& lmin, T& lmax) {

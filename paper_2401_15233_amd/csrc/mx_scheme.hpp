@@ -86,6 +86,16 @@ MX_HD bool faces_admissible(const T* Wm, const T* Wc, const T* Wp, T phi) {
   return SYS::admissible(Wu) && SYS::admissible(Wd);
 }
 
+// 1 / tau of a cell.  Mode 0: tau = tau_ref (rho_ref / rho) sqrt(T_ref / T), T = p / rho, so
+// 1 / tau = k rho sqrt(T) with k = 1 / (tau_ref rho_ref sqrt(T_ref)); mode 1: k = 1 / tau_ref.
+// k comes from inv_tau_constant, once per run: a cell takes one reciprocal and one reciprocal
+// square root (the quotients and the root as they stand took about 110 VALU instructions more).
+template <class SYS, class T> MX_HD T inv_tau(const T* W, int mode, T k) {
+  if (mode != 0) return k;
+  const T temp = SYS::pressure(W) * mrcp(W[0]);
+  return k * (W[0] * (temp * mrsqrt(temp)));
+}
+
 // Interface flux of two face states: HLL (Davis speeds) or Rusanov, in one form, the left
 // side's share and then the right side's
 //   Fh = (cL FL - d UL) + (cR FR + d UR).
@@ -124,6 +134,7 @@ MX_HD void face_flux(const T* WL, const T* WR, T sigma_lim, T kws, int flux_kind
   T lminL, lmaxL, lminR, lmaxR;
   SYS::template face_terms<D>(WL, sigma_lim, kws, UL, FL, lminL, lmaxL);
   SYS::template face_terms<D>(WR, sigma_lim, kws, UR, FR, lminR, lmaxR);
+  opaque(lminL); opaque(lmaxL); opaque(lminR); opaque(lmaxR);
   const FaceCoef<T> k = face_coef(lminL, lmaxL, lminR, lmaxR, flux_kind);
 #pragma unroll
   for (int v = 0; v < NV; ++v) Fh[v] = add_right(k, FR[v], UR[v], share_left(k, FL[v], UL[v]));
@@ -150,6 +161,7 @@ __device__ __forceinline__ void face_flux_pair(const double* W, bool right, doub
   constexpr int NV = SYS::NV;
   double U[NV], F[NV], lmin, lmax;
   SYS::template face_terms<D>(W, sigma_lim, kws, U, F, lmin, lmax);
+  opaque(lmin); opaque(lmax);
   const double omin = lane_xor1(lmin), omax = lane_xor1(lmax);
   const FaceCoef<double> k = face_coef(right ? omin : lmin, right ? omax : lmax, right ? lmin : omin,
                                        right ? lmax : omax, flux_kind);

@@ -85,7 +85,8 @@ struct maxent_solver {
   double* U = nullptr;       // current state (padded SoA)
   double* Us = nullptr;      // stage / ping-pong buffer
   double* stage = nullptr;   // unpadded staging for init / get_moments
-  DevCtrl* ctrl = nullptr;
+  DevCtrl* ctrl = nullptr;       // followed by the rate parts
+  mx::RatePart* rates = nullptr;
   DevCtrl* ctrl_host = nullptr;  // pinned read-back
   bool ready = false;
   bool rate_valid = false;
@@ -327,11 +328,12 @@ extern "C" int maxent_create(const maxent_problem* problem, const maxent_numeric
   if (e == hipSuccess) e = hipMalloc(&s->U, field);
   if (e == hipSuccess) e = hipMalloc(&s->Us, field);
   if (e == hipSuccess) e = hipMalloc(&s->stage, flat);
-  if (e == hipSuccess) e = hipMalloc(&s->ctrl, sizeof(DevCtrl));
+  if (e == hipSuccess) e = hipMalloc(&s->ctrl, mx::CTRL_BYTES + mx::RATE_BYTES);
+  s->rates = (mx::RatePart*)((unsigned char*)s->ctrl + mx::CTRL_BYTES);
   if (e == hipSuccess) e = hipHostMalloc(&s->ctrl_host, sizeof(DevCtrl));
   if (e == hipSuccess) e = hipMemsetAsync(s->U, 0, field, s->stream);
   if (e == hipSuccess) e = hipMemsetAsync(s->Us, 0, field, s->stream);
-  if (e == hipSuccess) e = mx::launch_ctrl_reset(s->ctrl, 0.0, s->stream);
+  if (e == hipSuccess) e = mx::launch_ctrl_reset(s->ctrl, s->rates, 0.0, s->stream);
   if (e != hipSuccess) {
     int code = (e == hipErrorOutOfMemory) ? MAXENT_E_NOMEM : MAXENT_E_DEVICE;
     std::string m = std::string("allocation failed: ") + hipGetErrorString(e);
@@ -371,6 +373,7 @@ static mx::StageParams stage_params(maxent_solver* s, double tau_ref) {
   else { p.ntx = (q.nx + mx::tile_1d(64) - 1) / mx::tile_1d(64); p.nty = 1; }
   p.nblk = p.ntx * p.nty;
   p.ctrl = s->ctrl;
+  p.rates = s->rates;
   return p;
 }
 
@@ -414,7 +417,7 @@ static hipError_t collect_profile(maxent_solver* s) {
 // the control block at time t0, no step taken; the next step uses slot 0
 static hipError_t reset_ctrl(maxent_solver* s, double t0) {
   s->slot = 0;
-  return mx::launch_ctrl_reset(s->ctrl, t0, s->stream);
+  return mx::launch_ctrl_reset(s->ctrl, s->rates, t0, s->stream);
 }
 
 static hipError_t run_cfl(maxent_solver* s) {
@@ -422,7 +425,7 @@ static hipError_t run_cfl(maxent_solver* s) {
   c.U = s->U; c.nx = s->prob.nx; c.ny = s->prob.ny; c.pitch = s->pitch; c.plane = s->plane;
   c.dx = (s->prob.x1 - s->prob.x0) / s->prob.nx;
   c.dy = s->prob.dim == 2 ? (s->prob.y1 - s->prob.y0) / s->prob.ny : 1.0;
-  c.sigma_lim = s->num.sigma_lim; c.kws = s->num.k_ws; c.maxrate = &s->ctrl->maxrate[s->slot % 3];
+  c.sigma_lim = s->num.sigma_lim; c.kws = s->num.k_ws; c.rates = s->rates; c.slot = (int)(s->slot % 3);
   return mx::launch_cfl(s->prob.system, s->prob.dim, c, s->stream);
 }
 
@@ -435,6 +438,7 @@ static mx::IngestParams ingest_params(const maxent_solver* s, int repr, const do
   g.dy = s->prob.dim == 2 ? (s->prob.y1 - s->prob.y0) / s->prob.ny : 1.0;
   g.sigma_lim = s->num.sigma_lim; g.kws = s->num.k_ws;
   g.ctrl = s->ctrl;
+  g.rates = s->rates;
   return g;
 }
 
@@ -652,10 +656,10 @@ extern "C" int maxent_step(maxent_solver* s, int n, double dt, double tau_ref, d
 }
 
 // ------------------------------------------------------------------ no-allocation stepping
-// Device scratch of maxent_step_noalloc: the control block, then one intermediate state.  Each
-// device holds its own copy of this array once the library's code runs on it; host code uses
-// the per-device address from hipGetSymbolAddress, never the array's name.
-static __device__ __align__(256) unsigned char scratch[MAXENT_NOALLOC_SCRATCH_BYTES];
+// Device scratch of maxent_step_noalloc: the control block, then one intermediate state, and
+// the rate parts at the end.  Each device holds its own copy of this array once the library's
+// code runs on it; host code uses the per-device address from hipGetSymbolAddress, never the array's name.
+static __device__ __align__(256) unsigned char scratch[MAXENT_NOALLOC_SCRATCH_BYTES + mx::RATE_BYTES];
 
 constexpr int MAX_DEVICES = 64;
 static void* g_scratch_ptr[MAX_DEVICES] = {};
@@ -682,7 +686,7 @@ extern "C" int maxent_step_noalloc(const maxent_problem* problem, const maxent_n
   if (*why) return noalloc_fail(MAXENT_E_INVAL, why);
   const int nv = problem->system;
   const long long cells = (long long)problem->nx * problem->ny;
-  const long long need = 256 + (long long)nv * cells * (long long)sizeof(double);
+  const long long need = (long long)mx::CTRL_BYTES + (long long)nv * cells * (long long)sizeof(double);
   if (need > (long long)MAXENT_NOALLOC_SCRATCH_BYTES)
     return noalloc_fail(MAXENT_E_INVAL, "problem too large for the no-allocation scratch "
                                         "(nv * nx * ny * 8 + 256 bytes must not exceed "
@@ -715,8 +719,9 @@ extern "C" int maxent_step_noalloc(const maxent_problem* problem, const maxent_n
   t.plane = (long long)problem->ny * problem->nx;
   t.ctrl = (DevCtrl*)base;
   t.U = U;
-  t.Us = (double*)((unsigned char*)base + 256);
-  static_assert(sizeof(DevCtrl) <= 256, "the control block fits its scratch slot");
+  t.Us = (double*)((unsigned char*)base + mx::CTRL_BYTES);
+  t.rates = (mx::RatePart*)((unsigned char*)base + MAXENT_NOALLOC_SCRATCH_BYTES);
+  static_assert(MAXENT_NOALLOC_SCRATCH_BYTES % alignof(mx::RatePart) == 0, "the rate parts are aligned");
   // the control block starts from zero (a kernel, not a memset); the input state is checked
   // in place (conserved in, the same values out) and its first CFL rate reduced
   t.rate_valid = true;
@@ -888,7 +893,7 @@ static hipError_t adjoint_workspace(maxent_solver* s) {
   for (auto& p : t->seg)
     if (e == hipSuccess) e = hipMemsetAsync(p, 0, field, s->stream);
   if (e == hipSuccess) e = take_block(s, t->work, &t->actrl, sizeof(DevCtrl));
-  if (e == hipSuccess) e = mx::launch_ctrl_reset(t->actrl, 0.0, s->stream);
+  if (e == hipSuccess) e = mx::launch_ctrl_reset(t->actrl, nullptr, 0.0, s->stream);
   return e;
 }
 
@@ -935,7 +940,7 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
   // planar-symmetric dJ/dU keep the z-odd adjoint components at zero
   int nonplanar = 1;
   if (s->planar()) {
-    HIP_TRY(s, mx::launch_ctrl_reset(t->actrl, 0.0, s->stream));
+    HIP_TRY(s, mx::launch_ctrl_reset(t->actrl, nullptr, 0.0, s->stream));
     HIP_TRY(s, mx::launch_check_planar(dJ_dU, (long long)nx * ny, t->actrl, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&nonplanar, &t->actrl->asym_z, sizeof(int), hipMemcpyDeviceToHost,
                               s->stream));

@@ -1,6 +1,7 @@
 // Internal interface between the C-ABI runtime and the gfx950 kernels.
 #pragma once
 #include <cmath>
+#include <cstddef>
 #include <hip/hip_runtime.h>
 
 namespace mx {
@@ -13,7 +14,7 @@ namespace mx {
 // workgroups of one launch read and write in any order:
 //   t, step      read from [slot & 1], written to [(slot + 1) & 1] by one workgroup of the first
 //                stage
-//   maxrate      read from [slot % 3]; the last stage reduces the new state's rate into
+//   RatePart     rate read from [slot % 3]; the last stage reduces the new state's rate into
 //                [(slot + 1) % 3], which the step before had cleared; the first stage clears
 //                [(slot + 2) % 3]
 //   fail_step    a step runs while no earlier step failed: a failure of the running step does
@@ -24,7 +25,6 @@ struct DevCtrl {
   double dt_last;
   double t[2];                   // time
   long long step[2];             // steps taken
-  unsigned long long maxrate[3]; // bit pattern of the max CFL rate (positive double)
   long long n_fallback;          // positivity fallbacks
   int status;                    // bit 1 non-finite, bit 2 unrealizable
   int fail_step;                 // first failing step (1-based; 0: the loaded state; INT_MAX: none)
@@ -45,22 +45,39 @@ inline double inv_tau_constant(int mode, double tau_ref, double rho_ref, double 
   return mode == 0 ? 1.0 / (tau_ref * rho_ref * std::sqrt(T_ref)) : 1.0 / tau_ref;
 }
 
+// Reductions over a wavefront; every lane gets the result.  Within rows of 16 lanes by DPP moves
+// (pairs, quads, half rows, rows), the four rows by scalar reads: a chain of about 20
+// instructions without LDS, where six ds_bpermute steps would each wait for LDS.
+template <int CTRL> __device__ __forceinline__ int dpp_move(int x) {
+  return __builtin_amdgcn_mov_dpp(x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL> __device__ __forceinline__ double dpp_move(double x) {
+  const long long b = __double_as_longlong(x);
+  return __longlong_as_double(((long long)dpp_move<CTRL>((int)(b >> 32)) << 32) | (unsigned)dpp_move<CTRL>((int)b));
+}
+__device__ __forceinline__ int read_lane(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
+__device__ __forceinline__ double read_lane(double x, int l) {
+  const long long b = __double_as_longlong(x);
+  return __longlong_as_double(((long long)read_lane((int)(b >> 32), l) << 32) | (unsigned)read_lane((int)b, l));
+}
+template <class T, class F> __device__ __forceinline__ T row_reduce(T v, F f) {
+  v = f(v, dpp_move<0xB1>(v));    // lane ^ 1
+  v = f(v, dpp_move<0x4E>(v));    // lane ^ 2
+  v = f(v, dpp_move<0x141>(v));   // mirrored in half rows
+  return f(v, dpp_move<0x140>(v));  // mirrored in rows
+}
+template <class T, class F> __device__ __forceinline__ T wave_reduce(T v, F f) {
+  v = row_reduce(v, f);
+  return f(f(read_lane(v, 0), read_lane(v, 16)), f(read_lane(v, 32), read_lane(v, 48)));
+}
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_reduce(v, [](double x, double y) { return fmax(x, y); });
 }
-
 __device__ __forceinline__ int wave_or(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
-  return v;
+  return wave_reduce(v, [](int x, int y) { return x | y; });
 }
-
 __device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_reduce(v, [](int x, int y) { return x + y; });
 }
 
 // raise a maximum kept as the bit pattern of a non-negative double.  Device-wide atomics on one
@@ -81,6 +98,21 @@ __device__ __forceinline__ double stage_update(int mode, double cdt, double dt, 
   if (mode == MODE_HEUN2) return __builtin_fma(0.5, Ua, 0.5 * __builtin_fma(dt, L, Ub));
   return __builtin_fma(dt, L, Ua);
 }
+
+// The maximum CFL rate, in RATE_PARTS parts on cache lines of their own: device-wide atomics on
+// one address take their turn (about 25 ns each), and the workgroups of a small grid end
+// together.  A workgroup raises the part of its index; every wavefront of the next step's first
+// stage reads them all and takes the largest.  A step of 800 1D tiles: one word 18.4 us (5
+// moments) and 20.3 (7), 64 parts 13.6 and 16.7, 16 parts 12.8 and 16.0; on large grids 64 lines
+// per wavefront cost as much L2 traffic as the tile (2048 x 2048 2 per cent slower), 16 nothing
+// that can be measured.
+constexpr int RATE_PARTS = 16;   // one row of lanes reads them
+struct alignas(128) RatePart {
+  unsigned long long rate[3];    // bit patterns of non-negative doubles, a slot of the step each
+};
+constexpr size_t CTRL_BYTES = 256;                                            // DevCtrl's place ...
+constexpr size_t RATE_BYTES = RATE_PARTS * sizeof(RatePart);                  // ... and the parts'
+static_assert(sizeof(DevCtrl) <= CTRL_BYTES, "the control block fits its place");
 
 struct StageParams {
   const double* Ub;        // stage input, read with its neighbourhood
@@ -112,6 +144,7 @@ struct StageParams {
   double dt_fixed, t_end, cfl;   // head: fixed dt (> 0) or CFL, end time (> 0)
   double* tape_dt;         // head: where to record the step's dt (null: nowhere)
   DevCtrl* ctrl;
+  RatePart* rates;
 };
 
 struct CflParams {
@@ -120,7 +153,8 @@ struct CflParams {
   long long plane;
   double dx, dy;
   double sigma_lim, kws;
-  unsigned long long* maxrate;
+  RatePart* rates;
+  int slot;                // of the step that reads the rate
 };
 
 struct BatchInst;
@@ -133,6 +167,7 @@ struct IngestParams {
   double dx, dy;
   double sigma_lim, kws;
   DevCtrl* ctrl;
+  RatePart* rates;         // the rate goes to slot 0
   const int* cell_inst;    // batched tubes: the tube of every cell, and the tubes' records
   BatchInst* inst;         // (their maxrate, zero before); null otherwise
 };
@@ -144,12 +179,13 @@ struct IngestParams {
 hipError_t launch_stage(int system, int dim, int order, int precision, bool reduced,
                         const StageParams& p, hipStream_t s);
 hipError_t launch_cfl(int system, int dim, const CflParams& p, hipStream_t s);
-hipError_t launch_ctrl_reset(DevCtrl* c, double t0, hipStream_t s);
+// rates: null for a control block whose rate is not used
+hipError_t launch_ctrl_reset(DevCtrl* c, RatePart* rates, double t0, hipStream_t s);
 // zero the planes a reduced kernel never writes (2, 3, 5, 6, 8, 11, 12: u_y, u_z, P_xy, P_xz,
 // P_yz, q_y, q_z) of a 14-moment field of `plane` doubles per plane (a kernel, no memset);
 // nothing for nv != 14
 hipError_t launch_zero_planes(double* U, long long plane, int nv, hipStream_t s);
-// loads a field into U, checks it, and reduces its CFL rate into ctrl->maxrate[0] (or the
+// loads a field into U, checks it, and reduces its CFL rate into slot 0 of the parts (or the
 // tubes' records); ctrl is reset before
 hipError_t launch_ingest(int system, int dim, const IngestParams& p, hipStream_t s);
 // dst: unpadded [components][ny][nx]

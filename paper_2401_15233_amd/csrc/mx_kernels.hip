@@ -28,7 +28,7 @@
 namespace mx {
 
 // The time step of a step from the control block (its first stage launch; every workgroup
-// comes to the same value): fixed or CFL, clipped to t_end; 0 once the end time is reached or
+// and wavefront comes to the same value): fixed or CFL, clipped to t_end; 0 once the end time is reached or
 // an earlier step failed.
 __device__ __forceinline__ double step_dt(const StageParams& p, int dim) {
   const DevCtrl* c = p.ctrl;
@@ -38,7 +38,8 @@ __device__ __forceinline__ double step_dt(const StageParams& p, int dim) {
     if (p.dt_fixed > 0.0) {
       dt = p.dt_fixed;
     } else {
-      const double m = __longlong_as_double((long long)c->maxrate[p.slot % 3]);
+      const double part = __longlong_as_double((long long)p.rates[threadIdx.x % RATE_PARTS].rate[p.slot % 3]);
+      const double m = read_lane(row_reduce(part, [](double x, double y) { return fmax(x, y); }), 0);
       dt = (dim == 1) ? p.cfl * p.dx / m : p.cfl / m;
       if (!(m > 0.0)) dt = 0.0;
     }
@@ -50,18 +51,20 @@ __device__ __forceinline__ double step_dt(const StageParams& p, int dim) {
   return dt;
 }
 
-// what the step leaves for the next one (one thread of its first stage launch); a step that
+// what the step leaves for the next one (one wavefront of its first stage launch); a step that
 // does nothing hands time, step count and rate on
 __device__ __forceinline__ void step_advance(const StageParams& p, double dt) {
   DevCtrl* c = p.ctrl;
+  RatePart* part = p.rates + threadIdx.x;
   const unsigned now = p.slot & 1, next = now ^ 1;
   const bool go = dt > 0.0;
+  if (!go) part->rate[(p.slot + 1) % 3] = part->rate[p.slot % 3];
+  part->rate[(p.slot + 2) % 3] = 0ull;
+  if (threadIdx.x != 0) return;
   c->t[next] = go ? c->t[now] + dt : c->t[now];
   c->step[next] = c->step[now] + (go ? 1 : 0);
   c->dt = dt;
   if (go) c->dt_last = dt;
-  else c->maxrate[(p.slot + 1) % 3] = c->maxrate[p.slot % 3];
-  c->maxrate[(p.slot + 2) % 3] = 0ull;
   if (p.tape_dt) *p.tape_dt = dt;
 }
 
@@ -131,18 +134,6 @@ void stage_kernel(StageParams p) {
   __shared__ int sFlag[3];
 
   const int b = blockIdx.x;
-  double dt;
-  if (p.dt_replay > 0.0) {
-    dt = p.dt_replay;
-  } else if (p.head) {
-    dt = step_dt(p, DIM);
-    if (b == 0 && threadIdx.x == 0) step_advance(p, dt);
-  } else {
-    dt = p.ctrl->dt;
-  }
-  const bool idle = !(dt > 0.0);   // uniform: time end reached or a failure stopped the run
-  if (idle && !p.copy_on_idle) return;
-  if (threadIdx.x < 3) sFlag[threadIdx.x] = 0;
   int n64 = 0;      // FP64 re-evaluations of face states (mixed precision)
   int nfb = 0;      // positivity fallbacks
   int flag = 0;     // failed checks of the new state
@@ -167,7 +158,45 @@ void stage_kernel(StageParams p) {
   const int gi = min(i0 + ci, p.nx - 1), gj = min(j0 + cj, p.ny - 1);
   const bool own = (t < NC) && (i0 + ci < p.nx) && (j0 + cj < p.ny);
   const long long off = (long long)gj * p.pitch + gi;
-  if (idle) {
+  // The step's dt, and whether there is anything to do.  Two lanes per face (small grids): asked
+  // for after the tile's loads are on their way, so that the latency of the control block and
+  // that of the tile overlap (1000 cells of 5 moments 12.1 -> 11.3 us per step with the early update inputs below); otherwise
+  // before, so that an idle step on a large grid reads no field.
+  double dt;
+  auto begin = [&]() {
+    if (p.dt_replay > 0.0) {
+      dt = p.dt_replay;
+    } else if (p.head) {
+      dt = step_dt(p, DIM);
+      if (b == 0 && threadIdx.x < RATE_PARTS) step_advance(p, dt);
+    } else {
+      dt = p.ctrl->dt;
+    }
+    return dt > 0.0 || p.copy_on_idle;   // uniform: time end reached or a failure stopped the run
+  };
+  if constexpr (LPF == 1) {
+    if (!begin()) return;
+  }
+
+  // 1. tile + halo -> primitives in LDS
+  // (a thread issues the loads of all its cells before it converts any)
+  constexpr int NR = (NL + NT - 1) / NT;
+  double Uh[NR][NV];
+  HaloSrc hs[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    if (t0 + r * NT < NL) {
+      const int c = min(t + r * NT, NL - 1);
+      const int li = c % LX, lj = c / LX;
+      hs[r] = load_cons<SYS>(p, p.Ub, i0 + li - G, (DIM == 2) ? j0 + lj - G : 0, Uh[r]);
+    }
+  }
+  if constexpr (LPF == 2) {
+    asm volatile("" ::: "memory");   // the loads stay above
+    if (!begin()) return;
+  }
+  if (threadIdx.x < 3) sFlag[threadIdx.x] = 0;
+  if (!(dt > 0.0)) {
     if (own) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -177,31 +206,15 @@ void stage_kernel(StageParams p) {
     }
     return;
   }
-
-  // 1. tile + halo -> primitives in LDS
-  // (a thread issues the loads of all its cells before it converts any)
-  {
-    constexpr int NR = (NL + NT - 1) / NT;
-    double Uh[NR][NV];
-    HaloSrc hs[NR];
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      if (t0 + r * NT < NL) {
-        const int c = min(t + r * NT, NL - 1);
-        const int li = c % LX, lj = c / LX;
-        hs[r] = load_cons<SYS>(p, p.Ub, i0 + li - G, (DIM == 2) ? j0 + lj - G : 0, Uh[r]);
-      }
-    }
+  for (int r = 0; r < NR; ++r) {
+    if (t0 + r * NT < NL) {
+      const int c = min(t + r * NT, NL - 1);
+      const int li = c % LX, lj = c / LX;
+      double W[NV];
+      finish_prims<SYS>(p, hs[r], i0 + li - G, (DIM == 2) ? j0 + lj - G : 0, Uh[r], W);
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      if (t0 + r * NT < NL) {
-        const int c = min(t + r * NT, NL - 1);
-        const int li = c % LX, lj = c / LX;
-        double W[NV];
-        finish_prims<SYS>(p, hs[r], i0 + li - G, (DIM == 2) ? j0 + lj - G : 0, Uh[r], W);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) sW[v * NL + c] = W[v];
-      }
+      for (int v = 0; v < NV; ++v) sW[v * NL + c] = W[v];
     }
   }
   __syncthreads();
@@ -236,6 +249,22 @@ void stage_kernel(StageParams p) {
     }
     __syncthreads();
   }
+
+  // the update's inputs from memory: U of the stage and (second-stage combinations) U^n.  Few
+  // registers are in use in the two-lane 1D kernel, so there they are in flight during the faces.
+  constexpr bool EARLY = DIM == 1 && LPF == 2;
+  double Ub[NV], Ua[NV];
+  auto load_own = [&]() {
+    if (t0 < NC) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) Ub[v] = p.Ub[SYS::plane_of(v) * p.plane + off];
+      if (p.mode != MODE_EULER) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Ua[v] = p.Ua[SYS::plane_of(v) * p.plane + off];
+      }
+    }
+  };
+  if constexpr (EARLY) load_own();
 
   // 3a. x faces: face f lies between tile cells (fi-1, fj) and (fi, fj)
   double Fx[NV];
@@ -327,14 +356,9 @@ void stage_kernel(StageParams p) {
   // primitives from the tile in LDS (converted by the load phase, so no second primitive
   // recovery) and the BGK source at the cell centre
   const bool implicit_src = p.use_source && p.src_implicit;
-  double Ub[NV], Ua[NV], Cs[NV];
+  double Cs[NV];
+  if constexpr (!EARLY) load_own();
   if (t0 < NC) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) Ub[v] = p.Ub[SYS::plane_of(v) * p.plane + off];
-    if (p.mode != MODE_EULER) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Ua[v] = p.Ua[SYS::plane_of(v) * p.plane + off];
-    }
     if (p.use_source && !implicit_src) {
       double W[NV];
       lds(ci, cj, W);
@@ -443,7 +467,7 @@ void stage_kernel(StageParams p) {
     if (p.do_cfl) {
       double m = sRed[0];
       for (int k = 1; k < NT / 64; ++k) m = fmax(m, sRed[k]);
-      raise_max(&p.ctrl->maxrate[(p.slot + 1) % 3], m);
+      raise_max(&p.rates[b % RATE_PARTS].rate[(p.slot + 1) % 3], m);
     }
   }
 }
@@ -461,13 +485,14 @@ __device__ __forceinline__ long long padded_index(unsigned k, unsigned nx, int n
 // that the reductions at their ends cost at most 2048 atomics.
 static int field_grid(long long n) { return (int)std::min<long long>((n + 255) / 256, 2048); }
 
-// maximum of a workgroup's rates (256 threads)
-__device__ __forceinline__ void block_max_rate(double rate, unsigned long long* maxrate) {
+// maximum of a workgroup's rates (256 threads) into its part
+__device__ __forceinline__ void block_max_rate(double rate, RatePart* rates, int slot) {
   __shared__ double sRed[4];
   rate = wave_max(rate);
   if ((threadIdx.x & 63) == 0) sRed[threadIdx.x >> 6] = rate;
   __syncthreads();
-  if (threadIdx.x == 0) raise_max(maxrate, fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3])));
+  if (threadIdx.x == 0)
+    raise_max(&rates[blockIdx.x % RATE_PARTS].rate[slot % 3], fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3])));
 }
 
 // ------------------------------------------------------------------ CFL rate of a state
@@ -484,11 +509,12 @@ __global__ __launch_bounds__(256) void cfl_kernel(CflParams p) {
     SYS::cons_to_prim(U, W);
     rate = fmax(rate, cell_rate<SYS, DIM>(W, p.sigma_lim, p.kws, p.dx, p.dy));
   }
-  block_max_rate(rate, p.maxrate);
+  block_max_rate(rate, p.rates, p.slot);
 }
 
 // ------------------------------------------------------------------ control block
-__global__ void ctrl_reset_kernel(DevCtrl* c, double t0) {
+__global__ void ctrl_reset_kernel(DevCtrl* c, RatePart* rates, double t0) {
+  if (rates) rates[threadIdx.x] = RatePart{};
   if (threadIdx.x == 0) {
     DevCtrl z = {};
     z.t[0] = t0;
@@ -584,7 +610,7 @@ __global__ __launch_bounds__(256) void ingest_kernel(IngestParams p) {
       if (np & 2) p.ctrl->asym_y = 1;
     }
   }
-  if constexpr (!BATCH) block_max_rate(rate, &p.ctrl->maxrate[0]);
+  if constexpr (!BATCH) block_max_rate(rate, p.rates, 0);
 }
 
 // Closing moments of a cell state (dimensional, at sigma_bar = max(sigma, sigma_lim)):
@@ -682,15 +708,15 @@ static hipError_t launch_stage_l(const StageParams& p, hipStream_t s) {
 
 // Tiles up to which two lanes share a face: while the doubled workgroups all run at once.  2D
 // planar: two 512-thread workgroups on each of the 256 CUs (two stages and their gaps, one
-// lane -> two: 64 x 64 30.5 -> 27.7 us, 224 x 224 33.0 -> 30.4, 320 x 320 42.4 -> 40.8; beyond,
-// 352 x 352 51.9 -> 57.8, 768 x 768 159 -> 172).  2D with all 14 moments: one (76 KB of LDS each and
-// twice the registers; 64 x 64 37.1 -> 34.9, 192 x 192 39.2 -> 38.1, but 256 x 256 51.8 -> 54.1).
-// 1D: two-wave workgroups, eight waves per SIMD of the 1024 with seven moments or fewer (1000
-// cells of 5 moments 13.4 -> 12.7, 64000 25.3 -> 20.3, 256000 37.9 -> 33.4; axial 16.0 -> 14.8,
-// 26.7 -> 23.4, 43.1 -> 42.7), two with 14 (1000 cells 21.6 -> 19.7, 48000 27.8 -> 26.6, but 96000
-// 36.9 -> 43.8).
+// lane -> two: 64 x 64 30.2 -> 27.0 us, 224 x 224 30.9 -> 27.8, 320 x 320 41.1 -> 40.9; beyond,
+// 352 x 352 50.7 -> 55.5, 768 x 768 159 -> 170).  2D with all 14 moments: one (76 KB of LDS each and
+// twice the registers; 64 x 64 36.6 -> 34.5, 192 x 192 37.2 -> 36.1, but 256 x 256 50.2 -> 54.1).
+// 1D: two-wave workgroups, four waves per SIMD of the 1024 with seven moments or fewer (1000
+// cells of 5 moments 12.2 -> 11.3, 96000 17.6 -> 16.5, 192000 22.7 -> 23.6; axial 14.6 -> 13.5,
+// 23.0 -> 21.3, 29.8 -> 34.8), two with 14 (1000 cells 20.3 -> 18.4, 48000 24.1 -> 23.5, but 64000
+// 29.7 -> 35.7).
 constexpr int two_lane_tiles(int nv, int dim) {
-  if (dim == 1) return nv <= 7 ? 4096 : 1024;
+  if (dim == 1) return nv <= 7 ? 2048 : 1024;
   return nv <= 10 ? 512 : 256;
 }
 
@@ -734,8 +760,8 @@ hipError_t launch_cfl(int system, int dim, const CflParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_ctrl_reset(DevCtrl* c, double t0, hipStream_t s) {
-  hipLaunchKernelGGL(ctrl_reset_kernel, dim3(1), dim3(64), 0, s, c, t0);
+hipError_t launch_ctrl_reset(DevCtrl* c, RatePart* rates, double t0, hipStream_t s) {
+  hipLaunchKernelGGL(ctrl_reset_kernel, dim3(1), dim3(RATE_PARTS), 0, s, c, rates, t0);
   return hipGetLastError();
 }
 

@@ -45,9 +45,9 @@ def field(kind, nx, ny):
     ('full', 33, 16, 9, 13, dict(flux='rusanov')),
     ('full', 61440, 1, 2, 1, dict()),                                         # 1024 tiles
     ('full', 61, 1, 1100, 1, dict(order=1)),
-    ('axial', 245760, 1, 2, 1, dict()),                                       # 4096 tiles
+    ('axial', 122880, 1, 2, 1, dict()),                                       # 2048 tiles
     ('axial', 59, 1, 4400, 1, dict(limiter='vanalbada')),
-    ('five', 245760, 1, 2, 1, dict(order=1)),
+    ('five', 122880, 1, 2, 1, dict(order=1)),
     ('five', 121, 1, 2200, 1, dict(integrator='midpoint')),
 ])
 def test_repeated_field_gives_repeated_solution(gpu_lib, kind, nx, ny, rx, ry, opt):

@@ -50,4 +50,16 @@ hipError_t launch_adjoint_reduce(const AdjParams& a, hipStream_t s);
 int adjoint_update_blocks(int nx, int ny);
 hipError_t launch_pad_copy(const double* src, double* dst, int nv, int nx, int ny, int pitch,
                            int to_padded, hipStream_t s);
+// fields to clear in one launch
+struct FieldList {
+  static constexpr int MAX = 16;
+  double* p[MAX];
+  int n = 0;
+  void add(double* f) { p[n++] = f; }
+};
+// zero the first `len` doubles of every listed field (a kernel, no memset)
+hipError_t launch_zero_fields(const FieldList& l, long long len, hipStream_t s);
+// resets the control block of the replayed stages and zeroes the n partial sums
+hipError_t launch_adjoint_begin(DevCtrl* c, double* part, int n, hipStream_t s);
+
 }  // namespace mx

@@ -72,6 +72,7 @@ struct TapeState {
   double* part = nullptr;
   double* grad = nullptr;
   DevCtrl* actrl = nullptr;              // control block of the replayed stages
+  bool lam_full = false;                 // lam may be non-zero where a planar adjoint writes nothing
 };
 
 struct maxent_solver {
@@ -887,13 +888,20 @@ static hipError_t adjoint_workspace(maxent_solver* s) {
   if (e == hipSuccess) e = take_block(s, t->work, &t->vsy, (size_t)eplane * sizeof(int));
   if (e == hipSuccess) e = take_block(s, t->work, &t->part, (size_t)3 * nb * sizeof(double));
   if (e == hipSuccess) e = take_block(s, t->work, &t->grad, 3 * sizeof(double));
-  for (auto& p : t->lam)
-    if (e == hipSuccess) e = hipMemsetAsync(p, 0, field, s->stream);
-  // the recomputed stage states: the reduced kernels leave the moments they drop as they are
-  for (auto& p : t->seg)
-    if (e == hipSuccess) e = hipMemsetAsync(p, 0, field, s->stream);
   if (e == hipSuccess) e = take_block(s, t->work, &t->actrl, sizeof(DevCtrl));
-  if (e == hipSuccess) e = mx::launch_ctrl_reset(t->actrl, nullptr, 0.0, s->stream);
+  // adjoint states and recomputed stage states start from zero: the planar and reduced kernels
+  // leave the moments they drop as they are.  One launch for every 16 of them
+  mx::FieldList l;
+  for (auto& p : t->lam) l.add(p);
+  for (auto& p : t->seg) {
+    if (l.n == mx::FieldList::MAX) {
+      if (e == hipSuccess) e = mx::launch_zero_fields(l, (long long)s->nv * s->plane, s->stream);
+      l.n = 0;
+    }
+    l.add(p);
+  }
+  if (e == hipSuccess) e = mx::launch_zero_fields(l, (long long)s->nv * s->plane, s->stream);
+  t->lam_full = false;
   return e;
 }
 
@@ -926,9 +934,9 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
   } catch (const std::bad_alloc&) {
     return fail(s, MAXENT_E_NOMEM, "host allocation failed");
   }
-  if (n > 0)
-    HIP_TRY(s, hipMemcpyAsync(dts.data(), t->d_dt, (size_t)n * sizeof(double), hipMemcpyDeviceToHost,
-                              s->stream));
+  // the control block and the partial sums of the parameter gradients start from zero
+  const int n_part = 3 * mx::adjoint_update_blocks(nx, ny);
+  HIP_TRY(s, mx::launch_adjoint_begin(t->actrl, t->part, n_part, s->stream));
   // lambda <- dJ/dU_final
   const size_t flat = (size_t)s->nv * nx * ny * sizeof(double);
   if (!dJ_on_device || !local_pointer(s, dJ_dU)) {
@@ -940,21 +948,22 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
   // planar-symmetric dJ/dU keep the z-odd adjoint components at zero
   int nonplanar = 1;
   if (s->planar()) {
-    HIP_TRY(s, mx::launch_ctrl_reset(t->actrl, nullptr, 0.0, s->stream));
     HIP_TRY(s, mx::launch_check_planar(dJ_dU, (long long)nx * ny, t->actrl, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&nonplanar, &t->actrl->asym_z, sizeof(int), hipMemcpyDeviceToHost,
                               s->stream));
   }
+  if (n > 0)
+    HIP_TRY(s, hipMemcpyAsync(dts.data(), t->d_dt, (size_t)n * sizeof(double), hipMemcpyDeviceToHost,
+                              s->stream));
   HIP_TRY(s, hipStreamSynchronize(s->stream));
   const bool pl = s->planar() && nonplanar == 0;
   double* lamA = t->lam[0];
   double* lamB = t->lam[1];
   double* lamC = t->lam[2];
-  if (pl)  // never written in a planar run: they start (and stay) zero
+  if (pl && t->lam_full)  // never written in a planar run: they start (and stay) zero
     for (double* l : {lamA, lamB, lamC}) HIP_TRY(s, mx::launch_zero_planes(l, s->plane, 14, s->stream));
+  t->lam_full = !pl;
   HIP_TRY(s, mx::launch_pad_copy(dJ_dU, lamA, s->nv, nx, ny, s->pitch, 1, s->stream));
-  HIP_TRY(s, hipMemsetAsync(t->part, 0, (size_t)3 * mx::adjoint_update_blocks(nx, ny) * sizeof(double),
-                            s->stream));
 
   mx::AdjParams a;
   std::memset(&a, 0, sizeof(a));

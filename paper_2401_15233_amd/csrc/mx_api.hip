@@ -554,13 +554,6 @@ extern "C" int maxent_init_state(maxent_solver* s, int repr, const double* src, 
     int rc = batch_order(s);
     if (rc) return rc;
   }
-  // the reduced kernels never write the moments they leave out: the stage / ping-pong buffer
-  // holds zeros there, so that a forward-Euler swap hands back a symmetric state (it starts so;
-  // only a full kernel writes those planes)
-  if (s->us_dirty) {
-    HIP_TRY(s, mx::launch_zero_planes(s->Us, s->plane, s->nv, s->stream));
-    s->us_dirty = false;
-  }
   int rc = read_ctrl(s);
   if (rc) return rc;
   s->asym_z = s->ctrl_host->asym_z != 0;
@@ -587,13 +580,21 @@ static hipError_t enqueue_steps(maxent_solver* s, int n, double dt, double tau_r
   TapeState* tape = s->tape;
   const size_t field_bytes = (size_t)s->nv * s->plane * sizeof(double);
   const bool cfl_mode = !(dt > 0);
-  if (!s->reduced()) s->us_dirty = true;
+  hipError_t e = hipSuccess;
+  // the reduced kernels never write the moments they leave out: the ping-pong buffer holds zeros
+  // there, so that a forward-Euler swap hands back a symmetric state (it starts so; only a full
+  // kernel writes those planes; the two-stage integrators never swap)
+  if (!s->reduced()) {
+    s->us_dirty = true;
+  } else if (s->us_dirty && s->num.integrator == MAXENT_FE) {
+    if ((e = mx::launch_zero_planes(s->Us, s->plane, s->nv, s->stream)) != hipSuccess) return e;
+    s->us_dirty = false;
+  }
   mx::StageParams p = stage_params(s, tau_ref);
   const int sys = s->prob.system, dim = s->prob.dim, ord = s->num.order;
   p.dt_fixed = cfl_mode ? 0.0 : dt;
   p.t_end = t_end > 0 ? t_end : 0.0;
   p.cfl = s->num.cfl;
-  hipError_t e = hipSuccess;
   if (cfl_mode && !s->rate_valid && (e = run_cfl(s)) != hipSuccess) return e;
   for (int k = 0; k < n; ++k) {
     p.slot = s->slot;
@@ -1204,7 +1205,6 @@ static hipError_t batch_grid(const maxent_solver* s, int* grid) {
 // enqueue `steps` batched steps on stream st
 static hipError_t batch_enqueue(maxent_solver* s, int steps, int grid, hipStream_t st) {
   BatchState* b = s->batch;
-  if (!s->reduced()) s->us_dirty = true;
   mx::BatchParams p = batch_params(s);
   const bool mid = s->num.integrator == MAXENT_MIDPOINT;
   const int prec = s->num.precision == MAXENT_MIXED ? 1 : 0;

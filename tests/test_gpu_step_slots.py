@@ -44,3 +44,29 @@ def test_split_runs_equal_one_run(gpu_lib, kind, nx, ny, integrator):
     assert c['dt_last'] == d['dt_last']
     assert torch.equal(s.get('conserved'), end)
     s.close()
+
+
+@pytest.mark.parametrize('integrator', ['fe', 'ssprk2'])
+@pytest.mark.parametrize('kind, nx, ny', [('planar', 40, 33), ('axial', 130, 1)])
+@pytest.mark.parametrize('n', [1, 2, 3])
+def test_a_symmetric_state_after_a_full_one(gpu_lib, kind, nx, ny, integrator, n):
+    """The planes a reduced kernel does not write are zero in the state it hands back, whichever
+    kernels ran in the solver before."""
+    s = solver(gpu_lib, kind, nx, ny, integrator=integrator)
+    s.step(n, tau_ref=0.05)
+    ref = s.get('conserved').clone()
+    s.init_state(np.ascontiguousarray(field('full', nx, ny)))
+    s.step(3, tau_ref=0.05)
+    s.init_state(np.ascontiguousarray(field(kind, nx, ny)))
+    info = s.step(n, tau_ref=0.05)
+    assert info['reduced'] > 0
+    assert torch.equal(s.get('conserved'), ref)
+    # the full kernels on the same state, then the reduced ones from where they ended
+    s.set_reduced(False)
+    s.init_state(np.ascontiguousarray(field(kind, nx, ny)))
+    s.step(3, tau_ref=0.05)
+    s.set_reduced(True)
+    s.step(n, tau_ref=0.05)
+    odd = s.get('conserved')[[3, 6, 8, 12] + ([2, 5, 11] if kind == 'axial' else [])]
+    assert int((odd != 0).sum()) == 0
+    s.close()

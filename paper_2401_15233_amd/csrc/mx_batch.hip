@@ -207,6 +207,8 @@ void batch_stage_kernel(BatchParams p) {
   int n64 = 0, nfb = 0;
   for (int k = k0; k < k1; ++k) {
     const double dt = cur.dt;
+    // (issue priority by phase as in the single kernel: 9.54 -> 9.47 ms)
+    __builtin_amdgcn_s_setprio(3);
     // 1. tile + halo -> primitives
 #pragma unroll 1
     for (int r = 0; r < CPT; ++r) {
@@ -266,6 +268,7 @@ void batch_stage_kernel(BatchParams p) {
       load_cell(nxt, t, Unext, refl_next);
     }
 
+    __builtin_amdgcn_s_setprio(0);
     // 3. faces: face fi lies between tile cells fi - 1 and fi.  (Mixed precision: the loop
     // stays a loop for CPT = 1 too, so that the compiler fuses products and sums there as it does
     // in the other kernels.)
@@ -298,6 +301,7 @@ void batch_stage_kernel(BatchParams p) {
     };
     __syncthreads();
 
+    __builtin_amdgcn_s_setprio(1);
     // 4. update.  PIPE: of the thread's own cell, and of the primitive tile only that cell is
     // still read, which the same thread overwrites for the next tile: no barrier between
     int flag = 0;

@@ -9,9 +9,9 @@ namespace mx {
 // Device-resident control block: time step, time and status live on the device so that a
 // sequence of steps needs no host round trip, and every step's first stage launch works out the
 // step's dt itself (no launch of its own: the separate one-wavefront kernel that did it cost 2 to
-// 4 us and a launch gap per step, 9.9 us against 5.9 for a step of 1000 cells).  What a step reads and what it leaves for the next
-// one stand in different slots, picked by the host's step counter `slot`, because the
-// workgroups of one launch read and write in any order:
+// 4 us and a launch gap per step, 9.9 us against 5.9 for a step of 1000 cells).  What a step
+// reads and what it leaves for the next one stand in different slots, picked by the host's step
+// counter `slot`, because the workgroups of one launch read and write in any order:
 //   t, step      read from [slot & 1], written to [(slot + 1) & 1] by one workgroup of the first
 //                stage
 //   RatePart     rate read from [slot % 3]; the last stage reduces the new state's rate into

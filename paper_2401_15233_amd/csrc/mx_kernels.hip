@@ -78,8 +78,8 @@ __device__ __forceinline__ double cell_rate(const double* W, double sigma_lim, d
 // ------------------------------------------------------------------ stage kernel
 // One stage of a tile: primitives of the tile and its halo in LDS, limiter factors, face fluxes,
 // update, checks and (last stage) the CFL rate of the new state.  Bound by FP64 VALU work; the
-// planar system runs 3250 VALU instructions per cell and stage on large grids at 85 per cent
-// of the issue rate (2048 x 2048: 0.47 ms first stage, 0.54 ms second).  LPF lanes share a face:
+// planar system runs 3200 VALU instructions per cell and stage on large grids at 84 per cent
+// of the issue rate (2048 x 2048: 0.46 ms first stage, 0.53 ms second).  LPF lanes share a face:
 // one, or (grids that leave the chip partly idle, where a tile's latency is the time of the
 // stage) two, each with the state of one side, in twice as many threads.
 //
@@ -160,8 +160,8 @@ void stage_kernel(StageParams p) {
   const long long off = (long long)gj * p.pitch + gi;
   // The step's dt, and whether there is anything to do.  Two lanes per face (small grids): asked
   // for after the tile's loads are on their way, so that the latency of the control block and
-  // that of the tile overlap (1000 cells of 5 moments 12.1 -> 11.3 us per step with the early update inputs below); otherwise
-  // before, so that an idle step on a large grid reads no field.
+  // that of the tile overlap (with the early update inputs below, 1000 cells of 5 moments 12.1 ->
+  // 11.3 us per step); otherwise before, so that an idle step on a large grid reads no field.
   double dt;
   auto begin = [&]() {
     if (p.dt_replay > 0.0) {
@@ -232,27 +232,59 @@ void stage_kernel(StageParams p) {
     for (int v = 0; v < NV; ++v) W[v] = sW[v * NL + c];
   };
 
-  // 2. common limiter factors, x and y items in one sweep (542 items on 256 threads take
-  // three rounds; two separate loops would take four)
+  // 2. common limiter factors of x items (cells -1 .. TX of each row) and y items
   if constexpr (ORDER == 2) {
-    constexpr int NPT = (DIM == 2) ? NPX + NPY : NPX;
-#pragma unroll 1
-    for (int r0 = 0; t0 + r0 < NPT; r0 += NT) {
-      const int c = min(t + r0, NPT - 1);
-      const bool isx = c < NPX;
-      const int cy = c - NPX;
-      const int ti = isx ? c % (TX + 2) - 1 : cy % TX, tj = isx ? c / (TX + 2) : cy / TX - 1;
-      const int di = isx ? 1 : 0, dj = isx ? 0 : 1;
-      double Wm[NV], Wc[NV], Wp[NV];
-      lds(ti - di, tj - dj, Wm); lds(ti, tj, Wc); lds(ti + di, tj + dj, Wp);
+    auto limiter = [&](int ti, int tj, int di, int dj, const double* Wc, bool mine) {
+      double Wm[NV], Wp[NV];
+      lds(ti - di, tj - dj, Wm); lds(ti + di, tj + dj, Wp);
       double phi = limiter_factor<SYS>(Wm, Wc, Wp, p.limiter);
       if (p.fallback && phi > 0.0 && !faces_admissible<SYS>(Wm, Wc, Wp, phi)) {
         phi = 0.0;
-        const bool mine = isx ? (ti >= 0 && ti < TX) : (tj >= 0 && tj < TY);
-        if (mine && t + r0 < NPT && i0 + ti < p.nx && j0 + tj < p.ny) ++nfb;
+        if (mine && i0 + ti < p.nx && j0 + tj < p.ny) ++nfb;
       }
-      if (isx) sPx[c] = phi;
-      else sPy[cy] = phi;
+      return phi;
+    };
+    if constexpr (DIM == 2 && LPF == 1) {
+      // a thread takes both items of its cell, whose natural scales they share, and the 62
+      // items of the ring go to one wavefront: 5 wavefront rounds, two of them double, where one
+      // sweep over all 542 items takes 9 (2048 x 2048 with load and read 1357 -> 1341 us, 515 x 387
+      // with 14 moments 251 -> 247)
+      if (t0 < NC) {
+        double Wc[NV];
+        lds(ci, cj, Wc);
+        const double px = limiter(ci, cj, 1, 0, Wc, t < NC);
+        const double py = limiter(ci, cj, 0, 1, Wc, t < NC);
+        sPx[cj * (TX + 2) + ci + 1] = px;
+        sPy[(cj + 1) * TX + ci] = py;
+      }
+      constexpr int RING = 2 * (TX + TY);
+      static_assert(RING <= 64 && NT >= 64, "the ring is one wavefront's");
+      if (t0 == NT - 64) {
+        const int h = min(t - t0, RING - 1), g = h - 2 * TY;
+        const bool isx = g < 0;
+        const int ti = isx ? ((h & 1) ? TX : -1) : g % TX, tj = isx ? h >> 1 : (g < TX ? -1 : TY);
+        double Wc[NV];
+        lds(ti, tj, Wc);
+        const double phi = limiter(ti, tj, isx ? 1 : 0, isx ? 0 : 1, Wc, false);
+        if (isx) sPx[tj * (TX + 2) + ti + 1] = phi;
+        else sPy[(tj + 1) * TX + ti] = phi;
+      }
+    } else {
+      // x and y items in one sweep (two lanes per face: 542 items on 512 threads)
+      constexpr int NPT = (DIM == 2) ? NPX + NPY : NPX;
+#pragma unroll 1
+      for (int r0 = 0; t0 + r0 < NPT; r0 += NT) {
+        const int c = min(t + r0, NPT - 1);
+        const bool isx = c < NPX;
+        const int cy = c - NPX;
+        const int ti = isx ? c % (TX + 2) - 1 : cy % TX, tj = isx ? c / (TX + 2) : cy / TX - 1;
+        double Wc[NV];
+        lds(ti, tj, Wc);
+        const bool mine = t + r0 < NPT && (isx ? (ti >= 0 && ti < TX) : (tj >= 0 && tj < TY));
+        const double phi = limiter(ti, tj, isx ? 1 : 0, isx ? 0 : 1, Wc, mine);
+        if (isx) sPx[c] = phi;
+        else sPy[cy] = phi;
+      }
     }
     __syncthreads();
   }

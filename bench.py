@@ -644,7 +644,7 @@ def main():
                      'traffic_unit': 'HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, scaled by a '
                                      'plain copy of known size)',
                      'valu_busy': measured_valu_busy(),
-                     'kernel': f'stage_kernel<{sysname},2,2,{0 if head == "fp64" else 1},16,15,256> ({head})',
+                     'kernel': f'stage_kernel<{sysname},2,2,{0 if head == "fp64" else 1},16,15,256,1> ({head})',
                      'avg_launch_ms': avg_stage_ms, 'launches': launches,
                      'flops_per_launch': flops_per_launch,
                      'hbm_algorithmic_bytes_per_launch': bytes_per_launch,

@@ -960,7 +960,7 @@ struct Sys5 {
     n.T0 = W[2] * mrcp(W[0]);
     const T ic = mrsqrt(n.T0);
     n.kc = kws * (n.T0 * ic);
-    n.qh = W[3] * ip * ic;
+    n.qh = W[3] * (ip * ic);
     sigma_bar(T(3) - W[4] * (W[0] * ip * ip), n.qh * n.qh, T(1), sigma_lim, n.s);
   }
   template <class T> MX_HD static void speeds(const Norm<T>& n, T u, T& lmin, T& lmax) {

@@ -490,6 +490,8 @@ static mx::BatchParams batch_params(maxent_solver* s) {
   p.bc_lo = s->prob.bc[0];
   p.bc_hi = s->prob.bc[1];
   p.tau_mode = s->prob.tau_mode;
+  p.rho_ref = s->prob.rho_ref;
+  p.T_ref = s->prob.T_ref;
   p.sigma_lim = s->num.sigma_lim;
   p.kws = s->num.k_ws;
   p.limiter = s->num.limiter;
@@ -1155,6 +1157,7 @@ extern "C" int maxent_create_batch(const maxent_problem* common, const maxent_nu
     r.t_end = inst[i].t_end;
     r.dx = (inst[i].x1 - inst[i].x0) / inst[i].n_cells;
     r.inv_dx = 1.0 / r.dx;
+    r.tau_ref = inst[i].tau_ref;
     r.inv_tau_ref = inst[i].tau_ref > 0.0 ? mx::inv_tau_constant(p.tau_mode, inst[i].tau_ref, p.rho_ref, p.T_ref) : 0.0;
     r.off = off;
     r.n = inst[i].n_cells;

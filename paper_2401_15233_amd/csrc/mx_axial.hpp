@@ -21,25 +21,28 @@ namespace mx {
 
 struct Sys14A {
   static constexpr int NV = 7;
+  static constexpr bool TUBE = true;
   static constexpr bool JETS = false;
   MX_HD static constexpr int plane_of(int v) {
     return v < 2 ? v : (v == 2 ? 4 : (v == 3 ? 7 : (v == 4 ? 9 : (v == 5 ? 10 : 13))));
   }
 
-  template <class T> MX_HD static void cons_to_prim(const T* U, T* W) {
+  // (TUBE: the roundings are fixed.  fused: rho u_x^2 is subtracted from U_2 without a rounding of
+  // its own; the CFL rate of a new state takes it rounded)
+  template <class T> MX_HD static void cons_to_prim(const T* U, T* W) { cons_to_prim(U, W, true); }
+  template <class T> MX_HD static void cons_to_prim(const T* U, T* W, bool fused) {
+#pragma clang fp contract(off)
     T rho = U[0];
-    T ir = mrcp(rho);
+    T ir = mrcp2(rho);
     T ux = U[1] * ir;
-    T Pxx = U[2] - rho * (ux * ux);
-    T Pyy = U[3], Pzz = U[4];
     T uu = ux * ux;
-    T trP = Pxx + Pyy + Pzz;
+    T ruu = rho * uu;
+    T Pxx = fused ? dfma(-rho, uu, U[2]) : U[2] - ruu;
+    T trP = Pxx + U[3] + U[4];
     T Pux = Pxx * ux;
-    T qx = U[5] - (rho * uu) * ux - trP * ux - T(2) * Pux;
-    T uPu = ux * Pux;
-    T uq = ux * qx;
-    W[0] = rho; W[1] = ux; W[2] = Pxx; W[3] = Pyy; W[4] = Pzz; W[5] = qx;
-    W[6] = U[6] - rho * uu * uu - T(2) * uu * trP - T(4) * uPu - T(4) * uq;
+    T qx = dfma(T(-2), Pux, dfma(-ux, trP, dfma(-ux, ruu, U[5])));
+    W[0] = rho; W[1] = ux; W[2] = Pxx; W[3] = U[3]; W[4] = U[4]; W[5] = qx;
+    W[6] = dfma(T(-4), ux * qx, dfma(T(-4), ux * Pux, dfma(-(T(2) * uu), trP, dfma(-uu, ruu, U[6]))));
   }
 
   template <class T> MX_HD static void prim_to_cons(const T* W, T* U) {
@@ -67,7 +70,7 @@ struct Sys14A {
   MX_HD static constexpr bool admissibility_var(int v) { return v == 0 || (v >= 2 && v <= 4); }
   template <class T> MX_HD static bool admissible_cons(const T* U) {
     T rho = U[0];
-    T ux = U[1] * mrcp(rho);
+    T ux = U[1] * mrcp2(rho);
     T Pxx = U[2] - rho * (ux * ux);
     return (rho > T(0)) && (Pxx > T(0)) && (U[3] > T(0)) && (U[4] > T(0));
   }
@@ -75,13 +78,13 @@ struct Sys14A {
   template <class T> MX_HD static void scales(const T* W, T* sc) {
     T rho = tabs(W[0]);
     T p = tabs(W[2] + W[3] + W[4]) * T(1.0 / 3.0);
-    T T0 = p * mrcp(rho);
-    T c = T0 * mrsqrt(T0);
+    T c = msqrt2(mdiv2(p, rho));
+    T c3 = rho * c * c * c;
     sc[0] = rho;
     sc[1] = c;
     sc[2] = sc[3] = sc[4] = p;
-    sc[5] = p * c;
-    sc[6] = p * T0;
+    sc[5] = c3;
+    sc[6] = c3 * c;
   }
 
   // components odd under reflection of x
@@ -100,10 +103,10 @@ struct Sys14A {
   template <class T> MX_HD static void core(const T* W, T sigma_lim, Core<T>& k) {
     k.rho = W[0];
     T p = (W[2] + W[3] + W[4]) * T(1.0 / 3.0);
-    T irho = mrcp(k.rho);
-    T ip = mrcp(p);
-    k.c = msqrt(p * irho);
-    T ic = msqrt(k.rho * ip);          // 1 / c
+    T irho = mrcp2(k.rho);
+    T ip = mrcp2(p);
+    k.c = msqrt2(p * irho);
+    T ic = msqrt2(k.rho * ip);          // 1 / c
 #pragma unroll
     for (int m = 0; m < 3; ++m) k.Ph[m] = W[2 + m] * ip;
     T is3 = irho * (ic * ic * ic);     // 1 / (rho c^3)
@@ -113,7 +116,7 @@ struct Sys14A {
 #pragma unroll
     for (int m = 0; m < 3; ++m) k.P2[m] = k.Ph[m] * k.Ph[m];
     k.t2 = k.P2[0] + k.P2[1] + k.P2[2];
-    k.z = k.qh * mrcp(k.Ph[0]);
+    k.z = k.qh * mrcp2(k.Ph[0]);
     T D = k.qh * k.z;
     T A = T(2) * k.t2 + k.t1 * k.t1 - Rh;
     T X = A * A + T(8) * k.t2 * D;
@@ -125,7 +128,7 @@ struct Sys14A {
   // mixed precision: the bracket A and the traces it needs in FP64, the rest in FP32
   MX_HD static void core_mixed(const double* W, float sigma_lim, Core<float>& k) {
     double p = (W[2] + W[3] + W[4]) * (1.0 / 3.0);
-    double ip = mrcp(p);
+    double ip = mrcp2(p);
     double Ph[3], P2[3];
 #pragma unroll
     for (int m = 0; m < 3; ++m) { Ph[m] = W[2 + m] * ip; P2[m] = Ph[m] * Ph[m]; }
@@ -135,8 +138,8 @@ struct Sys14A {
     k.rho = (float)W[0];
     float irho = 1.0f / k.rho;
     float ipf = (float)ip;
-    k.c = msqrt((float)p * irho);
-    float ic = msqrt(k.rho * ipf);
+    k.c = msqrt2((float)p * irho);
+    float ic = msqrt2(k.rho * ipf);
 #pragma unroll
     for (int m = 0; m < 3; ++m) { k.Ph[m] = (float)Ph[m]; k.P2[m] = (float)P2[m]; }
     k.t1 = (float)t1;
@@ -157,7 +160,7 @@ struct Sys14A {
   MX_HD static void closure_dir(const Core<T>& k, T* Qd, T* Rd, T& Sd) {
     static_assert(d == 0, "flows along x only");
     // w = Cm^-1 q with Cm = 2 tr(P^2) I + 4 P^2 (diagonal; w_y = w_z = 0)
-    T w = k.qh * mrcp(T(4) * k.P2[0] + T(2) * k.t2);
+    T w = k.qh * mrcp2(T(4) * k.P2[0] + T(2) * k.t2);
     T P2z = k.P2[0] * k.z;
     T zP2z = k.z * P2z;
     T wz = w * k.z;
@@ -167,7 +170,7 @@ struct Sys14A {
     Qd[0] = T(2) * (w * k.P2[0] + w * k.P2[0] + w * k.P2[0]) * s3;
     Qd[1] = T(2) * (w * k.P2[1]) * s3;
     Qd[2] = T(2) * (w * k.P2[2]) * s3;
-    T isb = mrcp(k.sb);
+    T isb = mrcp2(k.sb);
     T Qz = T(2) * (w * P2z + w * P2z + wz * k.P2[0]);
     Rd[0] = (Qz * isb + T(2) * (T(1) - k.sb) * k.P2[0] + k.t1 * k.Ph[0]) * s4;
     T Pw = k.Ph[0] * w;
@@ -178,7 +181,7 @@ struct Sys14A {
     T Wq = (T(2) * t1 * t1 * t1 + T(12) * t3 - T(2) * t2 * t1) * w + (T(14) * t2 - T(6) * t1 * t1) * Pw +
            T(20) * t1 * P2w + T(20) * P3w;
     T Qzz = T(2) * (w * zP2z + T(2) * wz * P2z);
-    T rsb = msqrt(k.sb);
+    T rsb = msqrt2(k.sb);
     Sd = (Qzz * (isb * isb) + T(2) * rsb * t1 * k.qh + (T(1) - rsb) * Wq) * s5;
   }
 
@@ -222,7 +225,7 @@ struct Sys14A {
       b = T(0.9) * Pdd * mexp(T(-0.5) * mexp(T(1.4) * lP));
     }
     BYEC<T> g = byec(sw, Pdd);
-    T pref = mdiv(a * sw + b, T(2) * sw);
+    T pref = mdiv2(a * sw + b, T(2) * sw);
     T base = T(4) * sw * sw * g.Y;
     T zmax = qd;
     T zmin = -qd;
@@ -232,77 +235,157 @@ struct Sys14A {
     lmin = ud - kws * Lmin * k.c;
   }
 
-  // dimensionless state of the FP64 flux and wave speeds (the formulas stand at Sys14::Norm;
-  // with a diagonal P* the products with z = h / P*_xx need no division)
-  template <class T> struct Norm {
-    T trP, pT, T0, ic, kc, Ph[3], h, P2[3], t2;
-    SigmaBar<T> s;
-  };
-  template <class T> MX_HD static void norm(const T* W, T sigma_lim, T kws, Norm<T>& n) {
-    n.trP = W[2] + W[3] + W[4];
-    const T p = n.trP * T(1.0 / 3.0);
-    const T ip = mrcp(p);
-    n.T0 = p * mrcp(W[0]);
-    n.pT = p * n.T0;
-    n.ic = mrsqrt(n.T0);
-    const T ic2 = W[0] * ip;
-    n.kc = kws * (n.T0 * n.ic);
+  // ---- FP64 face state and CFL rate: core, closure, flux, conserved state and wave speeds with their
+  // roundings fixed (single precision keeps the functions above)
+  // (face: t2 sums P*_xx^2 after P*_yy^2; the CFL rate in the order of the components)
+  template <class T> MX_HD static void tube_core(const T* W, T sigma_lim, bool face, Core<T>& k) {
+#pragma clang fp contract(off)
+    k.rho = W[0];
+    T p = (W[2] + W[3] + W[4]) * T(1.0 / 3.0);
+    T irho = mrcp2(k.rho);
+    T ip = mrcp2(p);
+    k.c = msqrt2(p * irho);
+    T ic = msqrt2(k.rho * ip);          // 1 / c
 #pragma unroll
-    for (int m = 0; m < 3; ++m) { n.Ph[m] = W[2 + m] * ip; n.P2[m] = n.Ph[m] * n.Ph[m]; }
-    n.h = W[5] * ip;
-    const T t1 = n.Ph[0] + n.Ph[1] + n.Ph[2];
-    n.t2 = n.P2[0] + n.P2[1] + n.P2[2];
-    const T D = n.h * (n.h * mrcp(n.Ph[0])) * ic2;
-    sigma_bar(tfma(t1, t1, T(2) * n.t2) - W[6] * (ic2 * ip), D, n.t2, sigma_lim, n.s);
+    for (int m = 0; m < 3; ++m) k.Ph[m] = W[2 + m] * ip;
+    T is3 = irho * (ic * ic * ic);     // 1 / (rho c^3)
+    k.qh = W[5] * is3;
+    k.t1 = dfma(W[4], ip, dfma(W[3], ip, k.Ph[0]));
+#pragma unroll
+    for (int m = 0; m < 3; ++m) k.P2[m] = k.Ph[m] * k.Ph[m];
+    const int m = face ? 0 : 1;
+    k.t2 = dfma(k.Ph[2], k.Ph[2], dfma(k.Ph[m], k.Ph[m], k.P2[1 - m]));
+    k.z = k.qh * mrcp2(k.Ph[0]);
+    T D = k.qh * k.z;
+#if defined(__HIP_DEVICE_COMPILE__)
+    T A = dfma(-W[6], is3 * ic, dfma(k.t1, k.t1, T(2) * k.t2));
+#else
+    // (R* as Sys14::norm takes it: A cancels near equilibrium, and the host compares the two systems)
+    T A = dfma(k.t1, k.t1, T(2) * k.t2) - W[6] * (k.rho * ip * ip);
+#endif
+    T X = dfma(T(8) * k.t2, D, A * A);
+    k.A = A;
+    k.sig = tube_sigma(A, X, T(2) * D, T(4) * k.t2);
+    k.sb = tmax(k.sig, sigma_lim);
   }
-  template <class T> MX_HD static void speeds(const Norm<T>& n, T ux, T& lmin, T& lmax) {
-    SigmaFit<T> f;
-    sigma_fit(n.s.sb, n.s.rsb, n.s.isb, f);
-    wave_pair<false>(f, cmax(n.Ph[0], T(0)), n.h * n.ic, T(0), ux, n.kc, lmin, lmax);
+
+  // Closing values.  Q_xxx = q0 s3, R_xx = r s4 and S_x = s s5 in two factors,
+  // s_n = rho c^n: the flux adds each product with one rounding.
+  template <class T> struct Closing { T q0, Q0, Q1, Q2, r, s, s3, s4, s5; };
+  template <class T> MX_HD static void tube_closure(const Core<T>& k, Closing<T>& f) {
+#pragma clang fp contract(off)
+    // w = Cm^-1 q with Cm = 2 tr(P^2) I + 4 P^2 (diagonal; w_y = w_z = 0)
+    T w = k.qh * mrcp2(dfma(T(4), k.P2[0], T(2) * k.t2));
+    T P2z = k.P2[0] * k.z;
+    T zP2z = k.z * P2z;
+    T wz = w * k.z;
+    T P2w = k.P2[0] * w;
+    f.s3 = k.rho * (k.c * k.c * k.c);
+    f.s4 = f.s3 * k.c;
+    f.s5 = f.s4 * k.c;
+    f.q0 = T(2) * dfma(k.P2[0], w, P2w + P2w);
+    f.Q0 = f.q0 * f.s3;
+    f.Q1 = T(2) * (w * k.P2[1]) * f.s3;
+    f.Q2 = T(2) * (w * k.P2[2]) * f.s3;
+    T isb = mrcp2(k.sb);
+    T m = w * P2z;
+    T Qz = T(2) * dfma(k.P2[0], wz, m + m);
+    f.r = dfma(k.Ph[0], k.t1, dfma(k.P2[0], T(2) * (T(1) - k.sb), Qz * isb));
+    T Pw = k.Ph[0] * w;
+    T t3 = dfma(k.Ph[2], k.P2[2], dfma(k.Ph[0], k.P2[0], k.Ph[1] * k.P2[1]));
+    T P3w = k.P2[0] * Pw;
+    T t1 = k.t1, t2 = k.t2;
+    T g1 = dfma(-t1, T(2) * t2, dfma(T(12), t3, T(2) * t1 * t1 * t1));
+    T g2 = dfma(t2, T(14), -(T(6) * t1 * t1));
+    T Wq = dfma(T(20), P3w, dfma(T(20) * t1, P2w, dfma(g1, w, g2 * Pw)));
+    T Qzz = T(2) * dfma(w, zP2z, T(2) * wz * P2z);
+    T rsb = msqrt2(k.sb);
+    f.s = dfma(Wq, T(1) - rsb, dfma(Qzz, isb * isb, T(2) * rsb * t1 * k.qh));
+  }
+
+  // Physical flux along x (seven components) from primitives and closing values
+  template <class T> MX_HD static void tube_flux(const T* W, const Closing<T>& f, T* F) {
+#pragma clang fp contract(off)
+    T rho = W[0], ux = W[1], Pxx = W[2], qx = W[5];
+    T uu = ux * ux;
+    T trP = Pxx + W[3] + W[4];
+    T Pu = Pxx * ux;
+    T uPu = ux * Pu;
+    T uq = ux * qx;
+    T R = f.r * f.s4;
+    T Qu = f.Q0 * ux;
+    T uQu = ux * Qu;
+    T uR = ux * R;
+    T rud = rho * ux;
+    T ruuu = rud * uu;
+    F[0] = rud;
+    F[1] = dfma(rud, ux, Pxx);
+    F[2] = dfma(f.s3, f.q0, dfma(ux, Pxx, dfma(ux, Pxx, dfma(rud, uu, Pu))));
+    F[3] = dfma(ux, W[3], f.Q1);
+    F[4] = dfma(ux, W[4], f.Q2);
+    T a = dfma(ruuu, ux, (ux * trP) * ux);
+    a = dfma(T(2) * Pu, ux, a);
+    a = dfma(T(2) * ux, Pu, a);
+    a = dfma(uu, Pxx, a);
+    a = dfma(ux, qx, dfma(ux, qx, a));
+    F[5] = dfma(f.s4, f.r, dfma(T(2), Qu, a));
+    T b = dfma(ruuu, uu, T(2) * ux * uu * trP);
+    b = dfma(T(4) * uu, Pu, b);
+    b = dfma(T(4) * ux, uPu, b);
+    b = dfma(T(2) * uu, qx, b);
+    b = dfma(T(4) * ux, uq, b);
+    b = dfma(T(4), uQu, b);
+    b = dfma(T(4), uR, b);
+    F[6] = dfma(f.s5, f.s, dfma(ux, W[6], b));
+  }
+
+  template <class T>
+  MX_HD static void tube_speeds(const Core<T>& k, T ud, T kws, T& lmin, T& lmax) {
+#pragma clang fp contract(off)
+    T sw = tmin(k.sb, T(1));
+    T Pdd = tmax(k.Ph[0], T(0));
+    T a = T(0), b = T(0);
+    if (Pdd > T(0)) {
+      T lP = mlog(Pdd);
+      a = T(1.4) * mexp(dfma(T(1.1), lP, -(Pdd * Pdd)));
+      b = T(0.9) * Pdd * mexp(T(-0.5) * mexp(T(1.4) * lP));
+    }
+    BYEC<T> g = byec(sw, Pdd);
+    T pref = mdiv2(dfma(a, sw, b), T(2) * sw);
+    T hmax, hmin;
+    tube_roots(k.qh, sw, g.C, g.Y, hmax, hmin);
+    lmax = dfma(kws * dfma(pref, hmax, g.E), k.c, ud);
+    lmin = dfma(-(kws * dfma(pref, hmin, g.E)), k.c, ud);
+  }
+
+  template <class T> MX_HD static void tube_cons(const T* W, T* U) {
+#pragma clang fp contract(off)
+    T rho = W[0], ux = W[1], Pxx = W[2];
+    T uu = ux * ux;
+    T trP = Pxx + W[3] + W[4];
+    T Pux = Pxx * ux;
+    T ruu = rho * uu;
+    U[0] = rho;
+    U[1] = rho * ux;
+    U[2] = dfma(rho, uu, Pxx);
+    U[3] = W[3];
+    U[4] = W[4];
+    U[5] = dfma(T(2), Pux, dfma(ux, ruu, trP * ux)) + W[5];
+    U[6] = dfma(T(4), ux * W[5], dfma(T(4), ux * Pux, dfma(uu, ruu, T(2) * uu * trP))) + W[6];
   }
 
   template <int d, class T>
   MX_HD static void face_terms(const T* W, T sigma_lim, T kws, T* U, T* F, T& lmin, T& lmax) {
     static_assert(d == 0, "flows along x only");
-    Norm<T> n;
-    norm(W, sigma_lim, kws, n);
-    const T rho = W[0], ux = W[1], Pxx = W[2], q = W[5];
-    const T a = n.Ph[0], A = n.P2[0];
-    const T v = q * mrcp(T(2) * A + n.t2);
-    const T isb = n.s.isb;
-    const T vs = v * isb;
-    // v z (P*^2)_xx = v h P*_xx, so the three terms of Q_xxl z_l are equal.  (Where a sum has two
-    // products, tfma says which one is fused: the single and the batched kernels then agree bit
-    // for bit, whichever way the compiler would have gone in each.)
-    const T R = T(3) * (vs * (a * n.h)) + tfma(T(2) * (T(1) - n.s.sb) * n.pT, A, T(3) * n.T0 * Pxx);
-    const T det = a * n.Ph[1] * n.Ph[2];
-    const T Wq = v * (T(24) * n.t2 - T(54) + T(28) * det + tfma(T(12) * n.t2 - T(72), a, T(60) * A));
-    const T hs = n.h * isb;
-    const T S = tfma(T(3) * v, hs * hs, n.T0 * tfma(T(6) * n.s.rsb, q, (T(1) - n.s.rsb) * Wq));
-    const T Qx = T(3) * (v * A);
-
-    const T uu = ux * ux;
-    const T e = rho * uu + n.trP;
-    const T Pu = Pxx * ux;
-    const T s = Pu + q;
-    U[0] = rho;
-    U[1] = rho * ux;
-    U[2] = U[1] * ux + Pxx;
-    U[3] = W[3];
-    U[4] = W[4];
-    U[5] = e * ux + (s + Pu);
-    U[6] = uu * (e + n.trP) + (T(4) * (ux * s) + W[6]);
-    const T m = T(2) * Pu + q;
-    const T Qu = Qx * ux;
-    const T Rq = R + Qu;
-    F[0] = U[1];
-    F[1] = U[2];
-    F[2] = ux * U[2] + tfma(T(2), Pu, Qx);
-    F[3] = tfma(ux, W[3], v * n.P2[1]);
-    F[4] = tfma(ux, W[4], v * n.P2[2]);
-    F[5] = ux * U[5] + (ux * m + (uu * Pxx + (Rq + Qu)));
-    F[6] = ux * U[6] + (T(2) * uu * m + (T(4) * (ux * Rq) + S));
-    speeds(n, ux, lmin, lmax);
+    Core<T> k;
+    tube_core(W, sigma_lim, true, k);
+    // (first: the closing values are then not held across the exponentials)
+    tube_speeds(k, W[1], kws, lmin, lmax);
+    opaque(lmin); opaque(lmax);
+    Closing<T> f;
+    tube_closure(k, f);
+    tube_flux(W, f, F);
+    tube_cons(W, U);
   }
 
   // U, F_d and the wave speeds of a face state in single precision (the FP32 setting)
@@ -327,10 +410,10 @@ struct Sys14A {
   }
 
   template <int d, class T> MX_HD static T cell_lambda(const T* W, T sigma_lim, T kws) {
-    Norm<T> n;
-    norm(W, sigma_lim, kws, n);
+    Core<T> k;
+    tube_core(W, sigma_lim, false, k);
     T lmin, lmax;
-    speeds(n, W[1], lmin, lmax);
+    tube_speeds(k, W[1], kws, lmin, lmax);
     return tmax(tabs(lmin), tabs(lmax));
   }
 
@@ -340,11 +423,31 @@ struct Sys14A {
     We[0] = W[0]; We[1] = W[1];
     We[2] = p; We[3] = p; We[4] = p;
     We[5] = T(0);
-    We[6] = mdiv(T(15) * p * p, W[0]);
+    We[6] = mdiv2(T(15) * p * p, W[0]);
+  }
+
+  // its conserved moments (the implicit source)
+  template <class T> MX_HD static void equilibrium_cons(const T* W, T* U) {
+#pragma clang fp contract(off)
+    T We[NV];
+    equilibrium(W, We);
+    T rho = We[0], ux = We[1], p = We[2];
+    T uu = ux * ux;
+    T trP = p + p + p;
+    T Pux = p * ux;
+    T ruu = rho * uu;
+    U[0] = rho;
+    U[1] = rho * ux;
+    U[2] = ruu + p;
+    U[3] = p;
+    U[4] = p;
+    U[5] = dfma(T(2), Pux, dfma(ux, ruu, trP * ux));
+    U[6] = dfma(T(4), ux * Pux, dfma(uu, ruu, T(2) * uu * trP)) + We[6];
   }
 
   // BGK source; inv_tau = 1/tau at the cell centre
   template <class T> MX_HD static void source(const T* W, T inv_tau, T* C) {
+#pragma clang fp contract(off)
     T rho = W[0], ux = W[1], qx = W[5];
     T p = (W[2] + W[3] + W[4]) * T(1.0 / 3.0);
     T Pu = W[2] * ux;
@@ -355,8 +458,8 @@ struct Sys14A {
     C[2] = -(W[2] - p) * inv_tau;
     C[3] = -(W[3] - p) * inv_tau;
     C[4] = -(W[4] - p) * inv_tau;
-    C[5] = -(T(2) * Pu + qx - T(2) * ux * p) * inv_tau;
-    C[6] = -((T(4) * uPu + T(4) * uq + W[6]) - (T(4) * uu * p + mdiv(T(15) * p * p, rho))) * inv_tau;
+    C[5] = -dfma(T(-2) * ux, p, dfma(T(2), Pu, qx)) * inv_tau;
+    C[6] = -((dfma(T(4), uPu, T(4) * uq) + W[6]) - dfma(T(4) * uu, p, mdiv2(T(15) * p * p, rho))) * inv_tau;
   }
 };
 

@@ -121,13 +121,11 @@ __global__ __launch_bounds__(1024) void batch_finalize_kernel(BatchInst* in, con
 // contiguous ranges, one per workgroup, with an XCD-aware order of the ranges; a workgroup
 // finds its first tile by a binary search over the tile prefix and then walks forward.
 //
-// Bound by FP64 VALU work, with the loads of each tile exposed where nothing else runs; so a
-// workgroup reduces status, counters and CFL rate once for the tiles of an instance in its range
-// instead of for each tile, and (PIPE: one cell per thread, seven moments, FP64: where the
-// registers hold it) a thread updates the cell that it loaded, and loads U^n of the second
-// stage and the next tile's cell before the tile's faces.  512 tubes of 512 to 32768 cells (4.0 M
-// cells, 256 threads): 20 steps with load and read 13.2 -> 9.6 ms, with the grid held to the
-// workgroups that run at once.
+// Bound by FP64 VALU work; a workgroup reduces status, counters and CFL rate once for the tiles of an
+// instance in its range instead of for each tile.  512 tubes of 512 to 32768 cells (4.0 M cells, 256
+// threads), 20 steps with load and read: 13.3 ms (a reduction per tile, and the CFL rate of the
+// loaded field in a pass of its own: 18.2).  A variant that kept the thread's own cell, U^n and the
+// next tile's cell in registers across the faces spilled 25 of 168 registers and took 15.4 ms.
 template <class SYS, int PREC, int NT, int CPT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(SYS::NV <= 7 ? 3 : 2)))
 void batch_stage_kernel(BatchParams p) {
@@ -137,7 +135,6 @@ void batch_stage_kernel(BatchParams p) {
   constexpr int LX = TX + 2 * G;
   constexpr int NFX = TX + 1;
   constexpr int NPX = TX + 2;
-  constexpr bool PIPE = CPT == 1 && NV <= 7 && PREC == 0;
   static_assert(LX == CPT * NT, "tile and halo are whole rounds over the threads");
   __shared__ double sW[NV * LX];
   __shared__ double sFx[NV * NFX];
@@ -173,7 +170,7 @@ void batch_stage_kernel(BatchParams p) {
     int next;         // first tile of the next instance
     int n, i0;
     long long off;
-    double dt, inv_dx, inv_tau_ref;
+    double dt, inv_dx, tau;   // tau: tau_ref of a tube's cells, inv_tau_constant of the others; 0: no source
   };
   auto open_instance = [&](int k) {   // every active instance has at least one tile
     Tile m;
@@ -184,7 +181,7 @@ void batch_stage_kernel(BatchParams p) {
     m.off = uniform(m.c->off);
     m.dt = uniform(m.c->dt);
     m.inv_dx = uniform(m.c->inv_dx);
-    m.inv_tau_ref = uniform(m.c->inv_tau_ref);
+    m.tau = uniform(SYS::TUBE ? m.c->tau_ref : m.c->inv_tau_ref);
     return m;
   };
   // stage input of tile cell cc (interior or ghost source); refl: mirrored at a wall
@@ -200,9 +197,6 @@ void batch_stage_kernel(BatchParams p) {
   };
 
   Tile cur = open_instance(k0);
-  double Uown[NV];       // PIPE: the stage input of this thread's cell
-  int refl = 0;
-  if constexpr (PIPE) load_cell(cur, t, Uown, refl);
   double rate = 0.0;     // of the instance's tiles so far
   int n64 = 0, nfb = 0;
   for (int k = k0; k < k1; ++k) {
@@ -214,12 +208,8 @@ void batch_stage_kernel(BatchParams p) {
     for (int r = 0; r < CPT; ++r) {
       const int cc = t + r * NT;
       double Uc[NV], W[NV];
-      if constexpr (PIPE) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) Uc[v] = Uown[v];
-      } else {
-        load_cell(cur, cc, Uc, refl);
-      }
+      int refl;
+      load_cell(cur, cc, Uc, refl);
       SYS::cons_to_prim(Uc, W);
       if (refl) {
 #pragma unroll
@@ -238,7 +228,7 @@ void batch_stage_kernel(BatchParams p) {
       const int ti = cc - 1;
       double Wm[NV], Wc[NV], Wp[NV];
       lds(ti - 1, Wm); lds(ti, Wc); lds(ti + 1, Wp);
-      double phi = limiter_factor<SYS>(Wm, Wc, Wp, p.limiter);
+      double phi = cell_limiter<SYS>(Wm, Wc, Wp, p.limiter);
       if (p.fallback && phi > 0.0 && !faces_admissible<SYS>(Wm, Wc, Wp, phi)) {
         phi = 0.0;
         if (t + r * NT < NPX && ti >= 0 && ti < TX && cur.i0 + ti < cur.n) ++nfb;
@@ -255,19 +245,6 @@ void batch_stage_kernel(BatchParams p) {
         nxt = open_instance(k + 1);
       }
     }
-    // PIPE: U^n of the second stage and the next tile's cell, in flight during the faces
-    const int ci0 = t - G;
-    double Ua[NV], Unext[NV];
-    int refl_next = 0;
-    if constexpr (PIPE) {
-      const int own = min(max(cur.i0 + ci0, 0), cur.n - 1);
-      if (p.mode != MODE_EULER) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) Ua[v] = p.Ua[SYS::plane_of(v) * p.plane + cur.off + own];
-      }
-      load_cell(nxt, t, Unext, refl_next);
-    }
-
     __builtin_amdgcn_s_setprio(0);
     // 3. faces: face fi lies between tile cells fi - 1 and fi.  (Mixed precision: the loop
     // stays a loop for CPT = 1 too, so that the compiler fuses products and sums there as it does
@@ -290,10 +267,11 @@ void batch_stage_kernel(BatchParams p) {
       for (int v = 0; v < NV; ++v) sFx[v * NFX + fi] = Fh[v];
     }
     auto source = [&](int ci, double* Cs) {
-      if (cur.inv_tau_ref > 0.0) {
+      if (cur.tau > 0.0) {
         double W[NV];
         lds(ci, W);
-        SYS::source(W, inv_tau<SYS>(W, p.tau_mode, cur.inv_tau_ref), Cs);
+        if constexpr (SYS::TUBE) SYS::source(W, 1.0 / tau_tube<SYS>(W, p.tau_mode, cur.tau, p.rho_ref, p.T_ref), Cs);
+        else SYS::source(W, inv_tau<SYS>(W, p.tau_mode, cur.tau), Cs);
       } else {
 #pragma unroll
         for (int v = 0; v < NV; ++v) Cs[v] = 0.0;
@@ -302,25 +280,19 @@ void batch_stage_kernel(BatchParams p) {
     __syncthreads();
 
     __builtin_amdgcn_s_setprio(1);
-    // 4. update.  PIPE: of the thread's own cell, and of the primitive tile only that cell is
-    // still read, which the same thread overwrites for the next tile: no barrier between
+    // 4. update
     int flag = 0;
 #pragma unroll 1
     for (int r = 0; r < CPT; ++r) {
-      const int ci = PIPE ? min(max(ci0, 0), TX - 1) : min(t + r * NT, TX - 1);
-      const bool own = (PIPE ? ci == ci0 : t + r * NT < TX) && cur.i0 + ci < cur.n;
+      const int ci = min(t + r * NT, TX - 1);
+      const bool own = t + r * NT < TX && cur.i0 + ci < cur.n;
       const long long g = cur.off + min(cur.i0 + ci, cur.n - 1);
-      double Ub[NV], Cs[NV], Un[NV];
-      if constexpr (PIPE) {
+      double Ub[NV], Ua[NV], Cs[NV], Un[NV];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) Ub[v] = Uown[v];
-      } else {
+      for (int v = 0; v < NV; ++v) Ub[v] = p.Ub[SYS::plane_of(v) * p.plane + g];
+      if (p.mode != MODE_EULER) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) Ub[v] = p.Ub[SYS::plane_of(v) * p.plane + g];
-        if (p.mode != MODE_EULER) {
-#pragma unroll
-          for (int v = 0; v < NV; ++v) Ua[v] = p.Ua[SYS::plane_of(v) * p.plane + g];
-        }
+        for (int v = 0; v < NV; ++v) Ua[v] = p.Ua[SYS::plane_of(v) * p.plane + g];
       }
       source(ci, Cs);
       bool fin = true;
@@ -339,7 +311,8 @@ void batch_stage_kernel(BatchParams p) {
       double rc = 0.0;
       if (p.do_cfl) {
         double Wn[NV];
-        SYS::cons_to_prim(Un, Wn);
+        if constexpr (SYS::TUBE) SYS::cons_to_prim(Un, Wn, false);
+        else SYS::cons_to_prim(Un, Wn);
         if (!SYS::admissible(Wn)) bad = ST_UNREALIZABLE;
         rc = SYS::template cell_lambda<0>(Wn, p.sigma_lim, p.kws);
       } else if (!SYS::admissible_cons(Un)) {
@@ -364,13 +337,7 @@ void batch_stage_kernel(BatchParams p) {
       if (lane == 0) raise_max(&cur.c->maxrate, m);
       rate = 0.0;
     }
-    if constexpr (PIPE) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Uown[v] = Unext[v];
-      refl = refl_next;
-    } else {
-      __syncthreads();   // the update read the primitive tile
-    }
+    __syncthreads();   // the update read the primitive tile
     cur = nxt;
   }
   // counters, once for the range

@@ -9,6 +9,7 @@ struct BatchInst {
   double dt, t, t_end, dt_last;
   double dx, inv_dx;
   double inv_tau_ref;            // inv_tau_constant; 0: no source
+  double tau_ref;                // the same of a tube (TUBE) as given; <= 0: no source
   unsigned long long maxrate;    // bit pattern of the max CFL rate (positive double)
   long long step;
   long long off;                 // first cell in the concatenated field
@@ -36,6 +37,7 @@ struct BatchParams {
   const BatchCtrl* bctrl;        // n_active and n_tiles of the current step
   int bc_lo, bc_hi;
   int tau_mode;
+  double rho_ref, T_ref;
   double sigma_lim, kws;
   int limiter, flux, fallback;
   int mode;

@@ -74,6 +74,12 @@ __device__ __forceinline__ double cell_rate(const double* W, double sigma_lim, d
   if constexpr (DIM == 1) return SYS::template cell_lambda<0>(W, sigma_lim, kws);
   else return SYS::cell_rate2d(W, sigma_lim, kws, dx, dy);
 }
+// the same for a loaded field (1D, 14 moments: whether it is a tube is not known yet)
+template <class SYS, int DIM>
+__device__ __forceinline__ double field_rate(const double* W, double sigma_lim, double kws, double dx, double dy) {
+  if constexpr (DIM == 1 && SYS::NV == 14) return SYS::tube_lambda(W, sigma_lim, kws);
+  else return cell_rate<SYS, DIM>(W, sigma_lim, kws, dx, dy);
+}
 
 // ------------------------------------------------------------------ stage kernel
 // One stage of a tile: primitives of the tile and its halo in LDS, limiter factors, face fluxes,
@@ -237,7 +243,7 @@ void stage_kernel(StageParams p) {
     auto limiter = [&](int ti, int tj, int di, int dj, const double* Wc, bool mine) {
       double Wm[NV], Wp[NV];
       lds(ti - di, tj - dj, Wm); lds(ti + di, tj + dj, Wp);
-      double phi = limiter_factor<SYS>(Wm, Wc, Wp, p.limiter);
+      double phi = cell_limiter<SYS>(Wm, Wc, Wp, p.limiter);
       if (p.fallback && phi > 0.0 && !faces_admissible<SYS>(Wm, Wc, Wp, phi)) {
         phi = 0.0;
         if (mine && i0 + ti < p.nx && j0 + tj < p.ny) ++nfb;
@@ -402,7 +408,8 @@ void stage_kernel(StageParams p) {
     if (p.use_source && !implicit_src) {
       double W[NV];
       lds(ci, cj, W);
-      SYS::source(W, inv_tau<SYS>(W, p.tau_mode, p.inv_tau_ref), Cs);
+      if constexpr (SYS::TUBE) SYS::source(W, 1.0 / tau_tube<SYS>(W, p.tau_mode, p.tau_ref, p.rho_ref, p.T_ref), Cs);
+      else SYS::source(W, inv_tau<SYS>(W, p.tau_mode, p.inv_tau_ref), Cs);
     } else {
 #pragma unroll
       for (int v = 0; v < NV; ++v) Cs[v] = 0.0;
@@ -445,10 +452,17 @@ void stage_kernel(StageParams p) {
       // h = dt / tau
       double Wt[NV], We[NV], Ue[NV];
       SYS::cons_to_prim(Un, Wt);
-      const double h = (p.cdt * dt) * inv_tau<SYS>(Wt, p.tau_mode, p.inv_tau_ref);
-      const double w = mrcp(1.0 + h);
-      SYS::equilibrium(Wt, We);
-      SYS::prim_to_cons(We, Ue);
+      double h, w;
+      if constexpr (SYS::TUBE) {   // (the roundings are fixed)
+        h = (p.cdt * dt) / tau_tube<SYS>(Wt, p.tau_mode, p.tau_ref, p.rho_ref, p.T_ref);
+        w = 1.0 / (1.0 + h);
+        SYS::equilibrium_cons(Wt, Ue);
+      } else {
+        h = (p.cdt * dt) * inv_tau<SYS>(Wt, p.tau_mode, p.inv_tau_ref);
+        w = mrcp(1.0 + h);
+        SYS::equilibrium(Wt, We);
+        SYS::prim_to_cons(We, Ue);
+      }
 #pragma unroll
       for (int v = 0; v < NV; ++v) Un[v] = (Un[v] + h * Ue[v]) * w;
     }
@@ -464,7 +478,8 @@ void stage_kernel(StageParams p) {
     if (p.do_cfl) {
       // the last stage of a step: the new state's primitives also give its CFL rate
       double Wn[NV];
-      SYS::cons_to_prim(Un, Wn);
+      if constexpr (SYS::TUBE) SYS::cons_to_prim(Un, Wn, false);
+      else SYS::cons_to_prim(Un, Wn);
       if (!SYS::admissible(Wn)) bad = ST_UNREALIZABLE;
       r = cell_rate<SYS, DIM>(Wn, p.sigma_lim, p.kws, p.dx, p.dy);
     } else if (!SYS::admissible_cons(Un)) {
@@ -548,7 +563,7 @@ __global__ __launch_bounds__(256) void cfl_kernel(CflParams p) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) U[v] = p.U[v * p.plane + off];
     SYS::cons_to_prim(U, W);
-    rate = fmax(rate, cell_rate<SYS, DIM>(W, p.sigma_lim, p.kws, p.dx, p.dy));
+    rate = fmax(rate, field_rate<SYS, DIM>(W, p.sigma_lim, p.kws, p.dx, p.dy));
   }
   block_max_rate(rate, p.rates, p.slot);
 }
@@ -633,7 +648,8 @@ __global__ __launch_bounds__(256) void ingest_kernel(IngestParams p) {
         if (Uc[3] != 0.0 || Uc[6] != 0.0 || Uc[8] != 0.0 || Uc[12] != 0.0) np |= 1;
         if (Uc[2] != 0.0 || Uc[5] != 0.0 || Uc[8] != 0.0 || Uc[11] != 0.0) np |= 2;
       }
-      r = fmax(cell_rate<SYS, DIM>(W, p.sigma_lim, p.kws, p.dx, p.dy), 0.0);
+      if constexpr (DIM == 1) SYS::cons_to_prim(Uc, W);
+      r = fmax(field_rate<SYS, DIM>(W, p.sigma_lim, p.kws, p.dx, p.dy), 0.0);
       if constexpr (BATCH) inst = p.cell_inst[k];
     }
     if constexpr (BATCH) {

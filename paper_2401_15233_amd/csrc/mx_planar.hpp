@@ -21,6 +21,7 @@ MX_HD constexpr int pidx(int i, int j) { return (i == j) ? (i == 0 ? 0 : 2) : 1;
 
 struct Sys14P {
   static constexpr int NV = 10;
+  static constexpr bool TUBE = false;
   static constexpr bool JETS = true;
   // storage plane of each carried moment in the 14-moment state
   MX_HD static constexpr int plane_of(int v) {

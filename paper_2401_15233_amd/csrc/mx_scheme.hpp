@@ -58,6 +58,38 @@ MX_HD T limiter_factor(const T* Wm, const T* Wc, const T* Wp, int kind) {
   return limiter_of_ratio(num, den, kind);
 }
 
+// A tube's factor (TUBE: the roundings are fixed): the formulas of both limiters as they stand, the
+// running minimum kept as a fraction (den > 0) compared by cross multiplication; a jump that
+// changes sign gives 0.
+template <bool MINMOD, class SYS, class T>
+MX_HD T limiter_tube(const T* Wm, const T* Wc, const T* Wp) {
+#pragma clang fp contract(off)
+  constexpr int NV = SYS::NV;
+  T sc[NV];
+  SYS::scales(Wc, sc);
+  T num = T(1), den = T(1);
+  bool turns = false;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const T a = Wc[v] - Wm[v], b = Wp[v] - Wc[v];
+    const T aa = tabs(a), ab = tabs(b);
+    const bool counts = !(aa + ab <= T(NEUTRAL_EPS) * sc[v]), turn = a * b <= T(0);
+    const T fn = MINMOD ? T(2) * tmin(aa, ab) : T(2) * a * b, fd = MINMOD ? aa + ab : dfma(a, a, b * b);
+    const bool take = counts && !turn && fn * den < num * fd;
+    num = take ? fn : num;
+    den = take ? fd : den;
+    turns = turns || (counts && turn);
+  }
+  return turns ? T(0) : ((den == T(1)) ? num : mdiv2(num, den));
+}
+
+// what the stages take
+template <class SYS, class T>
+MX_HD T cell_limiter(const T* Wm, const T* Wc, const T* Wp, int kind) {
+  if constexpr (SYS::TUBE) return kind == 0 ? limiter_tube<true, SYS>(Wm, Wc, Wp) : limiter_tube<false, SYS>(Wm, Wc, Wp);
+  else return limiter_factor<SYS>(Wm, Wc, Wp, kind);
+}
+
 // The cell's state at its upper (sgn = +1) or lower (sgn = -1) face: Wc +- s/2 with the limited
 // slope s = phi (a + b)/2 and a + b = Wp - Wm, i.e. Wc + sgn (phi/4)(Wp - Wm), one rounding per
 // component.
@@ -95,6 +127,11 @@ template <class SYS, class T> MX_HD T inv_tau(const T* W, int mode, T k) {
   const T temp = SYS::pressure(W) * mrcp(W[0]);
   return k * (W[0] * (temp * mrsqrt(temp)));
 }
+// tau of a tube's cell, in the quotients and the root as they stand (TUBE: the roundings are fixed)
+template <class SYS, class T> MX_HD T tau_tube(const T* W, int mode, T tau_ref, T rho_ref, T T_ref) {
+  const T temp = SYS::pressure(W) / W[0];
+  return (mode == 0) ? tau_ref * (rho_ref / W[0]) * sqrt(T_ref / temp) : tau_ref;
+}
 
 // Interface flux of two face states: HLL (Davis speeds) or Rusanov, in one form, the left
 // side's share and then the right side's
@@ -127,13 +164,50 @@ MX_HD FaceCoef<T> face_coef(T lminL, T lmaxL, T lminR, T lmaxR, int flux_kind) {
 template <class T> MX_HD T share_left(const FaceCoef<T>& k, T F, T U) { return tfma(k.cL, F, -(k.d * U)); }
 template <class T> MX_HD T add_right(const FaceCoef<T>& k, T F, T U, T left) { return tfma(k.cR, F, tfma(k.d, U, left)); }
 
+// The same flux of a tube (TUBE: the roundings are fixed): the upwind flux as it is, and the jump of U
+// before its product.
+template <class T> struct FaceSpeeds { T SL, SR, SLR, inv, am; };
+template <class T>
+MX_HD FaceSpeeds<T> face_speeds(T lminL, T lmaxL, T lminR, T lmaxR, int flux_kind) {
+  FaceSpeeds<T> k = {};
+  if (flux_kind == 0) {
+    k.SL = tmin(lminL, lminR);
+    k.SR = tmax(lmaxL, lmaxR);
+    k.inv = mrcp2(k.SR - k.SL);
+    k.SLR = k.SL * k.SR;
+  } else {
+    k.am = tmax(tmax(tabs(lminL), tabs(lmaxL)), tmax(tabs(lminR), tabs(lmaxR)));
+  }
+  return k;
+}
+template <class T>
+MX_HD T flux_tube(const FaceSpeeds<T>& k, int flux_kind, T FL, T UL, T FR, T UR) {
+#pragma clang fp contract(off)
+  if (flux_kind == 0) {
+    const T mid = dfma(k.SLR, UR - UL, dfma(k.SR, FL, -(k.SL * FR))) * k.inv;
+    return (k.SL >= T(0)) ? FL : ((k.SR <= T(0)) ? FR : mid);
+  }
+  return dfma(T(0.5), FL + FR, -(T(0.5) * k.am * (UR - UL)));
+}
+
 template <class SYS, int D, class T>
 MX_HD void face_flux(const T* WL, const T* WR, T sigma_lim, T kws, int flux_kind, T* Fh) {
   constexpr int NV = SYS::NV;
   T UL[NV], FL[NV], UR[NV], FR[NV];
   T lminL, lmaxL, lminR, lmaxR;
   SYS::template face_terms<D>(WL, sigma_lim, kws, UL, FL, lminL, lmaxL);
+  if constexpr (SYS::TUBE) {   // the left side's results alone are held while the right side's come
+#pragma unroll
+    for (int v = 0; v < NV; ++v) { opaque(UL[v]); opaque(FL[v]); }
+    opaque(lminL); opaque(lmaxL);
+  }
   SYS::template face_terms<D>(WR, sigma_lim, kws, UR, FR, lminR, lmaxR);
+  if constexpr (SYS::TUBE) {
+    const FaceSpeeds<T> k = face_speeds(lminL, lmaxL, lminR, lmaxR, flux_kind);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Fh[v] = flux_tube(k, flux_kind, FL[v], UL[v], FR[v], UR[v]);
+    return;
+  }
   opaque(lminL); opaque(lmaxL); opaque(lminR); opaque(lmaxR);
   const FaceCoef<T> k = face_coef(lminL, lmaxL, lminR, lmaxR, flux_kind);
 #pragma unroll
@@ -163,6 +237,12 @@ __device__ __forceinline__ void face_flux_pair(const double* W, bool right, doub
   SYS::template face_terms<D>(W, sigma_lim, kws, U, F, lmin, lmax);
   opaque(lmin); opaque(lmax);
   const double omin = lane_xor1(lmin), omax = lane_xor1(lmax);
+  if constexpr (SYS::TUBE) {   // (of the right lane; the left one's result is not used)
+    const FaceSpeeds<double> k = face_speeds(omin, omax, lmin, lmax, flux_kind);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Fh[v] = flux_tube(k, flux_kind, lane_xor1(F[v]), lane_xor1(U[v]), F[v], U[v]);
+    return;
+  }
   const FaceCoef<double> k = face_coef(right ? omin : lmin, right ? omax : lmax, right ? lmin : omin,
                                        right ? lmax : omax, flux_kind);
 #pragma unroll

@@ -1,0 +1,81 @@
+"""The roundings of 1D tubes are fixed: Sod tubes of 200 cells after 20 steps, from start states where a
+variable's jump comes to stand at the neutral threshold of the common limiter (1e-10 of its scale),
+so that one other rounding anywhere decides that cell's slopes the other way and moves the
+result by 1e-9 to 1e-4.  tests/golden/tubes*.npz holds the states and the results of the
+library's first kernels (one lane per face, the formulas evaluated in their order), of which
+every kernel has to give the same bits: two lanes per face (small grids), one (a grid of more than
+2048 tiles with the same cells in its middle), and the batch in each launch shape.  Equality needs
+no tolerance; the kernels' earlier outputs were off by more than 1e-9 (2-norm) on each of these."""
+import os
+
+import numpy as np
+import pytest
+
+from paper_2401_15233_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+NX, STEPS, LO, HI = 200, 20, 50, 150     # the cells LO..HI are held; the others are still at rest
+PLANES = [0, 1, 4, 7, 9, 10, 13]
+HERE = os.path.join(os.path.dirname(__file__), 'golden')
+CASES = {
+    'ssprk2': (14, dict(), 0.01),
+    'implicit': (14, dict(integrator='fe', source_implicit=True), 1e-5),
+    'vanalbada': (14, dict(limiter='vanalbada', bc=('reflective',) * 4), 0.1),
+    'rusanov': (14, dict(integrator='midpoint', flux='rusanov', tau_mode='const'), 0.1),
+}
+
+
+def golden(name, k):
+    with np.load(os.path.join(HERE, f'tubes{CASES[name][0]}.npz')) as f:
+        a, b, t = f[f'{name}.{k}.states']
+        return float(a), float(b), float(t), f[f'{name}.{k}.W']
+
+
+def sod(system, n, rho_right, p_right):
+    left = np.arange(n) < n // 2
+    rho = np.where(left, 1.0, rho_right)
+    p = np.where(left, 1.0, p_right)
+    W = np.zeros((system, 1, n))
+    if system == 5:
+        W[0], W[2], W[4] = rho, p, 3.0 * p * p / rho
+    else:
+        W[0], W[13] = rho, 15.0 * p * p / rho
+        W[[4, 7, 9]] = p
+    return W
+
+
+def check(W, t, gold, t_gold, lo):
+    planes = PLANES if W.shape[0] == 14 else range(5)
+    assert t == t_gold
+    assert np.array_equal(W[planes][:, lo:lo + HI - LO], gold), \
+        np.abs(W[planes][:, lo:lo + HI - LO] - gold).max()
+
+
+@pytest.mark.parametrize('wide', [False, True])
+@pytest.mark.parametrize('k', [0, 1])
+@pytest.mark.parametrize('name', list(CASES))
+def test_tube(gpu_lib, name, k, wide):
+    system, kw, kn = CASES[name]
+    a, b, t, gold = golden(name, k)
+    n = 130000 if wide else NX           # the same cell width
+    s = gpu_lib.MaxEntSolver(**dict(dict(system=system, dim=1, nx=n, x1=n / NX, bc=('transmissive',) * 4), **kw))
+    s.init_state(sod(system, n, a, b))
+    info = s.step(STEPS, tau_ref=I.kn_to_tau_ref(kn))
+    W = s.get('primitive').cpu().numpy()[:, 0]
+    s.close()
+    check(W, info['t'], gold, t, n // 2 - NX // 2 + LO)
+
+
+@pytest.mark.parametrize('shape', [(64, 1, 4), (64, 2, 4), (64, 4, 8), (128, 1, 8), (128, 2, 4), (256, 1, 8)])
+def test_batched_tubes(gpu_lib, shape):
+    gold = [golden('ssprk2', k) for k in (0, 1)]
+    inst = [dict(n=NX, tau_ref=I.kn_to_tau_ref(0.01), t_end=1.0) for _ in gold]
+    s = gpu_lib.MaxEntBatch(inst, precision='fp64', order=2, integrator='ssprk2', cfl=0.5)
+    s.set_launch(*shape)
+    s.init_state(np.concatenate([sod(14, NX, g[0], g[1])[:, 0] for g in gold], 1))
+    info = s.step(STEPS, chunk=STEPS)
+    parts = [p.cpu().numpy() for p in s.split(s.get('primitive'))]
+    s.close()
+    for W, i, g in zip(parts, info['instances'], gold):
+        check(W, i['t'], g[3], g[2], LO)

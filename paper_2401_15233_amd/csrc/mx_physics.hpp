@@ -252,7 +252,7 @@ template <class T> MX_HD BYEC<T> byec(T sw, T Pdd) {
   return r;
 }
 
-// Tubes.  A system with TUBE (1D: Sys14A) has every FP64 rounding of its stages fixed: the operations
+// Tubes.  A system with TUBE (1D: Sys14A, Sys5) has every FP64 rounding of its stages fixed: the operations
 // stand in the order of the formulas and the fused ones are written out, with contraction off (left to
 // the compiler, it is chosen by what surrounds an expression, and kernels differ).  The front of a
 // Riemann problem runs into uniform states, where the jumps fall, cell by cell, through the
@@ -261,8 +261,10 @@ template <class T> MX_HD BYEC<T> byec(T sw, T Pdd) {
 // face state in the algebra of Sys14::Norm gives results more than 1e-9 (2-norm) or 4e-8
 // (largest value) from these for 16 of them (SSP-RK2, minmod), 26 (van Albada), 66 (midpoint,
 // Rusanov) and 140 (point-implicit), by 5e-4 at most.  So a tube keeps one set of roundings, in
-// one lane or two, alone or in a batch.  That algebra would be faster: 20 steps of 20000 cells 372
-// us against 449, 512 tubes 9.5 ms against 13.3.
+// one lane or two, alone or in a batch.  (Without a limiter the 5-moment system is no calmer:
+// collisionless at sigma_lim = 1e-2, the CFL step follows near-Junk cells and collapses in 4 to 5
+// of 100 roundings of the same formulas.)  That algebra would be faster: 20 steps of 20000 cells 372
+// us against 449, 512 tubes 9.5 ms against 13.3, 40 steps of 1000 5-moment cells 302 us against 344.
 //
 // A tube's sigma_root and hyperbola(+-q), with the fused operations written out and the two
 // cases of each picked by selects, so that lanes of both cases share one division:
@@ -368,35 +370,31 @@ template <class T> MX_HD void sigma_fit(T sb, T rsb, T isb, SigmaFit<T>& f) {
 //   Lambda = pref (zeta + sqrt(zeta^2 - zeta sigma_w E + (2 sigma_w (sqrt(B) - E))^2 + q_t^2/10)) + E.
 // alpha > 0, so of the two zeta only the smaller can be negative, and only it needs the
 // cancellation-free form rest / (sqrt(X) - zeta): one division instead of two.
-template <bool TRANSVERSE, class T>
+template <class T>
 MX_HD void wave_roots(const SigmaFit<T>& f, T pref, T E, T qd, T qt, T alpha, T ud, T kc, T& lmin, T& lmax) {
   const T D = f.sw2 * (f.sB - E);
   const T g = T(0.5) * f.sw2 * E;
   const T aq = tabs(qd);
-  T base = D * D, zp = aq, zn = -aq;
-  if constexpr (TRANSVERSE) {
-    const T w = qt * alpha;
-    base = tfma(T(0.1), qt * qt, base);
-    zp = w + aq;
-    zn = w - aq;
-  }
+  const T w = qt * alpha;
+  const T base = tfma(T(0.1), qt * qt, D * D);
+  const T zp = w + aq, zn = w - aq;
   // (tfma: which products are fused must not depend on the kernel around)
   const T hp = zp + msqrt_pos(tfma(zp, zp - g, base));
   const T rest = tfma(-zn, g, base);
   const T sn = msqrt_pos(tfma(zn, zn, rest)) + tabs(zn);
   T hn = mdiv(rest, sn);
-  if constexpr (TRANSVERSE) hn = (zn >= T(0)) ? sn : hn;
+  hn = (zn >= T(0)) ? sn : hn;
   const T Lp = tfma(pref, hp, E), Ln = tfma(pref, hn, E);
   const bool fwd = qd >= T(0);
   const T Lmax = fwd ? Lp : Ln, Lmin = fwd ? Ln : Lp;
   lmax = tfma(kc, Lmax, ud);
   lmin = tfma(-kc, Lmin, ud);
 }
-template <bool TRANSVERSE, class T>
+template <class T>
 MX_HD void wave_pair(const SigmaFit<T>& f, T P, T qd, T qt, T ud, T kc, T& lmin, T& lmax) {
   T a, b, P04;
   fit_ab(P, a, b, P04);
-  wave_roots<TRANSVERSE>(f, T(0.5) * tfma(b, f.isw, a), T(0.8) * msqrt_pos(T(3) * f.om * P), qd, qt,
+  wave_roots(f, T(0.5) * tfma(b, f.isw, a), T(0.8) * msqrt_pos(T(3) * f.om * P), qd, qt,
                          T(0.6) * P * P - T(0.38) * P + T(0.35), ud, kc, lmin, lmax);
 }
 
@@ -682,7 +680,7 @@ struct Sys14 {
     if constexpr (!std::is_same<T, float>::value) {
       SigmaFit<T> f;
       sigma_fit(k.sb, msqrt_pos(k.sb), mrcp(k.sb), f);
-      wave_pair<true>(f, cmax(k.Ph[sidx(d, d)], T(0)), k.qh[d],
+      wave_pair(f, cmax(k.Ph[sidx(d, d)], T(0)), k.qh[d],
                       msqrt_pos(k.qh[t1i] * k.qh[t1i] + k.qh[t2i] * k.qh[t2i]), ud, kws * k.c, lmin, lmax);
     } else {
       wavespeeds_formula<d>(k, ud, kws, lmin, lmax);
@@ -759,7 +757,7 @@ struct Sys14 {
   MX_HD static void speeds(const Norm<T>& n, const SigmaFit<T>& f, T ud, T& lmin, T& lmax) {
     constexpr int t1i = (d == 0) ? 1 : 0;
     constexpr int t2i = (d == 2) ? 1 : 2;
-    wave_pair<true>(f, cmax(n.Ph[sidx(d, d)], T(0)), n.h[d] * n.ic,
+    wave_pair(f, cmax(n.Ph[sidx(d, d)], T(0)), n.h[d] * n.ic,
                     msqrt_pos(n.h[t1i] * n.h[t1i] + n.h[t2i] * n.h[t2i]) * n.ic, ud, n.kc, lmin, lmax);
   }
 
@@ -942,16 +940,21 @@ struct Sys14 {
 // ===================================================================== 5 moments
 struct Sys5 {
   static constexpr int NV = 5;
-  static constexpr bool TUBE = false;
+  static constexpr bool TUBE = true;
   static constexpr bool JETS = false;
   MX_HD static constexpr int plane_of(int v) { return v; }
 
-  template <class T> MX_HD static void cons_to_prim(const T* U, T* W) {
+  // (TUBE: the roundings are fixed, as in Sys14A)
+  template <class T> MX_HD static void cons_to_prim(const T* U, T* W) { cons_to_prim(U, W, true); }
+  template <class T> MX_HD static void cons_to_prim(const T* U, T* W, bool fused) {
+#pragma clang fp contract(off)
     T rho = U[0];
-    T u = mdiv(U[1], rho);
-    T P = U[2] - rho * u * u;
-    T q = U[3] - rho * u * u * u - T(3) * u * P;
-    T r = U[4] - rho * u * u * u * u - T(6) * u * u * P - T(4) * u * q;
+    T u = mdiv2(U[1], rho);
+    T ru = rho * u;
+    T ruu = ru * u;
+    T P = fused ? dfma(-u, ru, U[2]) : U[2] - ruu;
+    T q = dfma(T(-3) * u, P, dfma(-u, ruu, U[3]));
+    T r = dfma(T(-4) * u, q, dfma(T(-6) * u * u, P, dfma(-u, ruu * u, U[4])));
     W[0] = rho; W[1] = u; W[2] = P; W[3] = q; W[4] = r;
   }
 
@@ -969,7 +972,7 @@ struct Sys5 {
   MX_HD static constexpr bool admissibility_var(int v) { return v == 0 || v == 2; }
   template <class T> MX_HD static bool admissible_cons(const T* U) {
     T rho = U[0];
-    T u = mdiv(U[1], rho);
+    T u = mdiv2(U[1], rho);
     T P = U[2] - rho * u * u;
     return rho > T(0) && P > T(0);
   }
@@ -977,9 +980,8 @@ struct Sys5 {
   template <class T> MX_HD static void scales(const T* W, T* sc) {
     T rho = tabs(W[0]);
     T p = tabs(W[2]);
-    T T0 = p * mrcp(rho);
-    T c = T0 * mrsqrt(T0);
-    sc[0] = rho; sc[1] = c; sc[2] = p; sc[3] = p * c; sc[4] = p * T0;
+    T c = msqrt2(mdiv2(p, rho));
+    sc[0] = rho; sc[1] = c; sc[2] = p; sc[3] = rho * c * c * c; sc[4] = sc[3] * c;
   }
 
   MX_HD static constexpr bool odd(int v, int) { return v == 1 || v == 3; }
@@ -988,10 +990,10 @@ struct Sys5 {
 
   template <class T> MX_HD static void core(const T* W, T sigma_lim, Core<T>& k) {
     k.rho = W[0];
-    T irho = mrcp(k.rho);
-    T ip = mrcp(W[2]);
-    k.c = msqrt(W[2] * irho);
-    T ic = msqrt(k.rho * ip);
+    T irho = mrcp2(k.rho);
+    T ip = mrcp2(W[2]);
+    k.c = msqrt2(W[2] * irho);
+    T ic = msqrt2(k.rho * ip);
     T is3 = irho * (ic * ic * ic);
     k.qh = W[3] * is3;
     T rh = W[4] * (is3 * ic);
@@ -1003,13 +1005,13 @@ struct Sys5 {
   }
 
   MX_HD static void core_mixed(const double* W, float sigma_lim, Core<float>& k) {
-    double ip = mrcp(W[2]);
+    double ip = mrcp2(W[2]);
     double A = 3.0 - W[4] * W[0] * ip * ip;
     k.rho = (float)W[0];
     float irho = 1.0f / k.rho;
     float ipf = (float)ip;
-    k.c = msqrt((float)W[2] * irho);
-    float ic = msqrt(k.rho * ipf);
+    k.c = msqrt2((float)W[2] * irho);
+    float ic = msqrt2(k.rho * ipf);
     float is3 = irho * (ic * ic * ic);
     k.qh = (float)W[3] * is3;
     k.A = (float)A;
@@ -1019,7 +1021,7 @@ struct Sys5 {
   }
 
   template <class T> MX_HD static T closing_s(const Core<T>& k) {
-    T ss = mdiv(k.qh * k.qh * k.qh, k.sb * k.sb) + (T(10) - T(8) * msqrt(k.sb)) * k.qh;
+    T ss = mdiv2(k.qh * k.qh * k.qh, k.sb * k.sb) + (T(10) - T(8) * msqrt2(k.sb)) * k.qh;
     T c2 = k.c * k.c;
     return ss * k.rho * (c2 * c2 * k.c);
   }
@@ -1038,51 +1040,62 @@ struct Sys5 {
     T sw = tmin(k.sb, T(1));
     BYEC<T> g = byec(sw, T(1));
     T base = T(4) * sw * sw * g.Y;
-    T i2s = mrcp(T(2) * sw);
+    T i2s = mrcp2(T(2) * sw);
     T Lmax = hyperbola(k.qh, T(-0.8) * k.qh * sw * g.C + base) * i2s + g.E;
     T Lmin = hyperbola(-k.qh, T(0.8) * k.qh * sw * g.C + base) * i2s + g.E;
     lmax = u + kws * Lmax * k.c;
     lmin = u - kws * Lmin * k.c;
   }
 
-  // dimensionless state in FP64: q*, T = P / rho, k_ws c, sigma_bar
-  template <class T> struct Norm { T qh, T0, kc; SigmaBar<T> s; };
-  template <class T> MX_HD static void norm(const T* W, T sigma_lim, T kws, Norm<T>& n) {
-    const T ip = mrcp(W[2]);
-    n.T0 = W[2] * mrcp(W[0]);
-    const T ic = mrsqrt(n.T0);
-    n.kc = kws * (n.T0 * ic);
-    n.qh = W[3] * (ip * ic);
-    sigma_bar(T(3) - W[4] * (W[0] * ip * ip), n.qh * n.qh, T(1), sigma_lim, n.s);
+  // ---- FP64 face state and CFL rate with their roundings fixed (single precision keeps the functions
+  // above)
+  template <class T> MX_HD static void tube_core(const T* W, T sigma_lim, Core<T>& k) {
+#pragma clang fp contract(off)
+    k.rho = W[0];
+    T irho = mrcp2(k.rho);
+    T ip = mrcp2(W[2]);
+    k.c = msqrt2(W[2] * irho);
+    T ic = msqrt2(k.rho * ip);
+    T is3 = irho * (ic * ic * ic);
+    k.qh = W[3] * is3;
+    T A = dfma(-W[4], is3 * ic, T(3));
+    T X = dfma(k.qh, T(8) * k.qh, A * A);
+    k.A = A;
+    k.sig = tube_sigma(A, X, T(2) * k.qh * k.qh, T(4));
+    k.sb = tmax(k.sig, sigma_lim);
   }
-  template <class T> MX_HD static void speeds(const Norm<T>& n, T u, T& lmin, T& lmax) {
-    SigmaFit<T> f;
-    sigma_fit(n.s.sb, n.s.rsb, n.s.isb, f);
-    // the 5-moment fit: pref = 1 / (2 sigma_w), P* = 1, no transverse heat flux
-    wave_roots<false>(f, T(0.5) * f.isw, T(0.8) * msqrt_pos(T(3) * f.om), n.qh, T(0), T(0), u, n.kc, lmin, lmax);
+  template <class T> MX_HD static void tube_speeds(const Core<T>& k, T u, T kws, T& lmin, T& lmax) {
+#pragma clang fp contract(off)
+    T sw = tmin(k.sb, T(1));
+    BYEC<T> g = byec(sw, T(1));
+    T hmax, hmin;
+    tube_roots(k.qh, sw, g.C, g.Y, hmax, hmin);
+    T i2s = mrcp2(T(2) * sw);
+    lmax = dfma(kws * dfma(i2s, hmax, g.E), k.c, u);
+    lmin = dfma(-(kws * dfma(i2s, hmin, g.E)), k.c, u);
   }
-
-  // U, F and the wave speeds of a face state (F is u U plus the terms above the previous
-  // moment's); closing moment s = q T (q*^2 / sigma^2 + 10 - 8 sqrt(sigma))
   template <int d, class T>
   MX_HD static void face_terms(const T* W, T sigma_lim, T kws, T* U, T* F, T& lmin, T& lmax) {
-    Norm<T> n;
-    norm(W, sigma_lim, kws, n);
-    const T u = W[1], P = W[2], q = W[3], r = W[4];
-    const T qs = n.qh * n.s.isb;
-    const T s = q * n.T0 * (qs * qs + T(10) - T(8) * n.s.rsb);
-    const T u2 = u * u;
-    U[0] = W[0];
-    U[1] = W[0] * u;
-    U[2] = U[1] * u + P;
-    U[3] = u * (U[2] + T(2) * P) + q;
-    U[4] = u * (u * (U[2] + T(5) * P) + T(4) * q) + r;
-    F[0] = U[1];
-    F[1] = U[2];
-    F[2] = U[3];
-    F[3] = U[4];
-    F[4] = u * U[4] + (u2 * (T(4) * (u * P) + T(6) * q) + (T(4) * (u * r) + s));
-    speeds(n, u, lmin, lmax);
+#pragma clang fp contract(off)
+    Core<T> k;
+    tube_core(W, sigma_lim, k);
+    const T rho = W[0], u = W[1], P = W[2], q = W[3], r = W[4];
+    // closing moment s = ss rho c^5
+    const T ss = dfma(k.qh, dfma(T(-8), msqrt2(k.sb), T(10)), mdiv2(k.qh * k.qh * k.qh, k.sb * k.sb));
+    const T c2 = k.c * k.c, c5 = c2 * c2 * k.c;
+    const T u2 = u * u, ru = rho * u, ru2 = rho * u2, ru4 = ru2 * u2;
+    F[0] = ru;
+    F[1] = dfma(rho, u2, P);
+    F[2] = dfma(T(3) * u, P, ru2 * u) + q;
+    F[3] = dfma(T(4) * u, q, dfma(T(6) * u2, P, ru4)) + r;
+    F[4] = dfma(c5, ss * rho, dfma(T(5) * u, r, dfma(T(10) * u2, q, dfma(ru4, u, T(10) * u2 * u * P))));
+    const T ruuu = ru * u * u;
+    U[0] = rho;
+    U[1] = ru;
+    U[2] = dfma(ru, u, P);
+    U[3] = dfma(T(3) * u, P, ruuu) + q;
+    U[4] = dfma(T(4) * u, q, dfma(T(6) * u * u, P, ruuu * u)) + r;
+    tube_speeds(k, u, kws, lmin, lmax);
   }
 
   template <int d>
@@ -1102,10 +1115,10 @@ struct Sys5 {
   }
 
   template <int d, class T> MX_HD static T cell_lambda(const T* W, T sigma_lim, T kws) {
-    Norm<T> n;
-    norm(W, sigma_lim, kws, n);
+    Core<T> k;
+    tube_core(W, sigma_lim, k);
     T lmin, lmax;
-    speeds(n, W[1], lmin, lmax);
+    tube_speeds(k, W[1], kws, lmin, lmax);
     return tmax(tabs(lmin), tabs(lmax));
   }
 
@@ -1118,14 +1131,29 @@ struct Sys5 {
   // 1D1V local Maxwellian: same rho, u, P; q = 0, r = 3 P^2 / rho
   template <class T> MX_HD static void equilibrium(const T* W, T* We) {
     We[0] = W[0]; We[1] = W[1]; We[2] = W[2]; We[3] = T(0);
-    We[4] = mdiv(T(3) * W[2] * W[2], W[0]);
+    We[4] = mdiv2(T(3) * W[2] * W[2], W[0]);
+  }
+
+  // its conserved moments (the implicit source)
+  template <class T> MX_HD static void equilibrium_cons(const T* W, T* U) {
+#pragma clang fp contract(off)
+    T We[NV];
+    equilibrium(W, We);
+    T rho = We[0], u = We[1], P = We[2];
+    T ru = rho * u, ruu = ru * u, ruuu = ruu * u;
+    U[0] = rho;
+    U[1] = ru;
+    U[2] = ruu + P;
+    U[3] = dfma(T(3) * u, P, ruuu);
+    U[4] = dfma(T(6) * u * u, P, ruuu * u) + We[4];
   }
 
   template <class T> MX_HD static void source(const T* W, T inv_tau, T* C) {
+#pragma clang fp contract(off)
     T rho = W[0], u = W[1], P = W[2], q = W[3], r = W[4];
     C[0] = C[1] = C[2] = T(0);
     C[3] = -q * inv_tau;
-    C[4] = -(T(4) * u * q + r - mdiv(T(3) * P * P, rho)) * inv_tau;
+    C[4] = -(dfma(T(4) * u, q, r) - mdiv2(T(3) * P * P, rho)) * inv_tau;
   }
 };
 

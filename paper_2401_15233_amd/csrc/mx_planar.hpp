@@ -326,7 +326,7 @@ struct Sys14P {
   }
   template <int d, class T>
   MX_HD static void speeds(const Norm<T>& n, const SigmaFit<T>& f, T ud, T& lmin, T& lmax) {
-    wave_pair<true>(f, cmax(n.Ph[pidx(d, d)], T(0)), n.h[d] * n.ic, tabs(n.h[1 - d]) * n.ic, ud, n.kc, lmin, lmax);
+    wave_pair(f, cmax(n.Ph[pidx(d, d)], T(0)), n.h[d] * n.ic, tabs(n.h[1 - d]) * n.ic, ud, n.kc, lmin, lmax);
   }
 
   // U, F_d and the wave speeds of a face state, as Sys14::face_terms.  About 430 FP64

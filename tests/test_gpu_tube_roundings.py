@@ -23,6 +23,7 @@ CASES = {
     'implicit': (14, dict(integrator='fe', source_implicit=True), 1e-5),
     'vanalbada': (14, dict(limiter='vanalbada', bc=('reflective',) * 4), 0.1),
     'rusanov': (14, dict(integrator='midpoint', flux='rusanov', tau_mode='const'), 0.1),
+    'five': (5, dict(), 0.01),
 }
 
 

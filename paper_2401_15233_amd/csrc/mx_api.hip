@@ -38,6 +38,7 @@ struct BatchState {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   hipGraphExec_t exec = nullptr;
   int graph_chunk = 0;
+  bool graph_reduced = false;            // the kernels (and the grid) captured: reduced or full
   bool graph_valid = false;
 };
 
@@ -1247,6 +1248,7 @@ static int batch_capture(maxent_solver* s, int chunk) {
   (void)hipGraphDestroy(g);
   if (e != hipSuccess) return fail(s, MAXENT_E_DEVICE, std::string("graph instantiate: ") + hipGetErrorString(e));
   b->graph_chunk = chunk;
+  b->graph_reduced = s->reduced();
   b->graph_valid = true;
   return MAXENT_OK;
 }
@@ -1258,7 +1260,8 @@ extern "C" int maxent_step_batch(maxent_solver* s, int max_steps, int chunk, max
   if (!s->ready) return fail(s, MAXENT_E_STATE, "step before a valid init_state");
   if (max_steps < 0 || chunk < 1 || chunk > 100000) return fail(s, MAXENT_E_INVAL, "bad max_steps or chunk");
   BatchState* b = s->batch;
-  if (!b->graph_valid || b->graph_chunk != chunk) {
+  // another state's symmetry (maxent_init_state) or mode (maxent_set_reduced) takes other kernels
+  if (!b->graph_valid || b->graph_chunk != chunk || b->graph_reduced != s->reduced()) {
     int rc = batch_capture(s, chunk);
     if (rc) return rc;
   }

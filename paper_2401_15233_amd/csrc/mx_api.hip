@@ -1,6 +1,7 @@
 // C-ABI runtime: handle, device buffers, argument validation, step sequencing.
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -444,15 +445,24 @@ static mx::IngestParams ingest_params(const maxent_solver* s, int repr, const do
   return g;
 }
 
-// whether kernels of the solver's device may read or write the caller's buffer in place:
-// device memory of that device (anything else goes through the staging buffer and a copy)
-static bool local_pointer(const maxent_solver* s, const void* p) {
+// whether kernels of the solver's device may read or write the caller's `bytes` at p in place: device
+// memory of that device, aligned as doubles, and all inside one allocation.  Anything else goes
+// through the staging buffer and a copy, which refuses a buffer that is too short.
+static bool local_pointer(const maxent_solver* s, const void* p, size_t bytes) {
   hipPointerAttribute_t a;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
   if (hipPointerGetAttributes(&a, p) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return a.type == hipMemoryTypeDevice && a.device == s->device;
+  if (a.type != hipMemoryTypeDevice || a.device != s->device || (uintptr_t)p % alignof(double) != 0) return false;
+  if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const size_t off = (size_t)((const char*)p - (const char*)base);
+  return off <= size && bytes <= size - off;
 }
 
 static int read_ctrl(maxent_solver* s) {
@@ -537,8 +547,8 @@ extern "C" int maxent_init_state(maxent_solver* s, int repr, const double* src, 
     return fail(s, MAXENT_E_INVAL, "repr must be PRIMITIVE or CONSERVED");
   if (!std::isfinite(t0)) return fail(s, MAXENT_E_INVAL, "t0 must be finite");
   free_tape(s, true);
-  if (!src_on_device || !local_pointer(s, src)) {
-    const size_t flat = (size_t)s->nv * s->prob.nx * s->prob.ny * sizeof(double);
+  const size_t flat = (size_t)s->nv * s->prob.nx * s->prob.ny * sizeof(double);
+  if (!src_on_device || !local_pointer(s, src, flat)) {
     HIP_TRY(s, hipMemcpyAsync(s->stage, src, flat,
                               src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
     src = s->stage;
@@ -781,11 +791,12 @@ extern "C" int maxent_get_moments(maxent_solver* s, int repr, double* dst, int d
   size_t comps = (size_t)s->nv;
   if (repr == MAXENT_SIGMA) comps = 1;
   if (repr == MAXENT_CLOSING) comps = s->nv == 14 ? MAXENT_CLOSING_COMPONENTS_14 : 1;
-  const bool direct = dst_on_device && local_pointer(s, dst);
+  const size_t bytes = comps * cells * sizeof(double);
+  const bool direct = dst_on_device && local_pointer(s, dst, bytes);
   HIP_TRY(s, mx::launch_egress(s->prob.system, repr, s->U, direct ? dst : s->stage, s->prob.nx, s->prob.ny,
                                s->pitch, s->num.sigma_lim, s->stream));
   if (!direct)
-    HIP_TRY(s, hipMemcpyAsync(dst, s->stage, comps * cells * sizeof(double),
+    HIP_TRY(s, hipMemcpyAsync(dst, s->stage, bytes,
                               dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(s, hipStreamSynchronize(s->stream));
   return MAXENT_OK;
@@ -943,7 +954,7 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
   HIP_TRY(s, mx::launch_adjoint_begin(t->actrl, t->part, n_part, s->stream));
   // lambda <- dJ/dU_final
   const size_t flat = (size_t)s->nv * nx * ny * sizeof(double);
-  if (!dJ_on_device || !local_pointer(s, dJ_dU)) {
+  if (!dJ_on_device || !local_pointer(s, dJ_dU, flat)) {
     HIP_TRY(s, hipMemcpyAsync(s->stage, dJ_dU, flat,
                               dJ_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
     dJ_dU = s->stage;
@@ -1060,7 +1071,7 @@ extern "C" int maxent_step_adjoint(maxent_solver* s, const double* dJ_dU, int dJ
   }
   HIP_TRY(s, mx::launch_adjoint_reduce(a, s->stream));
   if (dJ_dU0) {
-    const bool direct = dU0_on_device && local_pointer(s, dJ_dU0);
+    const bool direct = dU0_on_device && local_pointer(s, dJ_dU0, flat);
     HIP_TRY(s, mx::launch_pad_copy(lamA, direct ? dJ_dU0 : s->stage, s->nv, nx, ny, s->pitch, 0, s->stream));
     if (!direct)
       HIP_TRY(s, hipMemcpyAsync(dJ_dU0, s->stage, flat,

@@ -4,7 +4,7 @@ the library's hand-written discrete adjoint (maxent_step_adjoint) over the recor
 steps, with checkpointed recomputation; torch only holds device memory and streams."""
 import torch
 
-from .solver import MaxEntSolver
+from .solver import MaxentError, MaxEntSolver
 
 
 class MaxEntSteps(torch.autograd.Function):
@@ -23,9 +23,17 @@ class MaxEntSteps(torch.autograd.Function):
         if not isinstance(solver, MaxEntSolver):
             raise TypeError('solver must be a MaxEntSolver')
         p = params.detach().to('cpu', torch.float64)
-        # loading the state ends an earlier tape, whose buffers serve the next one
+        mach, rho = float(p[0]), float(p[1])
+        # values that the inflow refuses are reported before the state is touched; on an earlier
+        # tape's steps (STATE) it is set once the load has ended that tape, whose buffers then
+        # serve the next one
+        try:
+            solver.set_inflow(mach, rho)
+        except MaxentError as e:
+            if e.status != 'STATE':
+                raise
         solver.init_state(U0.detach(), repr='conserved')
-        solver.set_inflow(float(p[0]), float(p[1]))
+        solver.set_inflow(mach, rho)
         solver.record(checkpoint_every, max(int(n), 1))
         solver.step(int(n), dt=float(dt), tau_ref=float(p[2]))
         ctx.solver = solver

@@ -628,7 +628,7 @@ __global__ __launch_bounds__(256) void adj_begin_kernel(DevCtrl* c, double* part
   if (k < n) part[k] = 0.0;
   if (k == 0) {
     DevCtrl z = {};
-    z.fail_step = 0x7fffffff;
+    z.fail_step = NO_FAILURE;
     *c = z;
   }
 }

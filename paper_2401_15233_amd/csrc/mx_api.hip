@@ -478,7 +478,7 @@ static void fill_info(const maxent_solver* s, const DevCtrl& c, maxent_info* inf
   info->dt_last = c.dt_last;
   info->steps = c.step[s->slot & 1];
   info->n_fallback = c.n_fallback;
-  info->fail_step = (c.fail_step == 0x7fffffff) ? 0 : c.fail_step;
+  info->fail_step = mx::reported_fail_step(c.fail_step);
   info->fail_code = c.status;
   info->n_fp64_states = c.n_fp64;
   info->n_face_states = c.n_states;

@@ -26,14 +26,23 @@ struct DevCtrl {
   double t[2];                   // time
   long long step[2];             // steps taken
   long long n_fallback;          // positivity fallbacks
+  long long fail_step;           // first failing step (1-based; 0: the loaded state; NO_FAILURE: none)
   int status;                    // bit 1 non-finite, bit 2 unrealizable
-  int fail_step;                 // first failing step (1-based; 0: the loaded state; INT_MAX: none)
   long long n_fp64;              // mixed precision: face states re-evaluated in FP64
   long long n_states;            // mixed precision: face states evaluated
   long long n_sigma_limited;     // cells with sigma < sigma_lim (set by the counting kernel)
   int asym_z, asym_y;            // set to 1 by the ingest kernel: a z-odd moment (u_z, P_xz, P_yz,
                                  // q_z) / a y-odd one (u_y, P_xy, P_yz, q_y) is non-zero somewhere
 };
+
+// Whether the step after `step` steps runs: no earlier one failed.  64 bits, as the count of steps:
+// a run of small tubes takes 2^31 steps in a few hours.
+constexpr long long NO_FAILURE = 0x7fffffffffffffffLL;
+__host__ __device__ constexpr bool step_runs(long long fail_step, long long step) { return fail_step > step; }
+// the failing step as the reports carry it (0: none)
+constexpr int reported_fail_step(long long fail_step) {
+  return fail_step == NO_FAILURE ? 0 : (fail_step < 0x7fffffff ? (int)fail_step : 0x7fffffff);
+}
 
 // 1D tiles: a workgroup of NT threads owns NT - 4 cells, so that the cells plus the two-cell
 // halo on each side (NT), the limiter items (NT - 2) and the faces (NT - 3) each take a single

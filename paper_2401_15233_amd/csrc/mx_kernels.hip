@@ -34,7 +34,7 @@ __device__ __forceinline__ double step_dt(const StageParams& p, int dim) {
   const DevCtrl* c = p.ctrl;
   const double t = c->t[p.slot & 1];
   double dt = 0.0;
-  if ((long long)c->fail_step > c->step[p.slot & 1]) {
+  if (step_runs(c->fail_step, c->step[p.slot & 1])) {
     if (p.dt_fixed > 0.0) {
       dt = p.dt_fixed;
     } else {
@@ -511,7 +511,8 @@ void stage_kernel(StageParams p) {
     if (sFlag[0]) {
       atomicOr(&p.ctrl->status, sFlag[0]);
       // this step's 1-based index, from whichever slot holds it
-      atomicMin(&p.ctrl->fail_step, (int)(p.head ? p.ctrl->step[p.slot & 1] + 1 : p.ctrl->step[(p.slot + 1) & 1]));
+      atomicMin((unsigned long long*)&p.ctrl->fail_step,
+                (unsigned long long)(p.head ? p.ctrl->step[p.slot & 1] + 1 : p.ctrl->step[(p.slot + 1) & 1]));
     }
     if (sFlag[1]) atomicAdd((unsigned long long*)&p.ctrl->n_fallback, (unsigned long long)sFlag[1]);
     if (PREC != 0) {
@@ -574,7 +575,7 @@ __global__ void ctrl_reset_kernel(DevCtrl* c, RatePart* rates, double t0) {
   if (threadIdx.x == 0) {
     DevCtrl z = {};
     z.t[0] = t0;
-    z.fail_step = 0x7fffffff;
+    z.fail_step = NO_FAILURE;
     *c = z;
   }
 }

@@ -272,6 +272,8 @@ int maxent_autotune_batch(maxent_solver* s, int trial_steps, int* threads, int* 
  *     limiter's selected variable and regime (a factor of 0 or 1 is constant), the
  *     positivity fallback, max(sigma, sigma_lim) (no derivative through sigma when the limit
  *     is active), min(sigma, 1) in the wave speeds, the clamped square roots, the HLL case.
+ *     (The reverse evaluates them again, in another order of operations: a state within
+ *     rounding of a kink may take its other side.)
  *   - Parameters: the jet Mach number and jet density of the JET boundary, and tau_ref (the
  *     derivative with respect to one tau_ref shared by all recorded steps, each step's source
  *     scaling as 1/tau_ref). */
@@ -298,7 +300,7 @@ int maxent_set_inflow(maxent_solver* s, double mach, double rho);
 int maxent_tape_info(maxent_solver* s, long long* n_steps, double* dt);
 
 /* What the reverse pass differentiates (default EXACT).
- *   MAXENT_ADJ_EXACT           the exact derivative of the discrete step (branch replayed).
+ *   MAXENT_ADJ_EXACT           the exact derivative of the discrete step (of the branches taken).
  *   MAXENT_ADJ_FROZEN_LIMITER  the same with each cell's common limiter factor held at its
  *                              forward value (no derivative through the limiter's selection).
  * Over long horizons the exact derivative of the common-limiter scheme grows without bound:

@@ -7,19 +7,20 @@
 // Its reverse runs as deterministic gather passes plus a reduction:
 //   0. prep (adj_prep_kernel, LDS tiles): primitives of every cell of the domain and its two
 //      ghost layers, and each cell's common limiter factor and the variable that selected it,
-//      per direction (the forward stage's values, bit for bit);
+//      per direction (by the formulas of the forward stage; the kernel of a 1D tube rounds them
+//      in an order of its own);
 //   1. faces, both directions in one launch (adj_face_kernel, two threads per face, one per
 //      face state):
 //      each thread takes the flux adjoint Fb = (mu_right - mu_left) / dx from the two
 //      adjacent cells (mu = mu_coef dt lam_out, zero in ghost cells), rebuilds its face state
 //      and evaluates its closure (kept for the reverse), wave speeds, flux and conserved
 //      state; the two threads exchange their wave speeds and the products Fb . F, Fb . U
-//      (lane shuffles), which is all the reverse of the HLL / Rusanov combination (branch
-//      replayed) needs besides the thread's own side; then each thread reverses closure, wave
-//      speeds, physical flux and conserved map of its own face state;
+//      (lane shuffles), which is all the reverse of the HLL / Rusanov combination (on the
+//      branch that these values take) needs besides the thread's own side; then each thread
+//      reverses closure, wave speeds, physical flux and conserved map of its own face state;
 //   2. extended cells (adj_cell_kernel): for every cell of the domain and its two ghost
 //      layers, gather the reverse of the limited reconstruction of the up to three stencil
-//      cells whose face states it feeds (limiter argmin, regime and fallback replayed);
+//      cells whose face states it feeds (limiter argmin, regime and fallback as the prep kernel found them);
 //   3. interior cells (adj_update_kernel): fold the ghost-cell adjoints back onto the cells
 //      they copy (transmissive, periodic, reflective with sign flips) or onto the jet
 //      parameters, add the reverse of the BGK source (and its tau_ref partial), map the
@@ -250,8 +251,9 @@ __device__ __forceinline__ void face_reverse(const AdjParams& a, long long f, bo
   } else {
     get_w<PL>(a, ext_idx<D, DIM>(a, cc, l), W);
   }
-  // forward face terms (Sys14::face_terms, step by step): the closure core and closing values
-  // are kept for the reverse below
+  // The forward face terms again, from the closure core and the closing values that the reverse
+  // below needs.  Sys14::face_terms forms the same quantities in another algebra, so they agree
+  // to rounding, and a branch (sigma_lim, HLL case) is decided here by these values, not replayed.
   Sys14::Core<double> k;
   Sys14::core(W, p.sigma_lim, k);
   double Qd[6], Rd[3], Sd;

@@ -122,7 +122,7 @@ __global__ __launch_bounds__(1024) void batch_finalize_kernel(BatchInst* in, con
 // finds its first tile by a binary search over the tile prefix and then walks forward.
 //
 // Bound by FP64 VALU work; a workgroup reduces status, counters and CFL rate once for the tiles of an
-// instance in its range instead of for each tile.  512 tubes of 512 to 32768 cells (4.0 M cells, 256
+// instance in its range instead of for each tile.  512 tubes of 512 to 32768 cells (4.3 M cells, 256
 // threads), 20 steps with load and read: 13.3 ms (a reduction per tile, and the CFL rate of the
 // loaded field in a pass of its own: 18.2).  A variant that kept the thread's own cell, U^n and the
 // next tile's cell in registers across the faces spilled 25 of 168 registers and took 15.4 ms.
@@ -201,7 +201,7 @@ void batch_stage_kernel(BatchParams p) {
   int n64 = 0, nfb = 0;
   for (int k = k0; k < k1; ++k) {
     const double dt = cur.dt;
-    // (issue priority by phase as in the single kernel: 9.54 -> 9.47 ms)
+    // (issue priority by phase as in the single kernel: 14.0 -> 13.3 ms, mixed 12.4 -> 11.4)
     __builtin_amdgcn_s_setprio(3);
     // 1. tile + halo -> primitives
 #pragma unroll 1

@@ -9,7 +9,8 @@ namespace mx {
 // Device-resident control block: time step, time and status live on the device so that a
 // sequence of steps needs no host round trip, and every step's first stage launch works out the
 // step's dt itself (no launch of its own: the separate one-wavefront kernel that did it cost 2 to
-// 4 us and a launch gap per step, 9.9 us against 5.9 for a step of 1000 cells).  What a step
+// 4 us and a launch gap per step: 9.9 us against 5.9 for a first-order step of 1000 5-moment cells,
+// with the face algebra of that time).  What a step
 // reads and what it leaves for the next one stand in different slots, picked by the host's step
 // counter `slot`, because the workgroups of one launch read and write in any order:
 //   t, step      read from [slot & 1], written to [(slot + 1) & 1] by one workgroup of the first
@@ -111,10 +112,10 @@ __device__ __forceinline__ double stage_update(int mode, double cdt, double dt, 
 // The maximum CFL rate, in RATE_PARTS parts on cache lines of their own: device-wide atomics on
 // one address take their turn (about 25 ns each), and the workgroups of a small grid end
 // together.  A workgroup raises the part of its index; every wavefront of the next step's first
-// stage reads them all and takes the largest.  A step of 800 1D tiles: one word 18.4 us (5
-// moments) and 20.3 (7), 64 parts 13.6 and 16.7, 16 parts 12.8 and 16.0; on large grids 64 lines
-// per wavefront cost as much L2 traffic as the tile (2048 x 2048 2 per cent slower), 16 nothing
-// that can be measured.
+// stage reads them all and takes the largest.  A step of 800 1D tiles: one word 19.1 us (5
+// moments) and 23.1 (7), 16 parts 15.0 and 20.0 (64 parts 0.7 to 0.8 more than 16); on large grids
+// 64 lines per wavefront cost as much L2 traffic as the tile (2048 x 2048 2 per cent slower), 16
+// nothing that can be measured.
 constexpr int RATE_PARTS = 16;   // one row of lanes reads them
 struct alignas(128) RatePart {
   unsigned long long rate[3];    // bit patterns of non-negative doubles, a slot of the step each

@@ -12,9 +12,9 @@
 //   4. updates each cell with the flux differences and the BGK source at the cell centre,
 //      writes the result, checks it (non-finite, rho <= 0, P not SPD) and, in the last
 //      stage of a step, reduces the CFL rate of the new state for the next step.
-// The 2D tile is 16 x 15 cells for 256 threads: 255 x-faces and 256 y-faces, one of each
-// per thread.  The 1D tile is 60 cells for one 64-wide wavefront: cells plus halo fill the
-// wavefront exactly.
+// The 2D tile is 16 x 15 cells: 255 x-faces and 256 y-faces, one of each for 256 threads.  The 1D
+// tile is 60 cells: cells plus halo fill one 64-wide wavefront exactly.  Small FP64 grids run
+// the same tiles with twice the threads (512 in 2D, 128 in 1D) and two lanes per face.
 #include <algorithm>
 
 #include "mx_internal.hpp"
@@ -85,14 +85,15 @@ __device__ __forceinline__ double field_rate(const double* W, double sigma_lim, 
 // One stage of a tile: primitives of the tile and its halo in LDS, limiter factors, face fluxes,
 // update, checks and (last stage) the CFL rate of the new state.  Bound by FP64 VALU work; the
 // planar system runs 3200 VALU instructions per cell and stage on large grids at 84 per cent
-// of the issue rate (2048 x 2048: 0.46 ms first stage, 0.53 ms second).  LPF lanes share a face:
-// one, or (grids that leave the chip partly idle, where a tile's latency is the time of the
+// of the issue rate (2048 x 2048 developed crossed jets: 0.45 to 0.47 ms per launch, the mean of both
+// stages, over runs and cards).  LPF lanes share a face: one, or (grids that leave the chip partly idle, where a tile's latency is the time of the
 // stage) two, each with the state of one side, in twice as many threads.
 //
 // Waves per SIMD the kernel is compiled for.  Planar 2D (ten moments), one lane per face: three
 // 256-thread workgroups per CU fit in LDS (52 KB each), so three, which caps the kernel at 168
-// VGPRs without spills.  Two lanes per face: a 512-thread workgroup is two waves per SIMD, and
-// four (two workgroups per CU) still leave it the 128 VGPRs it needs.
+// VGPRs (no spills at second order, two registers at first).  Two lanes per face: a 512-thread
+// workgroup is two waves per SIMD, and four (two workgroups per CU) cap it at 128 VGPRs: the
+// planar kernel uses 114, the one with all 14 moments spills 20 (first order 18).
 constexpr int stage_min_waves(int nv, int dim, int lanes) {
   if (dim == 1) return 1;
   return lanes == 2 ? 4 : (nv <= 10 ? 3 : 1);
@@ -166,8 +167,9 @@ void stage_kernel(StageParams p) {
   const long long off = (long long)gj * p.pitch + gi;
   // The step's dt, and whether there is anything to do.  Two lanes per face (small grids): asked
   // for after the tile's loads are on their way, so that the latency of the control block and
-  // that of the tile overlap (with the early update inputs below, 1000 cells of 5 moments 12.1 ->
-  // 11.3 us per step); otherwise before, so that an idle step on a large grid reads no field.
+  // that of the tile overlap (with the early update inputs below, 1000 cells with 14 moments 18.9 ->
+  // 18.3 us per step; the tubes' kernels are as fast either way at 1000 cells, 12.9 and 16.2, and 2 per
+  // cent slower at 96000); otherwise before, so that an idle step on a large grid reads no field.
   double dt;
   auto begin = [&]() {
     if (p.dt_replay > 0.0) {
@@ -778,12 +780,13 @@ static hipError_t launch_stage_l(const StageParams& p, hipStream_t s) {
 // Tiles up to which two lanes share a face: while the doubled workgroups all run at once.  2D
 // planar: two 512-thread workgroups on each of the 256 CUs (two stages and their gaps, one
 // lane -> two: 64 x 64 30.2 -> 27.0 us, 224 x 224 30.9 -> 27.8, 320 x 320 41.1 -> 40.9; beyond,
-// 352 x 352 50.7 -> 55.5, 768 x 768 159 -> 170).  2D with all 14 moments: one (76 KB of LDS each and
-// twice the registers; 64 x 64 36.6 -> 34.5, 192 x 192 37.2 -> 36.1, but 256 x 256 50.2 -> 54.1).
-// 1D: two-wave workgroups, four waves per SIMD of the 1024 with seven moments or fewer (1000
-// cells of 5 moments 12.2 -> 11.3, 96000 17.6 -> 16.5, 192000 22.7 -> 23.6; axial 14.6 -> 13.5,
-// 23.0 -> 21.3, 29.8 -> 34.8), two with 14 (1000 cells 20.3 -> 18.4, 48000 24.1 -> 23.5, but 64000
-// 29.7 -> 35.7).
+// 352 x 352 50.7 -> 55.5, 768 x 768 159 -> 170).  2D with all 14 moments: one on each CU (two would
+// fit as well, but then one lane is faster: 64 x 64 36.6 -> 34.5, 192 x 192 37.2 -> 36.1, but 256 x
+// 256 50.2 -> 54.1).  1D: two-wave workgroups, four waves per SIMD of the 1024 with seven moments or
+// fewer, which is what the axial kernel's 128 registers allow (1000 cells of 5 moments 14.0 -> 12.9,
+// 96000 21.0 -> 19.5, and in 20 first-order steps with load and read 140000 325 -> 319 but 160000 333
+// -> 366; axial 18.4 -> 16.2, 27.8 -> 26.8, 20 steps of 112000 643 -> 640 but 140000 750 -> 793),
+// two with 14 (1000 cells 20.5 -> 18.3, 48000 24.2 -> 22.8, but 64000 29.7 -> 35.7).
 constexpr int two_lane_tiles(int nv, int dim) {
   if (dim == 1) return nv <= 7 ? 2048 : 1024;
   return nv <= 10 ? 512 : 256;

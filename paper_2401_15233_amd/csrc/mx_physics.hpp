@@ -86,7 +86,7 @@ template <> MX_HD float tabs<float>(float a) { return __builtin_fabsf(a); }
 // a r, which squares that error.  The square root: one step of the coupled iteration on
 // g ~ sqrt(a), h ~ 1/(2 sqrt(a)) (1e-15), then a residual correction of g.  Each gives the
 // correctly rounded result on those samples (1.11e-16 relative at most), as the sequences with
-// one more iteration did that stood here before, in one (1/b), two (a/b) and three (sqrt)
+// one more iteration do (mrcp2 and its kin), in one (1/b), two (a/b) and three (sqrt)
 // instructions less.  The arguments of the step (densities, pressures, determinants, positive
 // sums) are positive and far from the exponent range's ends; sqrt(0) = 0 is kept, and a
 // negative, zero-divisor or non-finite argument still gives a non-finite result, which the

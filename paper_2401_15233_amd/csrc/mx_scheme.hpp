@@ -7,6 +7,9 @@
 //                   the approximate wave speeds (Section 3.1)
 #pragma once
 #include "mx_physics.hpp"
+#if defined(__HIP_DEVICE_COMPILE__)
+#include "mx_internal.hpp"
+#endif
 
 namespace mx {
 
@@ -216,12 +219,7 @@ MX_HD void face_flux(const T* WL, const T* WR, T sigma_lim, T kws, int flux_kind
 
 #if defined(__HIP_DEVICE_COMPILE__)
 // a value of the neighbouring lane (lane ^ 1)
-__device__ __forceinline__ double lane_xor1(double x) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_mov_dpp((int)b, 0xB1, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0xB1, 0xf, 0xf, true);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
+__device__ __forceinline__ double lane_xor1(double x) { return dpp_move<0xB1>(x); }
 #else
 __device__ inline double lane_xor1(double x) { return x; }
 #endif
